@@ -274,14 +274,9 @@ def _run_forward(s, case, ctx):
     return out
 
 
-def _image_loss(rgb, dep, alpha, t_rgb, t_dep, sizes):
-    """What a torch training loop computes on the images: L1 colour, depth and a silhouette term, per view."""
-    loss, at = 0.0, 0
-    for p in sizes:
-        loss = loss + ((rgb[3 * at:3 * (at + p)] - t_rgb[3 * at:3 * (at + p)]).abs().sum()
-                       + 0.5 * (dep[at:at + p] - t_dep[at:at + p]).abs().sum() + 0.1 * (1.0 - alpha[at:at + p]).square().sum()) / p
-        at += p
-    return loss
+def _image_loss(rgb, dep, alpha, t_rgb, t_dep, p):
+    """What a torch training loop computes on the images: L1 colour, depth and a silhouette term; p pixels a view."""
+    return ((rgb - t_rgb).abs().sum() + 0.5 * (dep - t_dep).abs().sum() + 0.1 * (1.0 - alpha).square().sum()) / p
 
 
 def _run_step(s, case, ctx):
@@ -289,7 +284,7 @@ def _run_step(s, case, ctx):
     if case["api"] == "autograd":
         leaf = {k: v.detach().requires_grad_(k in GRADS) for k, v in g.items()}
         rgb, dep, alpha, _ = raster.rasterize(ctx, leaf, cams, s["S"])
-        loss = _image_loss(rgb, dep, alpha, t_rgb, t_dep, [c["width"] * c["height"] for c in cams])
+        loss = _image_loss(rgb, dep, alpha, t_rgb, t_dep, case["width"] * case["height"])
         loss.backward()
         return {"rgb": rgb.detach(), "depth": dep.detach(), "alpha": alpha.detach(), "grads": {k: leaf[k].grad for k in GRADS if k in g}}
     for t in s["grads"].values():
@@ -470,7 +465,7 @@ def _exact_step(case, seed):
         at += p
         im = img.clone().requires_grad_()
         if case["api"] == "autograd":
-            loss = _image_loss(im[:3].reshape(-1), im[3], im[4], tr.reshape(-1), td, [p])
+            loss = _image_loss(im[:3], im[3], im[4], tr, td, p)
         elif case["loss"] == "l1":
             loss = ((im[:3] - tr).abs().sum() + 0.5 * (im[3] - td).abs().sum()) / p
         else:
