@@ -424,20 +424,21 @@ rtg_status rtg_region_utility(rtg_ctx *ctx, int64_t n, const float *means, const
  * planar 3 x n_points; collide: device, n_points int32 (required);
  * clearance: device, n_points floats or NULL.  Only g->means and
  * g->log_scales are read.  r_robot, lambda_g: finite and >= 0 (the paper
- * uses lambda_g = 3).  Every point is tested against every Gaussian (no
- * spatial index).  Asynchronous on `stream`. */
+ * uses lambda_g = 3).  The results are those of testing every point against
+ * every Gaussian; the time falls with how close together the points lie that
+ * follow each other in space.  Asynchronous on `stream`. */
 rtg_status rtg_collision_check(rtg_ctx *ctx, const rtg_gaussians *g, const float *points,
                                int64_t n_points, float r_robot, float lambda_g, int32_t *collide,
                                float *clearance, void *stream);
 
 /* rtg_collision_check for callers that cannot allocate device memory (code
  * under hipGraph capture, tight planning loops, hosts that forbid
- * allocation): the same check and results, with its scratch (24 bytes per
- * Gaussian + 4 per point, each part 256-byte aligned) taken from a fixed
+ * allocation): the same check and results, with its scratch taken from a fixed
  * 96 MiB device array that every GPU the library runs on holds from the
  * library's load until the process ends; it calls no hipMalloc, hipFree or
- * allocating routine.  Larger inputs return RTG_ERR_UNSUPPORTED before any
- * launch (use rtg_collision_check).  All calls on one GPU share that array:
+ * allocating routine.  Inputs of more than 96 MiB at 24 bytes per Gaussian +
+ * 4 per point (each part 256-byte aligned) return RTG_ERR_UNSUPPORTED before
+ * any launch (use rtg_collision_check).  All calls on one GPU share that array:
  * calls that overlap on one GPU (several streams, threads or contexts) race,
  * so the caller must order them.  The caller still passes the inputs and
  * outputs, as for rtg_collision_check. */

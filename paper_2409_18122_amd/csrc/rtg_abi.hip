@@ -1587,12 +1587,9 @@ rtg_status rtg_collision_check(rtg_ctx* ctx, const rtg_gaussians* g, const float
     RTG_TRY(collision_args(g, points, n_points, r_robot, lambda_g, collide));
     if (n_points == 0) return RTG_OK;
     hipStream_t s = (hipStream_t)stream;
-    Buf packed, bound, key;
-    RTG_TRY(packed.ensure(ctx, sizeof(float4) * (size_t)std::max<int64_t>(g->n, 1)));
-    RTG_TRY(bound.ensure(ctx, sizeof(float2) * (size_t)std::max<int64_t>(g->n, 1)));
-    RTG_TRY(key.ensure(ctx, sizeof(uint32_t) * (size_t)n_points));
-    collision_check(to_dev(*g), points, n_points, r_robot, lambda_g, packed.as<float4>(), bound.as<float2>(), collide,
-                    key.as<uint32_t>(), clearance, s);
+    Buf ws;
+    RTG_TRY(ws.ensure(ctx, collision_ws_bytes(n_points)));
+    collision_check(to_dev(*g), points, n_points, r_robot, lambda_g, ws.p, collide, clearance, s);
     return check_launch("collision check");
 }
 
@@ -1601,12 +1598,10 @@ rtg_status rtg_collision_check_noalloc(rtg_ctx* ctx, const rtg_gaussians* g, con
                                        void* stream) {
     RTG_TRY(ctx_ok(ctx));
     RTG_TRY(collision_args(g, points, n_points, r_robot, lambda_g, collide));
-    // the same three scratch arrays as rtg_collision_check, carved from the
-    // fixed array: packed (16 B per Gaussian), bound (8 B), clear_key (4 B
-    // per point); the kernels write all of them before reading them
+    // the documented limit on the inputs (24 bytes per Gaussian + 4 per
+    // point); the check's own scratch is smaller
     const size_t n = (size_t)g->n, np = (size_t)n_points;
-    const size_t off_bound = align256(16 * n), off_key = off_bound + align256(8 * n);
-    const size_t need = off_key + align256(4 * np);
+    const size_t need = align256(16 * n) + align256(8 * n) + align256(4 * np);
     if (need > SCRATCH_BYTES)
         return set_err(RTG_ERR_UNSUPPORTED,
                        "%lld Gaussians and %lld points need %zu bytes of scratch, above the fixed %zu "
@@ -1618,10 +1613,10 @@ rtg_status rtg_collision_check_noalloc(rtg_ctx* ctx, const rtg_gaussians* g, con
         RTG_TRY(scratch_address(ctx->device, &p));
         ctx->scratch = p;
     }
-    unsigned char* base = static_cast<unsigned char*>(ctx->scratch);
-    collision_check(to_dev(*g), points, n_points, r_robot, lambda_g, reinterpret_cast<float4*>(base),
-                    reinterpret_cast<float2*>(base + off_bound), collide, reinterpret_cast<uint32_t*>(base + off_key),
-                    clearance, (hipStream_t)stream);
+    if (collision_ws_bytes(n_points) > SCRATCH_BYTES)
+        return set_err(RTG_ERR_UNSUPPORTED, "collision scratch exceeds the fixed array");
+    collision_check(to_dev(*g), points, n_points, r_robot, lambda_g, ctx->scratch, collide, clearance,
+                    (hipStream_t)stream);
     return check_launch("collision check (fixed scratch)");
 }
 

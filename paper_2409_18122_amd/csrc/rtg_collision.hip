@@ -13,55 +13,296 @@ namespace rtg {
 
 namespace {
 
-inline unsigned grid_cap(uint64_t n, unsigned block, unsigned cap) {
-    uint64_t g = (n + block - 1) / block;
-    if (g < 1) g = 1;
-    if (g > cap) g = cap;
-    return (unsigned)g;
-}
-
 // Sec. IV-B (trajectory planner, Collision Checking): a sampled point (a
 // sphere of radius r_robot) collides with a Gaussian whose mean is closer than r_robot + lambda_g r, r = the Gaussian's
-// principal axis exp(max log-scale).  Every point against every Gaussian:
-// a prep pass packs each Gaussian as (mu, w = lambda_g r) plus the squared
-// bound (r_robot + w)^2 widened down and up by a relative CC_BAND; the pair
-// loop stages them through LDS in tiles and decides in binary32 outside the
-// band, in binary64 (from the original parameters, in the oracle's order)
-// inside it.  The clearance min_i (||p - mu_i|| - w_i) is binary32 (the
-// hardware square root, within an ulp).
+// principal axis exp(max log-scale); the clearance is min_i (||p - mu_i|| - w_i), w_i = lambda_g r_i.
+//
+// Two things bound the check: reading the map once, and the pair tests.  Testing every pair of a
+// 3M-Gaussian map with 8,256 points is 2.5e10 pairs (7.5 ms at the FP32 vector rate), but a
+// Gaussian can matter to a point only if it lies within the point's clearance.  So:
+//   k_cc_points puts the points of a batch in spatial order and covers every 64 of them (one per
+//     lane) with a ball (c, R);
+//   k_cc_bound gives every point an upper bound of its clearance from a strided sample of the map;
+//   k_cc_check streams the map once per slab of points: a lane takes a Gaussian and tests it against the
+//     balls; one that is nearer to c than R + w + the largest bound of the group's points is tested
+//     against the group's 64 points, a point per lane.
+// What is left out is further from all 64 points than a clearance that some pair reaches, so it
+// neither sets a minimum nor (where the clearance is below r_robot, that pair collides itself) a
+// flag: the results do not depend on the grouping.  Points far apart or in no order cost
+// more tests, at worst all pairs.
+// Flags are decided in binary32 outside a relative CC_BAND of the bound, inside it in
+// binary64 (from the original parameters, in the oracle's order).  A clearance is a minimum of
+// binary32 values (the hardware square root, within an ulp), the same in every order.
 
-constexpr int CC_THREADS = 256;
-constexpr int CC_TILE = 1024;            // Gaussians per LDS tile
-constexpr double CC_BAND = 4e-6;         // relative band re-taken in binary64 (d^2 error < 4e-7)
+constexpr float CC_BAND = 5e-6f;  // relative band re-taken in binary64 (errors of d^2 and of the bound below 8e-7)
+constexpr float CC_INF = __builtin_inff();
 
-__device__ __forceinline__ uint32_t ordered_key(float f) {
-    const uint32_t b = __float_as_uint(f);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+// Points of a batch (one block of k_cc_points) and their spatial order: 2^CP_BITS bins, the box
+// halved along its longest side each time, so that bins stay near cubes for points on a
+// plane or a line too.
+constexpr int CP_THREADS = 1024;
+constexpr int CP_IPT = 4;
+constexpr int CP_BATCH = CP_THREADS * CP_IPT;
+constexpr int CP_BITS = 12;
+constexpr int CP_BINS = 1 << CP_BITS;
+constexpr int CP_BPT = CP_BINS / CP_THREADS;
+
+// k_cc_check: a block holds a slab of up to CK_GROUPS groups of 64 points in LDS and takes
+// CK_THREADS Gaussians a step.
+constexpr int CK_THREADS = 768;
+constexpr int CK_GROUPS = 44;
+constexpr int CK_UNROLL = 4;  // balls tested per branch
+
+// Sorted points of one call, planar; index: the point's place in the caller's arrays.  Places past a
+// batch's finite points hold NaN coordinates, which no comparison passes.
+struct CcPoints {
+    float *x, *y, *z;
+    uint32_t* index;
+    float4 *ball, *sub;  // per 64 and per 8 points: centre, radius (NaN centre: no finite point)
+};
+
+// Minimum of *p and v (v never -0: then +0 would not order below negative bits).  Binary32
+// values order as their bits do, negative ones in reverse.
+__device__ __forceinline__ void atomic_min_float(float* p, float v) {
+    if (v >= 0.0f) atomicMin(reinterpret_cast<int*>(p), __float_as_int(v));
+    else atomicMax(reinterpret_cast<unsigned*>(p), __float_as_uint(v));
 }
-__device__ __forceinline__ float ordered_val(uint32_t k) {
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+
+__device__ __forceinline__ float wave_min(float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
+    return v;
+}
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    return v;
 }
 
-// packed[i] = (mu, w); bound[i] = ((r_robot + w)^2 (1 - band), (r_robot + w)^2 (1 + band)), both
-// formed in binary64 and rounded once.  Non-finite Gaussians: NaN mean (every comparison false), w 0.
-__global__ __launch_bounds__(256) void k_collision_prep(GaussDev g, float r_robot, float lambda_g,
-                                                        float4* __restrict__ packed, float2* __restrict__ bound) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float m0 = g.means[i], m1 = g.means[g.n + i], m2 = g.means[2 * g.n + i];
-        const float l0 = g.log_scales[i], l1 = g.log_scales[g.n + i], l2 = g.log_scales[2 * g.n + i];
-        const bool ok = isfinite(m0) && isfinite(m1) && isfinite(m2) && isfinite(l0) && isfinite(l1) && isfinite(l2);
-        const double w = (double)lambda_g * exp((double)fmaxf(fmaxf(l0, l1), l2));
-        const double gm = (double)r_robot + w;
-        const double g2 = gm * gm;
-        const float nan = __uint_as_float(0x7fc00000u);
-        packed[i] = ok ? make_float4(m0, m1, m2, (float)w) : make_float4(nan, nan, nan, 0.0f);
-        bound[i] = ok ? make_float2((float)(g2 * (1.0 - CC_BAND)), (float)(g2 * (1.0 + CC_BAND)))
-                      : make_float2(0.0f, 0.0f);
+// One Gaussian's mean and w = lambda_g r, formed in binary64 and rounded once; an ignored one (a
+// non-finite mean or log-scale) gets a NaN mean, which no comparison passes.
+__device__ __forceinline__ float4 cc_gauss(const float (&v)[6], float lambda_g) {
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < 6; k++) ok = ok && isfinite(v[k]);
+    const double w = (double)lambda_g * exp((double)fmaxf(fmaxf(v[3], v[4]), v[5]));
+    return make_float4(ok ? v[0] : __builtin_nanf(""), v[1], v[2], (float)w);
+}
+
+// Block b orders the points [b per, (b + 1) per) of the caller's planar arrays (stride np_all) and
+// clears their results.  One block per batch: a counting sort over the bins in LDS; the order within a
+// bin is arbitrary, and nothing depends on it.
+__global__ __launch_bounds__(CP_THREADS) void k_cc_points(const float* __restrict__ pts, int64_t np_all, int np,
+                                                          int per, CcPoints P, int32_t* __restrict__ collide,
+                                                          float* __restrict__ clearance) {
+    __shared__ uint32_t hist[CP_BINS];
+    __shared__ float s_lo[3][CP_THREADS / 64], s_hi[3][CP_THREADS / 64];
+    __shared__ uint32_t s_w[CP_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int begin = blockIdx.x * per, end = min(begin + per, np);
+    for (int i = tid; i < CP_BINS; i += CP_THREADS) hist[i] = 0;
+    float x[CP_IPT][3];
+    uint32_t live = 0;
+    float lo[3] = {CC_INF, CC_INF, CC_INF}, hi[3] = {-CC_INF, -CC_INF, -CC_INF};
+#pragma unroll
+    for (int k = 0; k < CP_IPT; k++) {
+        const int i = begin + tid + k * CP_THREADS;
+#pragma unroll
+        for (int a = 0; a < 3; a++) x[k][a] = i < end ? pts[a * np_all + i] : 0.0f;
+        if (i >= end) continue;
+        collide[i] = 0;
+        if (clearance) clearance[i] = CC_INF;
+        if (!(isfinite(x[k][0]) && isfinite(x[k][1]) && isfinite(x[k][2]))) continue;
+        live |= 1u << k;
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            lo[a] = fminf(lo[a], x[k][a]);
+            hi[a] = fmaxf(hi[a], x[k][a]);
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        lo[a] = wave_min(lo[a]);
+        hi[a] = wave_max(hi[a]);
+        if (lane == 0) {
+            s_lo[a][wv] = lo[a];
+            s_hi[a][wv] = hi[a];
+        }
+    }
+    __syncthreads();
+    float size[3], scale[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        for (int w = 0; w < CP_THREADS / 64; w++) {
+            lo[a] = fminf(lo[a], s_lo[a][w]);
+            hi[a] = fmaxf(hi[a], s_hi[a][w]);
+        }
+        // an extent of 0 or beyond binary32 is not split
+        size[a] = hi[a] - lo[a];
+        if (!(size[a] > 0.0f && size[a] < 1e38f)) size[a] = 0.0f;
+        scale[a] = size[a] > 0.0f ? 1.0f / size[a] : 0.0f;
+    }
+    // the halvings, first to last: axis of split s in bits 2 s of `axes`; levels per axis
+    uint32_t axes = 0;
+    int lev[3] = {0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < CP_BITS; s++) {
+        const int a = size[0] >= size[1] ? (size[0] >= size[2] ? 0 : 2) : (size[1] >= size[2] ? 1 : 2);
+        axes |= (uint32_t)a << (2 * s);
+#pragma unroll
+        for (int b = 0; b < 3; b++)
+            if (b == a) {
+                size[b] *= 0.5f;
+                lev[b]++;
+            }
+    }
+    uint32_t bin[CP_IPT], rank[CP_IPT];
+#pragma unroll
+    for (int k = 0; k < CP_IPT; k++) {
+        bin[k] = rank[k] = 0;
+        if (!((live >> k) & 1u)) continue;
+        uint32_t q[3];
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            const float cells = (float)(1u << lev[a]);
+            // cell within the axis, its bits left-aligned so that each split takes the next one
+            const uint32_t c = (uint32_t)fminf((x[k][a] - lo[a]) * scale[a] * cells, cells - 1.0f);
+            q[a] = c << (CP_BITS - lev[a]);
+        }
+        uint32_t code = 0;
+#pragma unroll
+        for (int s = 0; s < CP_BITS; s++) {
+            const uint32_t a = (axes >> (2 * s)) & 3u;
+            const uint32_t qa = a == 0 ? q[0] : a == 1 ? q[1] : q[2];
+            code = 2 * code + ((qa >> (CP_BITS - 1)) & 1u);
+            q[0] = a == 0 ? q[0] << 1 : q[0];
+            q[1] = a == 1 ? q[1] << 1 : q[1];
+            q[2] = a == 2 ? q[2] << 1 : q[2];
+        }
+        bin[k] = code;
+        rank[k] = atomicAdd(&hist[code], 1u);
+    }
+    __syncthreads();
+    // exclusive scan of the bins, CP_BPT consecutive ones per thread
+    uint32_t c[CP_BPT], mine = 0;
+#pragma unroll
+    for (int j = 0; j < CP_BPT; j++) {
+        c[j] = hist[tid * CP_BPT + j];
+        mine += c[j];
+    }
+    uint32_t inc = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) s_w[wv] = inc;
+    __syncthreads();
+    uint32_t run = inc - mine, total = 0;
+    for (int w = 0; w < CP_THREADS / 64; w++) {
+        if (w < wv) run += s_w[w];
+        total += s_w[w];
+    }
+#pragma unroll
+    for (int j = 0; j < CP_BPT; j++) {
+        hist[tid * CP_BPT + j] = run;
+        run += c[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CP_IPT; k++) {
+        if (!((live >> k) & 1u)) continue;
+        const uint32_t at = (uint32_t)begin + hist[bin[k]] + rank[k];
+        P.x[at] = x[k][0];
+        P.y[at] = x[k][1];
+        P.z[at] = x[k][2];
+        P.index[at] = (uint32_t)(begin + tid + k * CP_THREADS);
+    }
+    const float nan = __builtin_nanf("");
+    for (uint32_t i = total + tid; i < (uint32_t)per; i += CP_THREADS) {
+        P.x[begin + i] = nan;
+        P.y[begin + i] = nan;
+        P.z[begin + i] = nan;
+        P.index[begin + i] = 0;
+    }
+    __syncthreads();  // the block's own stores are read below
+    for (int gr = wv; gr < per / 64; gr += CP_THREADS / 64) {
+        const int at = begin + gr * 64 + lane;
+        const bool in = (uint32_t)(gr * 64 + lane) < total;
+        const float p0 = P.x[at], p1 = P.y[at], p2 = P.z[at];
+        float mn[3] = {in ? p0 : CC_INF, in ? p1 : CC_INF, in ? p2 : CC_INF};
+        float mx[3] = {in ? p0 : -CC_INF, in ? p1 : -CC_INF, in ? p2 : -CC_INF};
+        // the ball over the 2^level lanes around this one (no points: inf - inf gives NaN)
+        auto ball = [&](int from, int to) {
+            for (int o = from; o < to; o <<= 1)
+#pragma unroll
+                for (int a = 0; a < 3; a++) {
+                    mn[a] = fminf(mn[a], __shfl_xor(mn[a], o, 64));
+                    mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], o, 64));
+                }
+            float4 c = make_float4(0.5f * mn[0] + 0.5f * mx[0], 0.5f * mn[1] + 0.5f * mx[1],
+                                   0.5f * mn[2] + 0.5f * mx[2], 0.0f);
+            const float dx = p0 - c.x, dy = p1 - c.y, dz = p2 - c.z;
+            c.w = in ? sqrtf(dx * dx + dy * dy + dz * dz) : 0.0f;
+            for (int o = 1; o < to; o <<= 1) c.w = fmaxf(c.w, __shfl_xor(c.w, o, 64));
+            return c;
+        };
+        const float4 b8 = ball(1, 8), b64 = ball(8, 64);
+        if ((lane & 7) == 0) P.sub[at / 8] = b8;
+        if (lane == 0) P.ball[at / 64] = b64;
+    }
+}
+
+// Upper bounds of the clearances: 256 PPL ordered points of a block against `per` Gaussians of the
+// sample (sample s is Gaussian s n / m), staged 256 at a time.  Each LDS read of a Gaussian serves PPL
+// tests; below 16,384 points one test each, which gives four times as many waves (8,256 points and
+// 4,096 Gaussians: 18 us, against 22 us with PPL = 4).
+template <int PPL>
+__global__ __launch_bounds__(256) void k_cc_bound(GaussDev g, int m, int per, float lambda_g, CcPoints P, int npad,
+                                                  float* __restrict__ clearance) {
+    __shared__ float4 s_c[256];
+    const float nan = __builtin_nanf("");
+    float px[PPL], py[PPL], pz[PPL], best[PPL];
+#pragma unroll
+    for (int k = 0; k < PPL; k++) {
+        const int j = (blockIdx.x * PPL + k) * 256 + threadIdx.x;
+        px[k] = j < npad ? P.x[j] : nan;
+        py[k] = j < npad ? P.y[j] : nan;
+        pz[k] = j < npad ? P.z[j] : nan;
+        best[k] = CC_INF;
+    }
+    const int s0 = blockIdx.y * per, s1 = min(s0 + per, m);
+    for (int s = s0; s < s1; s += 256) {
+        __syncthreads();
+        float4 c = make_float4(nan, nan, nan, 0.0f);
+        if (s + (int)threadIdx.x < s1) {
+            const int64_t i = (int64_t)(s + threadIdx.x) * g.n / m;
+            const float v[6] = {g.means[i],      g.means[g.n + i],      g.means[2 * g.n + i],
+                                g.log_scales[i], g.log_scales[g.n + i], g.log_scales[2 * g.n + i]};
+            c = cc_gauss(v, lambda_g);
+        }
+        s_c[threadIdx.x] = c;
+        __syncthreads();
+#pragma unroll 8
+        for (int t = 0; t < 256; t++) {
+            const float4 q = s_c[t];
+#pragma unroll
+            for (int k = 0; k < PPL; k++) {
+                const float dx = px[k] - q.x, dy = py[k] - q.y, dz = pz[k] - q.z;
+                const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                best[k] = fminf(best[k], __builtin_amdgcn_sqrtf(d2) - q.w);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < PPL; k++) {  // a place past the points has found nothing
+        const int j = (blockIdx.x * PPL + k) * 256 + threadIdx.x;
+        if (best[k] < CC_INF) atomic_min_float(&clearance[P.index[j]], best[k]);
     }
 }
 
 // binary64 test of point (px, py, pz) against Gaussian i, as the oracle takes it
-__device__ __noinline__ bool collide64(const GaussDev& g, int64_t i, float px, float py, float pz, float r_robot,
+__device__ __forceinline__ bool collide64(const GaussDev& g, int64_t i, float px, float py, float pz, float r_robot,
                                        float lambda_g) {
     const double l0 = g.log_scales[i], l1 = g.log_scales[g.n + i], l2 = g.log_scales[2 * g.n + i];
     double lm = l0 > l1 ? l0 : l1;
@@ -75,93 +316,253 @@ __device__ __noinline__ bool collide64(const GaussDev& g, int64_t i, float px, f
     return d2 < gm * gm;
 }
 
-// grid: x over blocks of CC_THREADS points, y over chunks of `chunk` Gaussians.  The pair loop
-// only notes a pair inside the band (`amb`); a tile with such a point is walked once more by the
-// whole block, taking the binary64 test for those points alone.
-__global__ __launch_bounds__(CC_THREADS) void k_collision(GaussDev g, const float4* __restrict__ packed,
-                                                          const float2* __restrict__ bound,
-                                                          const float* __restrict__ pts, int64_t np, int64_t chunk,
-                                                          float r_robot, float lambda_g,
-                                                          int32_t* __restrict__ collide,
-                                                          uint32_t* __restrict__ clear_key) {
-    __shared__ float4 s_c[CC_TILE];
-    __shared__ float2 s_b[CC_TILE];
-    const int64_t j = (int64_t)blockIdx.x * CC_THREADS + threadIdx.x;
-    const bool live = j < np;
-    const float px = live ? pts[j] : 0.0f, py = live ? pts[np + j] : 0.0f, pz = live ? pts[2 * np + j] : 0.0f;
-    const int64_t c0 = (int64_t)blockIdx.y * chunk, c1 = min(c0 + chunk, g.n);
-    bool hit = false;
-    float best = __uint_as_float(0x7f800000u);  // +inf
-    for (int64_t t0 = c0; t0 < c1; t0 += CC_TILE) {
-        const int cnt = (int)min<int64_t>(CC_TILE, c1 - t0);
-        __syncthreads();
-        for (int k = threadIdx.x; k < cnt; k += CC_THREADS) {
-            s_c[k] = packed[t0 + k];
-            s_b[k] = bound[t0 + k];
+// Orders a wave's LDS stores before its later LDS loads (its own lanes' queues below).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// grid: x over the Gaussians (a block takes every gridDim.x-th step), y over slabs of `gps` groups.
+// CLR: the clearance is wanted; otherwise a group's reach is r_robot alone.
+//
+// A wave takes 64 Gaussians, one per lane, and tests them against the slab's balls of 64 points; a
+// pair (Gaussian, ball) that passes goes into the wave's queue q1.  Of 64 such pairs at a time, a pair
+// per lane, the eight balls of 8 points inside are tested into q2, and of 64 of these the
+// 8 points.  Few Gaussians pass a ball (on a lot, one in 40), so without the queues
+// nearly every lane of the later tests would be idle: testing all 64 points of a ball (a point
+// per lane) for each passing Gaussian took 931 us for 8,256 points and 3M Gaussians, with the queues 440 us.
+// Bound by instruction issue there (about 1.8e8 vector and 1.4e8 scalar wave instructions); for few points
+// by the one pass over the map (129 points, 3M Gaussians: 37 us, 1.9 TB/s).
+// Slabs of 44 groups: 63 KB of LDS, two blocks of twelve waves a CU at 80 VGPRs (512 threads and 24
+// groups, which read the map twice as often: 533 us).
+template <bool CLR>
+__global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_robot, float lambda_g, CcPoints P,
+                                                         int ngroups, int gps, int32_t* __restrict__ collide,
+                                                         float* clearance) {
+    extern __shared__ float4 s_all[];
+    const int ngp = (gps + CK_UNROLL - 1) / CK_UNROLL * CK_UNROLL;  // ck_lds_bytes
+    float4* s_pt = s_all;             // x, y, z and the least clearance so far
+    float4* s_sub = s_pt + ngp * 64;  // balls of 8 points: centre and reach (radius + bound)
+    float4* s_ball = s_sub + ngp * 8;  // of 64
+    unsigned long long* s_hit = reinterpret_cast<unsigned long long*>(s_ball + ngp);
+    __shared__ uint16_t s_q1[CK_THREADS / 64][64 * (CK_UNROLL + 1)], s_q2[CK_THREADS / 64][128];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int g0 = blockIdx.y * gps, ng = min(gps, ngroups - g0);
+    const float nan = __builtin_nanf("");
+    // a reach, widened by far more than the rounding of a distance
+    auto reach_of = [](float r, float ub) { return (r + ub) + 1e-5f * (r + fabsf(ub)); };
+    for (int gr = wv; gr < ngp; gr += CK_THREADS / 64) {
+        float4 ball = make_float4(nan, nan, nan, 0.0f);
+        if (gr < ng) {
+            const int at = (g0 + gr) * 64 + lane;
+            const float x = P.x[at], y = P.y[at], z = P.z[at];
+            float b = r_robot;
+            if (CLR) b = x == x ? clearance[P.index[at]] : -CC_INF;
+            s_pt[gr * 64 + lane] = make_float4(x, y, z, b);
+            float4 sub = P.sub[at / 8];
+            ball = P.ball[at / 64];
+            for (int o = 1; CLR && o < 8; o <<= 1) b = fmaxf(b, __shfl_xor(b, o, 64));
+            sub.w = reach_of(sub.w, b);
+            if ((lane & 7) == 0) s_sub[gr * 8 + (lane >> 3)] = sub;
+            for (int o = 8; CLR && o < 64; o <<= 1) b = fmaxf(b, __shfl_xor(b, o, 64));
+            ball.w = reach_of(ball.w, b);
         }
-        __syncthreads();
-        bool amb = false;
-        if (live) {
-#pragma unroll 4
-            for (int k = 0; k < cnt; k++) {
-                const float4 c = s_c[k];
-                const float2 bd = s_b[k];
-                const float dx = px - c.x, dy = py - c.y, dz = pz - c.z;
-                const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                hit |= d2 < bd.x;
-                amb |= d2 <= bd.y;
-                // sqrt(d2) - w < best  <=>  d2 < (best + w) |best + w|   (false when best + w <= 0)
-                const float tb = best + c.w;
-                if (d2 < tb * fabsf(tb)) best = __builtin_amdgcn_sqrtf(d2) - c.w;
+        if (lane == 0) {
+            s_ball[gr] = ball;
+            s_hit[gr] = 0ull;
+        }
+    }
+    __syncthreads();
+    uint16_t *q1 = s_q1[wv], *q2 = s_q2[wv];
+    int n1 = 0, n2 = 0;
+    auto passes = [&](float4 b, float4 q) {
+        const float dx = q.x - b.x, dy = q.y - b.y, dz = q.z - b.z;
+        const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+        const float reach = fmaf(q.w, 1.00001f, b.w);
+        return d2 <= reach * reach;
+    };
+    // appends the entries of the lanes in m
+    auto push = [&](uint16_t* queue, int& n, bool pass, uint64_t m, uint32_t entry) {
+        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        if (pass) queue[n + (int)at] = (uint16_t)entry;
+        n += (int)__popcll(m);
+    };
+    const int64_t stride = (int64_t)gridDim.x * CK_THREADS;
+    float raw[6];
+    auto fetch = [&](int64_t i0) {
+        const int64_t i = min(i0 + lane, g.n - 1);
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            raw[k] = g.means[k * g.n + i];
+            raw[3 + k] = g.log_scales[k * g.n + i];
+        }
+    };
+    int64_t base = (int64_t)blockIdx.x * CK_THREADS + wv * 64;
+    if (base < g.n) fetch(base);
+    for (; base < g.n; base += stride) {
+        float4 q = cc_gauss(raw, lambda_g);
+        if (base + lane >= g.n) q.x = nan;
+        if (base + stride < g.n) fetch(base + stride);  // in flight during this step
+        for (int gr0 = 0; gr0 < ng; gr0 += CK_UNROLL) {
+            bool pass[CK_UNROLL];
+            uint64_t m[CK_UNROLL], some = 0;
+#pragma unroll
+            for (int k = 0; k < CK_UNROLL; k++) {
+                pass[k] = passes(s_ball[gr0 + k], q);
+                m[k] = __ballot(pass[k]);
+                some |= m[k];
             }
-        }
-        const bool need = live && amb && !hit;
-        if (__syncthreads_or(need) && need) {
-            for (int k = 0; k < cnt && !hit; k++) {
-                const float4 c = s_c[k];
-                const float dx = px - c.x, dy = py - c.y, dz = pz - c.z;
-                const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                if (d2 <= s_b[k].y && collide64(g, t0 + k, px, py, pz, r_robot, lambda_g)) hit = true;
+            if (some) {
+#pragma unroll
+                for (int k = 0; k < CK_UNROLL; k++)
+                    push(q1, n1, pass[k], m[k], (uint32_t)lane | (uint32_t)(gr0 + k) << 6);
+            }
+            // 64 entries at a time; the queues name this step's lanes, so they end with it
+            const bool last = gr0 + CK_UNROLL >= ng;
+            while (n1 >= 64 || (last && n1 + n2 > 0)) {
+                wave_lds_fence();
+                const int t1 = min(n1, 64);
+                n1 -= t1;
+                const uint32_t e1 = lane < t1 ? q1[n1 + lane] : 0u;  // (lane of the Gaussian, ball of 64)
+                const int src1 = (int)(e1 & 63u);
+                float4 u;
+                u.x = __shfl(q.x, src1, 64);
+                u.y = __shfl(q.y, src1, 64);
+                u.z = __shfl(q.z, src1, 64);
+                u.w = __shfl(q.w, src1, 64);
+#pragma unroll 1
+                for (int k = 0; k < 8; k++) {
+                    // lanes start at different balls (and points below): those of one place would share its banks
+                    const uint32_t sub = (e1 >> 6) * 8 + ((k + lane) & 7);
+                    const bool ps = lane < t1 && passes(s_sub[sub], u);
+                    push(q2, n2, ps, __ballot(ps), (uint32_t)src1 | sub << 6);
+                    while (n2 >= 64 || (last && n1 == 0 && k == 7 && n2 > 0)) {
+                        wave_lds_fence();
+                        const int t2 = min(n2, 64);
+                        n2 -= t2;
+                        const uint32_t e2 = lane < t2 ? q2[n2 + lane] : 0u;  // (lane of the Gaussian, ball of 8)
+                        const int src = (int)(e2 & 63u);
+                        float4 c;
+                        c.x = __shfl(q.x, src, 64);
+                        c.y = __shfl(q.y, src, 64);
+                        c.z = __shfl(q.z, src, 64);
+                        c.w = __shfl(q.w, src, 64);
+                        wave_lds_fence();
+                        const float gm = r_robot + c.w, g2 = gm * gm;
+                        const float lo = g2 * (1.0f - CC_BAND), hi = g2 * (1.0f + CC_BAND);
+                        uint32_t amb = 0;  // points in the band
+                        if (lane < t2) {
+#pragma unroll
+                            for (int j = 0; j < 8; j++) {
+                                const int i = (int)(e2 >> 6) * 8 + ((j + lane) & 7);
+                                const float4 p = s_pt[i];
+                                const float dx = p.x - c.x, dy = p.y - c.y, dz = p.z - c.z;
+                                const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                                if (CLR) {
+                                    const float v = __builtin_amdgcn_sqrtf(d2) - c.w;
+                                    if (v < p.w) atomic_min_float(&s_pt[i].w, v);
+                                }
+                                if (d2 <= hi) {
+                                    const unsigned long long bit = 1ull << (i & 63);
+                                    if (!(s_hit[i >> 6] & bit)) {
+                                        if (d2 < lo) atomicOr(&s_hit[i >> 6], bit);
+                                        else amb |= 1u << j;
+                                    }
+                                }
+                            }
+                        }
+                        if (__ballot(amb != 0)) {
+                            for (; amb; amb &= amb - 1) {
+                                const int i = (int)(e2 >> 6) * 8 + ((__builtin_ctz(amb) + lane) & 7);
+                                const float4 p = s_pt[i];
+                                if (collide64(g, base + src, p.x, p.y, p.z, r_robot, lambda_g))
+                                    atomicOr(&s_hit[i >> 6], 1ull << (i & 63));
+                            }
+                        }
+                    }
+                }
             }
         }
     }
-    if (!live) return;
-    if (hit) atomicOr(&collide[j], 1);
-    atomicMin(&clear_key[j], ordered_key(best));
-}
-
-__global__ __launch_bounds__(256) void k_collision_init(int64_t np, int32_t* __restrict__ collide,
-                                                        uint32_t* __restrict__ clear_key) {
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < np; j += (int64_t)gridDim.x * blockDim.x) {
-        collide[j] = 0;
-        clear_key[j] = ordered_key(__uint_as_float(0x7f800000u));
+    __syncthreads();
+    for (int gr = wv; gr < ng; gr += CK_THREADS / 64) {
+        const float4 p = s_pt[gr * 64 + lane];
+        if (!(p.x == p.x)) continue;
+        const uint32_t i = P.index[(g0 + gr) * 64 + lane];
+        if ((s_hit[gr] >> lane) & 1ull) collide[i] = 1;  // every writer writes 1
+        if (CLR && p.w < clearance[i]) atomic_min_float(&clearance[i], p.w);
     }
 }
 
-__global__ __launch_bounds__(256) void k_collision_finish(int64_t np, const uint32_t* __restrict__ clear_key,
-                                                          float* __restrict__ clearance) {
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < np; j += (int64_t)gridDim.x * blockDim.x)
-        clearance[j] = ordered_val(clear_key[j]);
+// Points of one set of launches; more are taken in turn (their scratch is shared, in stream order).
+constexpr int64_t CC_MAX_POINTS = (int64_t)1 << 20;
+// Most Gaussians of the bounds' sample.  A 40 m lot's points are then bounded to half a metre on
+// average; four times as many cost 30 us more for 8,256 points and leave a tenth fewer pairs.
+constexpr int64_t CC_SAMPLE = 4096;
+
+// LDS of k_cc_check for slabs of gps groups.
+size_t ck_lds_bytes(int gps) {
+    const int ngp = (gps + CK_UNROLL - 1) / CK_UNROLL * CK_UNROLL;
+    return (size_t)ngp * ((64 + 8 + 1) * sizeof(float4) + sizeof(unsigned long long));
 }
+
+// Batches of k_cc_points for np points: their number and (equal) size, whole groups.
+struct CcBatches {
+    int blocks, per, groups;
+    explicit CcBatches(int64_t np) {
+        blocks = (int)((np + CP_BATCH - 1) / CP_BATCH);
+        per = (int)(((np + blocks - 1) / blocks + 63) / 64 * 64);
+        groups = blocks * per / 64;
+    }
+};
 
 }  // namespace
 
-void collision_check(const GaussDev& g, const float* pts, int64_t np, float r_robot, float lambda_g, float4* packed,
-                     float2* bound, int32_t* collide, uint32_t* clear_key, float* clearance, hipStream_t s) {
-    if (np <= 0) return;
-    k_collision_init<<<grid_cap((uint64_t)np, 256, 4096), 256, 0, s>>>(np, collide, clear_key);
-    if (g.n > 0) {
-        k_collision_prep<<<grid_cap((uint64_t)g.n, 256, 1u << 16), 256, 0, s>>>(g, r_robot, lambda_g, packed, bound);
-        const int64_t nbx = (np + CC_THREADS - 1) / CC_THREADS;
-        // chunks sized for about 4096 blocks, whole tiles, at most 65535 rows
-        int64_t chunk = (g.n * nbx + 4095) / 4096;
-        chunk = std::max<int64_t>(CC_TILE, (chunk + CC_TILE - 1) / CC_TILE * CC_TILE);
-        chunk = std::max<int64_t>(chunk, (g.n + 65534) / 65535);
-        const int64_t nby = (g.n + chunk - 1) / chunk;
-        dim3 grid((unsigned)nbx, (unsigned)nby);
-        k_collision<<<grid, CC_THREADS, 0, s>>>(g, packed, bound, pts, np, chunk, r_robot, lambda_g, collide, clear_key);
+size_t collision_ws_bytes(int64_t np) {
+    if (np <= 0) return 256;
+    // the largest set of launches; a smaller last one needs no more
+    const CcBatches b(std::min(np, CC_MAX_POINTS));
+    return (size_t)b.groups * (64 * 16 + 9 * 16);
+}
+
+void collision_check(const GaussDev& g, const float* pts, int64_t np_all, float r_robot, float lambda_g, void* ws,
+                     int32_t* collide, float* clearance, hipStream_t s) {
+    for (int64_t p0 = 0; p0 < np_all; p0 += CC_MAX_POINTS) {
+        const int np = (int)std::min(np_all - p0, CC_MAX_POINTS);
+        const CcBatches b(np);
+        const int npad = b.groups * 64;
+        CcPoints P;
+        P.ball = static_cast<float4*>(ws);
+        P.sub = P.ball + b.groups;
+        P.x = reinterpret_cast<float*>(P.sub + 8 * b.groups);
+        P.y = P.x + npad;
+        P.z = P.y + npad;
+        P.index = reinterpret_cast<uint32_t*>(P.z + npad);
+        int32_t* hit = collide + p0;
+        float* clr = clearance ? clearance + p0 : nullptr;
+        k_cc_points<<<b.blocks, CP_THREADS, 0, s>>>(pts + p0, np_all, np, b.per, P, hit, clr);
+        if (g.n <= 0) continue;
+        if (clr) {
+            const int m = (int)std::min<int64_t>(g.n, std::max<int64_t>(1024, std::min<int64_t>(CC_SAMPLE, g.n / 128)));
+            const bool wide = npad >= 16384;  // enough points for 256 blocks with four per lane
+            const int gx = (npad + (wide ? 1023 : 255)) / (wide ? 1024 : 256);
+            // about 1,024 blocks, each with whole rounds of 256 Gaussians
+            const int rounds = (m + 255) / 256;
+            const int gy = std::max(1, std::min(rounds, 1024 / gx));
+            const int per = (rounds + gy - 1) / gy * 256;
+            const dim3 grid((unsigned)gx, (unsigned)((m + per - 1) / per));
+            if (wide) k_cc_bound<4><<<grid, 256, 0, s>>>(g, m, per, lambda_g, P, npad, clr);
+            else k_cc_bound<1><<<grid, 256, 0, s>>>(g, m, per, lambda_g, P, npad, clr);
+        }
+        // slabs of equal numbers of groups, and blocks for about two rounds of the chip
+        const int ny = (b.groups + CK_GROUPS - 1) / CK_GROUPS, gps = (b.groups + ny - 1) / ny;
+        const int64_t steps = (g.n + CK_THREADS - 1) / CK_THREADS;
+        const int nx = (int)std::min<int64_t>(steps, std::max(1, 512 / ny));
+        const dim3 grid((unsigned)nx, (unsigned)ny);
+        const size_t lds = ck_lds_bytes(gps);
+        if (clr) k_cc_check<true><<<grid, CK_THREADS, lds, s>>>(g, r_robot, lambda_g, P, b.groups, gps, hit, clr);
+        else k_cc_check<false><<<grid, CK_THREADS, lds, s>>>(g, r_robot, lambda_g, P, b.groups, gps, hit, clr);
     }
-    if (clearance) k_collision_finish<<<grid_cap((uint64_t)np, 256, 4096), 256, 0, s>>>(np, clear_key, clearance);
 }
 
 }  // namespace rtg

@@ -210,11 +210,12 @@ int ssim_blocks_per_view(int max_w, int max_h);
 void loss_ssim(const ViewDev* views, int n_views, int blocks_per_view, uint64_t pix_total, const float* rgb,
                const float* depth, const float* trgb, const float* tdepth, float w_depth, float l1, float l2,
                float* maps, double* partial, float* d_rgb, float* d_depth, double* loss, hipStream_t s);
-// Collision check of np points (planar 3 x np) against the map; packed,
-// bound: n float4 / float2 scratch, collide: np int32 (required), clear_key:
-// np uint32 scratch, clearance: np floats or NULL.
-void collision_check(const GaussDev& g, const float* pts, int64_t np, float r_robot, float lambda_g, float4* packed,
-                     float2* bound, int32_t* collide, uint32_t* clear_key, float* clearance, hipStream_t s);
+// Collision check of np points (planar 3 x np) against the map; ws: scratch of
+// collision_ws_bytes(np) (about 16 bytes per point, at most 17 MiB), collide:
+// np int32 (required), clearance: np floats or NULL.
+size_t collision_ws_bytes(int64_t np);
+void collision_check(const GaussDev& g, const float* pts, int64_t np, float r_robot, float lambda_g, void* ws,
+                     int32_t* collide, float* clearance, hipStream_t s);
 // Uncertainty bookkeeping (n Gaussians, planar 3 x n means).
 void uncertainty_update(int64_t n, const float* prev, const float* cur, const float* u_prev, int squared,
                         float* u_out, hipStream_t s);
