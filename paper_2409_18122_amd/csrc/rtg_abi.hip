@@ -1511,7 +1511,7 @@ rtg_status rtg_uncertainty_thresholds(rtg_ctx* ctx, const float* uncert, int64_t
     if (!lo_hi) return set_err(RTG_ERR_INVALID, "lo_hi is NULL");
     if (!std::isfinite(k_std)) return set_err(RTG_ERR_INVALID, "k_std is not finite");
     Buf scratch;
-    RTG_TRY(scratch.ensure(ctx, sizeof(double) * 520));
+    RTG_TRY(scratch.ensure(ctx, sizeof(double) * 1024));
     uncertainty_thresholds(uncert, n, k_std, scratch.as<double>(), lo_hi, (hipStream_t)stream);
     return check_launch("uncertainty thresholds");
 }

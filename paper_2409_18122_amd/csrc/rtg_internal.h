@@ -239,7 +239,7 @@ void export_records(const uint32_t* R_dev, uint32_t cap, Records rec, double* me
 
 // Paper-literal view utility: per-view counts of visible high / low
 // uncertainty Gaussians, their uncertainty sum and xi.  acc: 3 * nv u64
-// scratch.  thresholds: scratch of 1 + 512 doubles.
+// scratch.  thresholds: scratch of 2 x 512 doubles.
 void view_utility(const GaussDev& g, const ViewDev* views, int nv, float z_near, float range, const double* lo_hi,
                   unsigned long long* acc, double lambda, int64_t* n_high, int64_t* n_low, double* sum_u, double* xi,
                   hipStream_t s);

@@ -2943,150 +2943,289 @@ __device__ __forceinline__ bool fov_exact(double mx0, double my0, double mz0, co
     return mx >= 0.0 && mx <= (double)(V.W - 1) && my >= 0.0 && my <= (double)(V.H - 1);
 }
 
-// A view's binary32 values for the field-of-view screen (the camera's own
-// binary32 values: its binary64 fields are these, widened).
-struct ViewF {
-    float T[3], R[9], fx, fy, cx, cy, W1, H1, kf, pad;
+// Screen of the field-of-view test.  With p the mean, d = R^T (p - T) its camera coordinates and
+// h = (W - 1) / 2, the projection lies inside the image's columns where |s_x| <= d_z, s_x = (fx d_x +
+// (cx - h) d_z) / h, for d_z > 0: s_x is a linear form of (p, 1); likewise s_y; and the depth is in
+// (z_near, range].  So one number e = max(|s_x| - d_z, |s_y| - d_z, z_near - d_z, d_z - range)
+// decides: visible where e < -m, not where e > m, and the binary64 test between.
+// m = k |p|_1 + c bounds the rounding of the forms: a coefficient's (2^-24), the two
+// products of third parts that are left out (2^-23) and at most 26 roundings or truncations
+// (2^-23) of sums below k |p|_1 + c; UT_EPS is over twice that.  (The rounding of a large range
+// matters only near d_z = range, where |p|_1 or |T| is as large.)  A coefficient or a mean beyond
+// UT_HUGE, or an image one pixel wide or high, gets an infinite m, which leaves the decision to
+// the binary64 test.
+constexpr float UT_EPS = 8e-6f;
+constexpr float UT_HUGE = 1e15f;
+
+struct ViewScreen {
+    float row[4][4];  // s_x, s_y, d_z as forms of (x, y, z, 1); the fourth is 0
+    float k, c;       // margin
 };
 
-__device__ __forceinline__ ViewF view_f(const ViewDev& V) {
-    ViewF f;
-#pragma unroll
-    for (int k = 0; k < 3; k++) f.T[k] = V.Tf[k];
-#pragma unroll
-    for (int k = 0; k < 9; k++) f.R[k] = V.Rf[k];
-    f.fx = V.fxf;
-    f.fy = V.fyf;
-    f.cx = V.cxf;
-    f.cy = V.cyf;
-    f.W1 = (float)(V.W - 1);
-    f.H1 = (float)(V.H - 1);
-    f.kf = 1e-3f * (V.fxf + V.fyf);
-    f.pad = 0.0f;
-    return f;
+__device__ inline ViewScreen view_screen(const ViewDev& V, double z_near) {
+    const double h[2] = {0.5 * (V.W - 1), 0.5 * (V.H - 1)};
+    const double along[2] = {V.fx / h[0], V.fy / h[1]}, off[2] = {(V.cx - h[0]) / h[0], (V.cy - h[1]) / h[1]};
+    double kmax = 0.0, cmax = 0.0;
+    ViewScreen s;
+    for (int r = 0; r < 3; r++) {
+        double bias = 0.0, k = 0.0, c = z_near;
+        for (int a = 0; a < 3; a++) {
+            const double z = V.R[3 * a + 2], f = r < 2 ? along[r] * V.R[3 * a + r] + off[r] * z : z;
+            bias -= f * V.T[a];
+            s.row[r][a] = (float)f;
+            // the form's own terms and those of the d_z it is compared with
+            k = fmax(k, fabs(f) + fabs(z));
+            c += (fabs(f) + fabs(z)) * fabs(V.T[a]);
+        }
+        s.row[r][3] = (float)bias;
+        // the negated test also takes a NaN
+        kmax = k < UT_HUGE ? fmax(kmax, k) : HUGE_VAL;
+        cmax = c < UT_HUGE ? fmax(cmax, c) : HUGE_VAL;
+    }
+    for (int a = 0; a < 4; a++) s.row[3][a] = 0.0f;
+    s.k = UT_EPS * (float)kmax;
+    s.c = UT_EPS * (float)cmax;
+    if (!(kmax < UT_HUGE) || !(cmax < UT_HUGE)) {
+        for (int r = 0; r < 3; r++)
+            for (int a = 0; a < 4; a++) s.row[r][a] = 0.0f;
+        s.k = 0.0f;
+        s.c = __builtin_inff();
+    }
+    return s;
 }
 
-// Binary32 screen of the field-of-view test: 1 certainly visible, 0
-// certainly not, -1 too close to a depth limit or an image border to tell
-// (the binary64 test then decides).  Branch-free: every Gaussian of a wave
-// takes the same instructions.
-__device__ __forceinline__ int fov_fast(float x, float y, float z, const ViewF& V, float z_near, float range) {
-    const float dx = x - V.T[0], dy = y - V.T[1], dz = z - V.T[2];
-    const float mag = fabsf(dx) + fabsf(dy) + fabsf(dz) + 1.0f;
-    const float tx = fmaf(dz, V.R[6], fmaf(dy, V.R[3], dx * V.R[0]));
-    const float ty = fmaf(dz, V.R[7], fmaf(dy, V.R[4], dx * V.R[1]));
-    const float tz = fmaf(dz, V.R[8], fmaf(dy, V.R[5], dx * V.R[2]));
-    const float ez = 1e-5f * mag;
-    // hardware reciprocal (within an ulp or two): far inside the margin m
-    const float iz = __builtin_amdgcn_rcpf(tz);
-    const float mx = fmaf(V.fx * tx, iz, V.cx);
-    const float my = fmaf(V.fy * ty, iz, V.cy);
-    const float m = fmaf(1e-3f, 1.0f + fabsf(mx) + fabsf(my), V.kf * mag * iz);
-    const bool out = (tz <= z_near - ez) | (tz > range + ez) | (mx < -m) | (mx > V.W1 + m) | (my < -m) |
-                     (my > V.H1 + m);
-    const bool in = (tz > z_near + ez) & (tz <= range - ez) & (mx > m) & (mx < V.W1 - m) & (my > m) &
-                    (my < V.H1 - m);
-    return out ? 0 : (in ? 1 : -1);
+// The forms of four views at 16 Gaussians are one matrix product: 16 rows (three forms per view and a
+// spare one) by the columns (x, y, z, 1), each binary32 number the exact sum of three bfloat16
+// parts (high, mid, low) and each product the six leading products of parts, 24 of the 32 columns of
+// v_mfma_f32_16x16x32_bf16.  Lane l then holds the forms of view l / 16 at Gaussian l % 16.
+// Measured for 576 views x 2M Gaussians: one projection per lane with a reciprocal and
+// twelve compares (about 65 vector instructions a test) 1,823 us; the product in binary32
+// (v_mfma_f32_16x16x4_f32, which the vector unit does not overlap) 755 us; this 501 us, of which the
+// tests' eight vector instructions take most.
+// A block takes UT_VB views (their forms in registers) and a share of the Gaussians, 64 per
+// wave and step; counts and fixed-point sums stay in registers, per lane and view, until the
+// end.  They are integers: the result does not depend on the order.
+constexpr int UT_GROUPS = 8;  // of four views
+constexpr int UT_VB = 4 * UT_GROUPS;
+constexpr int64_t UT_LANE_MAX = 60000;  // Gaussians per lane and view: the two counts share a word
+
+constexpr int UT_CHUNK = 4;
+static_assert(UT_GROUPS % UT_CHUNK == 0 && UT_CHUNK == 4, "whole chunks, four minima");
+
+// Maxima without the quieting of their operands that fmaxf asks for (it would double their count).
+__device__ __forceinline__ float max2(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+// max(|a|, |b|, c), c uniform, of matrix-core results a and b.  `after`, unused, was formed from the same
+// result by ordinary code, which has waited for it.
+__device__ __forceinline__ float max_abs(float a, float b, float c, float after) {
+    float r;
+    asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c), "v"(after));
+    return r;
+}
+// The least magnitude of four.
+__device__ __forceinline__ float min_abs4(float a, float b, float c, float d) {
+    float r;
+    asm("v_min3_f32 %0, |%1|, |%2|, |%3|\n\tv_min_f32 %0, %0, |%4|" : "=&v"(r) : "v"(a), "v"(b), "v"(c), "v"(d));
+    return r;
 }
 
-__device__ __noinline__ bool fov_exact_call(float x, float y, float z, const ViewDev& V, float z_near, float range) {
-    return fov_exact((double)x, (double)y, (double)z, V, (double)z_near, (double)range);
+// a += x and b += y in the lanes of m (two vector instructions under the mask instead of the five of
+// two sums and three selects).
+__device__ __forceinline__ void add_where(uint64_t m, uint32_t& a, uint32_t x, unsigned long long& b,
+                                          unsigned long long y) {
+    uint64_t keep;
+    asm volatile("s_and_saveexec_b64 %2, %3\n\tv_add_u32 %0, %0, %4\n\tv_lshl_add_u64 %1, %5, 0, %1\n\ts_mov_b64 exec, %2"
+                 : "+v"(a), "+v"(b), "=&s"(keep)
+                 : "s"(m), "v"(x), "v"(y)
+                 : "scc");
 }
 
-// Work split: a block takes UT_VB views (their screen values in LDS) and a
-// share of the Gaussians, streamed UT_G per thread per step with coalesced
-// loads; each thread keeps its counts and fixed-point sum per view in
-// registers and the wave reduces them once at the end.  Counts and sums are
-// integers: the result does not depend on the order.
-constexpr int UT_VB = 8;
-constexpr int UT_G = 4;
+using f32x4 = __attribute__((__vector_size__(4 * sizeof(float)))) float;
+using bf16x8 = __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16;
 
-__global__ __launch_bounds__(UT_THREADS) void k_view_utility(GaussDev g, const ViewDev* __restrict__ views, int nv,
+// A binary32 number as three bfloat16 parts (their exact sum): .x = mid << 16 | high, .y = high << 16 | low.
+__device__ __forceinline__ uint2 split_bf16(float x) {
+    const uint32_t h = __float_as_uint(x) & 0xffff0000u;
+    const float r = x - __uint_as_float(h);
+    const uint32_t m = __float_as_uint(r) & 0xffff0000u;
+    const uint32_t l = __float_as_uint(r - __uint_as_float(m));
+    return make_uint2(h >> 16 | m, l >> 16 | h);
+}
+// One component's eight columns: A (h, h, m, m, l, h, 0, 0) against B (h, m, h, m, h, l, 0, 0).
+__device__ __forceinline__ bf16x8 operand_a(uint2 p) {
+    const uint32_t h = p.x & 0xffffu, m = p.x >> 16;
+    const uint4 v = make_uint4(h | h << 16, m | m << 16, (p.y & 0xffffu) | h << 16, 0u);
+    return __builtin_bit_cast(bf16x8, v);
+}
+__device__ __forceinline__ bf16x8 operand_b(uint2 p) {
+    return __builtin_bit_cast(bf16x8, make_uint4(p.x, p.x, p.y >> 16 | p.y << 16, 0u));
+}
+
+__global__ __launch_bounds__(UT_THREADS, 4) void k_view_utility(GaussDev g, const ViewDev* __restrict__ views, int nv,
                                                              float z_near, float range,
                                                              const double* __restrict__ lo_hi,
                                                              unsigned long long* __restrict__ cnt_h,
                                                              unsigned long long* __restrict__ cnt_l,
                                                              unsigned long long* __restrict__ fix_u) {
-    __shared__ ViewF s_v[UT_VB];
+    constexpr int WAVES = UT_THREADS / 64;
+    __shared__ float s_row[UT_VB][4][4];
+    __shared__ float2 s_h[UT_VB];  // margins
+    __shared__ uint2 s_x[WAVES][3][64];  // the split mean
+    __shared__ uint4 s_d[WAVES][64];     // counts' increments, fixed-point u (two words), margin
+    __shared__ unsigned long long s_sum[3][UT_VB];
+    __shared__ uint16_t s_ask[WAVES][64 * UT_GROUPS];  // Gaussian of the step | view << 6
     const int v0 = (int)blockIdx.y * UT_VB;
-    const int nvb = min(UT_VB, nv - v0);
-    if ((int)threadIdx.x < nvb) s_v[threadIdx.x] = view_f(views[v0 + threadIdx.x]);
+    const int nvb = min(UT_VB, nv - v0), ngr = (nvb + 3) / 4;
+    const int lane = (int)lane_id(), wv = (int)threadIdx.x >> 6, col = lane & 15, quad = lane >> 4;
+    if ((int)threadIdx.x < UT_VB) {
+        ViewScreen s;
+        if ((int)threadIdx.x < nvb) {
+            s = view_screen(views[v0 + threadIdx.x], (double)z_near);
+        } else {  // sees nothing
+            for (int r = 0; r < 4; r++)
+                for (int a = 0; a < 4; a++) s.row[r][a] = 0.0f;
+            s.row[2][3] = -1e38f;
+            s.k = s.c = 0.0f;
+        }
+        for (int r = 0; r < 4; r++)
+            for (int a = 0; a < 4; a++) s_row[threadIdx.x][r][a] = s.row[r][a];
+        s_h[threadIdx.x] = make_float2(s.k, s.c);
+        s_sum[0][threadIdx.x] = s_sum[1][threadIdx.x] = s_sum[2][threadIdx.x] = 0ull;
+    }
     __syncthreads();
+    bf16x8 A[UT_GROUPS];
+    uint32_t cnt[UT_GROUPS];
+    unsigned long long su[UT_GROUPS];
+#pragma unroll
+    for (int q = 0; q < UT_GROUPS; q++) {
+        // operand A: row lane % 16 (view of four, form), columns of component lane / 16
+        A[q] = operand_a(split_bf16(s_row[4 * q + (col >> 2)][col & 3][quad]));
+        cnt[q] = 0u;
+        su[q] = 0ull;
+    }
+    // one margin for the block's views
+    float mk = 0.0f, mc = 0.0f;
+    for (int v = 0; v < nvb; v++) {
+        mk = fmaxf(mk, s_h[v].x);
+        mc = fmaxf(mc, s_h[v].y);
+    }
     const double lo = lo_hi[0], hi = lo_hi[1];
     const int64_t n = g.n;
-    uint32_t ch[UT_VB], cl[UT_VB];
-    unsigned long long su[UT_VB];
+    const int64_t stride = (int64_t)gridDim.x * UT_THREADS;
+    int64_t base = (int64_t)blockIdx.x * UT_THREADS + wv * 64;
+    int nask = 0;
+    float raw[4];
+    auto fetch = [&](int64_t i0) {
+        const int64_t i = min(i0 + lane, n - 1);
+        raw[0] = g.means[i];
+        raw[1] = g.means[n + i];
+        raw[2] = g.means[2 * n + i];
+        raw[3] = g.uncert[i];
+    };
+    if (base < n) fetch(base);
+    for (; base < n; base += stride) {
+        const float u = raw[3];
+        // a Gaussian past the end or without a finite mean counts nothing
+        const bool ok = base + lane < n && isfinite(raw[0]) && isfinite(raw[1]) && isfinite(raw[2]);
+        const uint32_t inc = !ok ? 0u : ((double)u > hi ? 1u : 0u) | ((double)u < lo ? 0x10000u : 0u);
+        const unsigned long long fu =
+            ok && isfinite(u) && u > 0.0f ? (unsigned long long)((double)u * FIX_SCALE) : 0ull;
+        const float mag = fabsf(raw[0]) + fabsf(raw[1]) + fabsf(raw[2]);
+        const bool tame = ok && mag < UT_HUGE;
 #pragma unroll
-    for (int b = 0; b < UT_VB; b++) {
-        ch[b] = cl[b] = 0u;
-        su[b] = 0ull;
-    }
-    constexpr int64_t CH = (int64_t)UT_THREADS * UT_G;
-    for (int64_t base = (int64_t)blockIdx.x * CH; base < n; base += (int64_t)gridDim.x * CH) {
-        float x[UT_G], y[UT_G], z[UT_G];
-        unsigned long long fu[UT_G];
-        uint32_t ok = 0, isH = 0, isL = 0;  // bit j: Gaussian j of this thread
+        for (int a = 0; a < 3; a++) s_x[wv][a][lane] = split_bf16(tame ? raw[a] : 0.0f);
+        // 0 <= mk, mc; one that counts nothing needs no second look
+        const float margin = !ok ? 0.0f : tame ? fmaf(mk, mag, mc) : __builtin_inff();
+        s_d[wv][lane] = make_uint4(inc, (uint32_t)fu, (uint32_t)(fu >> 32), __float_as_uint(margin));
+        if (base + stride < n) fetch(base + stride);  // in flight during this step
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int s = 0; s < 4; s++) {
+            // operand B: columns of component lane / 16 (the fourth is 1) of Gaussian lane % 16
+            const uint2 bx = s_x[wv][min(quad, 2)][16 * s + col];
+            const bf16x8 B = operand_b(quad < 3 ? bx : make_uint2(0x3f80u, 0x3f800000u));
+            const uint4 d = s_d[wv][16 * s + col];
+            const float m = __uint_as_float(d.w);
+            const unsigned long long du = (unsigned long long)d.z << 32 | d.y;
+            // UT_CHUNK products in flight, then their tests; groups past the last view see nothing
 #pragma unroll
-        for (int j = 0; j < UT_G; j++) {
-            const int64_t i = base + (int64_t)j * UT_THREADS + threadIdx.x;
-            x[j] = y[j] = z[j] = 0.0f;
-            fu[j] = 0ull;
-            if (i < n) {
-                x[j] = g.means[i];
-                y[j] = g.means[n + i];
-                z[j] = g.means[2 * n + i];
-                const float u = g.uncert[i];
-                if (isfinite(x[j]) && isfinite(y[j]) && isfinite(z[j])) ok |= 1u << j;
-                if ((double)u > hi) isH |= 1u << j;
-                if ((double)u < lo) isL |= 1u << j;
-                fu[j] = (isfinite(u) && u > 0.0f) ? (unsigned long long)((double)u * FIX_SCALE) : 0ull;
+            for (int q0 = 0; q0 < UT_GROUPS; q0 += UT_CHUNK) {
+                if (q0 >= ngr) break;
+                f32x4 f[UT_CHUNK];
+#pragma unroll
+                for (int k = 0; k < UT_CHUNK; k++)
+                    f[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[q0 + k], B, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                float e[UT_CHUNK];
+                uint64_t vis[UT_CHUNK];
+#pragma unroll
+                for (int k = 0; k < UT_CHUNK; k++) {
+                    const float beyond = f[k][2] - range;
+                    e[k] = max2(max_abs(f[k][0], f[k][1], z_near, beyond) - f[k][2], beyond);
+                    vis[k] = __ballot(e[k] < -m);
+                }
+                // the least |e| tells whether any test is undecided (also with an infinite m)
+                if (__ballot(!(min_abs4(e[0], e[1], e[2], e[3]) > m))) {
+#pragma unroll
+                    for (int k = 0; k < UT_CHUNK; k++) {
+                        const uint64_t um = __ballot(!(e[k] > m)) & ~vis[k];
+                        if ((um >> lane) & 1ull)
+                            s_ask[wv][nask + (int)__popcll(um & lanemask_lt())] =
+                                (uint16_t)(16 * s + col + ((4 * (q0 + k) + quad) << 6));
+                        nask += (int)__popcll(um);
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < UT_CHUNK; k++) add_where(vis[k], cnt[q0 + k], d.x, su[q0 + k], du);
             }
+            // the undecided tests of this round, a pair (Gaussian, view) per lane; rare, so they go to
+            // the block's sums one by one
+            if (nask == 0) continue;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+            for (int a = lane; a < nask; a += 64) {
+                const int j = s_ask[wv][a] & 63, v = s_ask[wv][a] >> 6;
+                const int64_t i = base + j;
+                if (i >= n || v >= nvb) continue;
+                if (!fov_exact((double)g.means[i], (double)g.means[n + i], (double)g.means[2 * n + i], views[v0 + v],
+                               (double)z_near, (double)range))
+                    continue;
+                const uint4 e = s_d[wv][j];
+                atomicAdd(&s_sum[0][v], (unsigned long long)(e.x & 0xffffu));
+                atomicAdd(&s_sum[1][v], (unsigned long long)(e.x >> 16));
+                atomicAdd(&s_sum[2][v], (unsigned long long)e.z << 32 | e.y);
+            }
+            nask = 0;
         }
-        // the views' values are read from LDS in every step (a compiler
-        // barrier keeps them from being hoisted into registers, which would
-        // cost occupancy)
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int b = 0; b < UT_VB; b++) {
-            if (b >= nvb) break;
-            const ViewF V = s_v[b];
-            uint32_t vis = 0, unsure = 0;
-#pragma unroll
-            for (int j = 0; j < UT_G; j++) {
-                const int f = fov_fast(x[j], y[j], z[j], V, z_near, range);
-                vis |= (uint32_t)(f == 1) << j;
-                unsure |= (uint32_t)(f < 0) << j;
-            }
-            unsure &= ok;
-            // near a border or the depth limits the binary64 test decides
-            if (__ballot(unsure != 0)) {
-#pragma unroll
-                for (int j = 0; j < UT_G; j++)
-                    if (((unsure >> j) & 1u) && fov_exact_call(x[j], y[j], z[j], views[v0 + b], z_near, range))
-                        vis |= 1u << j;
-            }
-            vis &= ok;
-            ch[b] += __popc(vis & isH);
-            cl[b] += __popc(vis & isL);
-#pragma unroll
-            for (int j = 0; j < UT_G; j++) su[b] += ((vis >> j) & 1u) ? fu[j] : 0ull;
-        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 #pragma unroll
-    for (int b = 0; b < UT_VB; b++) {
-        if (b >= nvb) break;
-        unsigned long long h = ch[b], l = cl[b], t = su[b];
+    for (int q = 0; q < UT_GROUPS; q++) {
+        uint32_t h = cnt[q] & 0xffffu, l = cnt[q] >> 16;
+        unsigned long long t = su[q];
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            h += __shfl_xor(h, o, 64);
-            l += __shfl_xor(l, o, 64);
+        for (int o = 1; o < 16; o <<= 1) {
+            h += (uint32_t)__shfl_xor((int)h, o, 64);
+            l += (uint32_t)__shfl_xor((int)l, o, 64);
             t += __shfl_xor(t, o, 64);
         }
-        if (lane_id() == 0) {
-            if (h) atomicAdd(cnt_h + v0 + b, h);
-            if (l) atomicAdd(cnt_l + v0 + b, l);
-            if (t) atomicAdd(fix_u + v0 + b, t);
+        if (col == 0) {
+            atomicAdd(&s_sum[0][4 * q + quad], (unsigned long long)h);
+            atomicAdd(&s_sum[1][4 * q + quad], (unsigned long long)l);
+            atomicAdd(&s_sum[2][4 * q + quad], t);
         }
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < nvb) {
+        const int v = v0 + (int)threadIdx.x;
+        if (s_sum[0][threadIdx.x]) atomicAdd(cnt_h + v, s_sum[0][threadIdx.x]);
+        if (s_sum[1][threadIdx.x]) atomicAdd(cnt_l + v, s_sum[1][threadIdx.x]);
+        if (s_sum[2][threadIdx.x]) atomicAdd(fix_u + v, s_sum[2][threadIdx.x]);
     }
 }
 
@@ -3103,11 +3242,27 @@ __global__ void k_utility_finish(int nv, const unsigned long long* __restrict__ 
     }
 }
 
-// mean and population standard deviation of u, binary64, fixed reduction order
+// Mean and population standard deviation of u, binary64, fixed reduction order: the
+// blocks' partial sums (MO_BLOCKS of them at most), then the partial sums of the squared deviations
+// from the mean, which every block forms from the first pass's partial sums itself.
+constexpr int MO_BLOCKS = 512;
+
+// The sum of partial[0 .. nb), the same in every block of 256 threads that forms it.
+__device__ __forceinline__ double sum_partials_256(const double* __restrict__ partial, int nb, double* ws) {
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nb; b += 256) s += partial[b];
+    s = wave_sum_d(s);
+    if (lane_id() == 0) ws[threadIdx.x >> 6] = s;
+    __syncthreads();
+    s = (ws[0] + ws[1]) + (ws[2] + ws[3]);
+    __syncthreads();
+    return s;
+}
+
 __global__ __launch_bounds__(256) void k_moments(const float* __restrict__ u, int64_t n, int pass,
-                                                 const double* __restrict__ mean_in, double* __restrict__ partial) {
+                                                 const double* __restrict__ sums, double* __restrict__ partial) {
     __shared__ double ws[4];
-    const double mean = pass ? *mean_in : 0.0;
+    const double mean = pass ? sum_partials_256(sums, (int)gridDim.x, ws) / (double)n : 0.0;
     double s = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         double d = (double)u[i] - mean;
@@ -3119,37 +3274,54 @@ __global__ __launch_bounds__(256) void k_moments(const float* __restrict__ u, in
     if (threadIdx.x == 0) partial[blockIdx.x] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
 }
 
-__global__ void k_moments_finish(const double* __restrict__ partial, int nb, int64_t n, int pass, double k,
-                                 double* __restrict__ mean_io, double* __restrict__ lo_hi) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double s = 0.0;
-    for (int b = 0; b < nb; b++) s += partial[b];
-    if (pass == 0) {
-        *mean_io = n > 0 ? s / (double)n : 0.0;
-    } else {
-        double sd = n > 0 ? sqrt(s / (double)n) : 0.0;
-        lo_hi[0] = *mean_io - k * sd;
-        lo_hi[1] = *mean_io + k * sd;
+__global__ __launch_bounds__(256) void k_moments_finish(const double* __restrict__ sums, const double* __restrict__ sq,
+                                                        int nb, int64_t n, double k, double* __restrict__ lo_hi) {
+    __shared__ double ws[4];
+    const double mean = n > 0 ? sum_partials_256(sums, nb, ws) / (double)n : 0.0;
+    const double sd = n > 0 ? sqrt(sum_partials_256(sq, nb, ws) / (double)n) : 0.0;
+    if (threadIdx.x == 0) {
+        lo_hi[0] = mean - k * sd;
+        lo_hi[1] = mean + k * sd;
     }
 }
 
 // eq. (10): utility of trajectory t = sum of xi over its states
 // [off[t], off[t+1]) in order; best = first trajectory of maximal utility.
-__global__ void k_traj_select(const double* __restrict__ xi, const int32_t* __restrict__ off, int n_traj,
-                              double* __restrict__ util, int32_t* __restrict__ best) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    int b = -1;
+// One block, a trajectory per thread (one thread for all of them waited for 576 loads in turn:
+// 39 us).  A NaN utility is never greater, and nothing is greater than a NaN first one.
+__global__ __launch_bounds__(256) void k_traj_select(const double* __restrict__ xi, const int32_t* __restrict__ off,
+                                                     int n_traj, double* __restrict__ util,
+                                                     int32_t* __restrict__ best) {
+    __shared__ double s_v[256];
+    __shared__ int s_t[256];
+    __shared__ int s_nan;
+    int b = n_traj;  // none
     double bv = 0.0;
-    for (int t = 0; t < n_traj; t++) {
+    for (int t = threadIdx.x; t < n_traj; t += 256) {
         double s = 0.0;
         for (int k = off[t]; k < off[t + 1]; k++) s += xi[k];
         if (util) util[t] = s;
-        if (b < 0 || s > bv) {
+        if (t == 0) s_nan = s != s;
+        if (s == s && (b == n_traj || s > bv)) {
             b = t;
             bv = s;
         }
     }
-    *best = b;
+    s_v[threadIdx.x] = bv;
+    s_t[threadIdx.x] = b;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) {
+            const int t2 = s_t[threadIdx.x + o], t1 = s_t[threadIdx.x];
+            const double v2 = s_v[threadIdx.x + o], v1 = s_v[threadIdx.x];
+            if (t2 < n_traj && (t1 == n_traj || v2 > v1 || (v2 == v1 && t2 < t1))) {
+                s_t[threadIdx.x] = t2;
+                s_v[threadIdx.x] = v2;
+            }
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *best = s_nan ? 0 : s_t[0];
 }
 
 inline unsigned grid_for(uint64_t n, unsigned block, unsigned cap = 65535u * 16u) {
@@ -3310,10 +3482,12 @@ void view_utility(const GaussDev& g, const ViewDev* views, int nv, float z_near,
                   hipStream_t s) {
     fill_u32(reinterpret_cast<uint32_t*>(acc), 0u, (uint64_t)6 * nv, s);
     if (g.n > 0) {
-        // about 2048 blocks over (Gaussian shares) x (groups of UT_VB views)
+        // about 2048 blocks over (Gaussian shares) x (groups of UT_VB views), more where a lane's
+        // share would not fit its counters (a step gives each lane four Gaussians a view)
         const unsigned gy = (unsigned)((nv + UT_VB - 1) / UT_VB);
-        const unsigned gmax = grid_for(((uint64_t)g.n + UT_G - 1) / UT_G, UT_THREADS, 1u << 20);
-        const unsigned gx = std::max(1u, std::min(gmax, (2048u + gy - 1) / gy));
+        const unsigned gmax = grid_for((uint64_t)g.n, UT_THREADS, 1u << 30);
+        const unsigned gfit = (unsigned)(g.n * 4 / (UT_THREADS * UT_LANE_MAX) + 1);
+        const unsigned gx = std::max(gfit, std::min(gmax, (2048u + gy - 1) / gy));
         k_view_utility<<<dim3(gx, gy), UT_THREADS, 0, s>>>(g, views, nv, z_near, range, lo_hi, acc, acc + nv,
                                                            acc + 2 * nv);
     }
@@ -3322,18 +3496,17 @@ void view_utility(const GaussDev& g, const ViewDev* views, int nv, float z_near,
 }
 
 void uncertainty_thresholds(const float* u, int64_t n, double k, double* scratch, double* lo_hi, hipStream_t s) {
-    const int nb = (int)grid_for((uint64_t)std::max<int64_t>(n, 1), 256, 512);
-    double* mean = scratch;
-    double* partial = scratch + 1;
-    k_moments<<<nb, 256, 0, s>>>(u, n, 0, mean, partial);
-    k_moments_finish<<<1, 64, 0, s>>>(partial, nb, n, 0, k, mean, lo_hi);
-    k_moments<<<nb, 256, 0, s>>>(u, n, 1, mean, partial);
-    k_moments_finish<<<1, 64, 0, s>>>(partial, nb, n, 1, k, mean, lo_hi);
+    const int nb = (int)grid_for((uint64_t)std::max<int64_t>(n, 1), 256, MO_BLOCKS);
+    double* sums = scratch;
+    double* sq = scratch + MO_BLOCKS;
+    k_moments<<<nb, 256, 0, s>>>(u, n, 0, nullptr, sums);
+    k_moments<<<nb, 256, 0, s>>>(u, n, 1, sums, sq);
+    k_moments_finish<<<1, 256, 0, s>>>(sums, sq, nb, n, k, lo_hi);
 }
 
 void trajectory_select(const double* xi, const int32_t* offsets, int n_traj, double* util, int32_t* best,
                        hipStream_t s) {
-    k_traj_select<<<1, 64, 0, s>>>(xi, offsets, n_traj, util, best);
+    k_traj_select<<<1, 256, 0, s>>>(xi, offsets, n_traj, util, best);
 }
 
 int device_cu_count() {
