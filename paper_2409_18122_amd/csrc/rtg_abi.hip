@@ -297,7 +297,12 @@ rtg_status resolve_settings(rtg_ctx* ctx, const rtg_settings* in, rtg_settings* 
 }
 
 SetDev to_dev(const rtg_settings& s) {
-    return SetDev{s.T_min, s.alpha_min, s.alpha_max, s.z_near, s.eps2d, (float)std::log2((double)s.alpha_min),
+    const double l = std::log2((double)s.alpha_min);
+    // the band of amin_band: twice and ten times the bounds on the rounding of alpha
+    const double pw = std::max(1.0, -l);
+    const double band_e = s.alpha_min * 2.5 * (2.0 * std::log(2.0) * std::sqrt(pw) * 5.0 * 0x1p-24);
+    const double band_c = s.alpha_min * 1e-5 * std::max(1.0, pw / 8.0);
+    return SetDev{s.T_min, s.alpha_min, s.alpha_max, s.z_near, s.eps2d, (float)l, (float)band_e, (float)band_c,
                   s.isotropic};
 }
 
@@ -558,7 +563,6 @@ rtg_status ensure_pixel_state(rtg_frame* f) {
     size_t P = std::max<uint64_t>(f->L.hdr.pix_total, 1);
     RTG_TRY(f->T_final.ensure(f->ctx, 4 * P));
     RTG_TRY(f->n_last.ensure(f->ctx, 4 * P));
-    RTG_TRY(f->n_contrib.ensure(f->ctx, 4 * P));
     return RTG_OK;
 }
 
@@ -737,8 +741,7 @@ rtg_status rtg_render(rtg_ctx* ctx, rtg_frame* f, float* rgb, float* depth, floa
         return set_err(RTG_ERR_INVALID, "unc requested but the map has no uncertainty");
     hipStream_t s = (hipStream_t)stream;
     RTG_TRY(ensure_pixel_state(f));
-    RenderOut o{rgb, depth, alpha, unc, f->T_final.as<float>(), f->n_last.as<uint32_t>(),
-                f->n_contrib.as<uint32_t>()};
+    RenderOut o{rgb, depth, alpha, unc, f->T_final.as<float>(), f->n_last.as<uint32_t>(), nullptr};
     Timer tm(ctx, 3, s);
     render_forward(f->st.tile_w, f->st.tile_h, f->st.batch, f->views.as<ViewDev>(), f->n_views,
                    f->L.hdr.tiles_total, f->ranges.as<uint2>(), f->tile_ord.as<uint32_t>(), f->sorted_irec(), f->records(), to_dev(f->st), o,
@@ -848,6 +851,13 @@ rtg_status rtg_frame_stats(rtg_ctx* ctx, rtg_frame* f, int64_t out[4], void* str
     hipStream_t s = (hipStream_t)stream;
     RTG_TRY(f->stats.ensure(ctx, 2 * sizeof(unsigned long long)));
     fill_u32(f->stats.as<uint32_t>(), 0u, 4, s);
+    // the contributors are counted here, by the forward's walk without its sums
+    RTG_TRY(f->n_contrib.ensure(ctx, 4 * (size_t)std::max<uint64_t>(f->L.hdr.pix_total, 1)));
+    RenderOut o{};
+    o.n_contrib = f->n_contrib.as<uint32_t>();
+    render_forward(f->st.tile_w, f->st.tile_h, f->st.batch, f->views.as<ViewDev>(), f->n_views, f->L.hdr.tiles_total,
+                   f->ranges.as<uint2>(), f->tile_ord.as<uint32_t>(), f->sorted_irec(), f->records(), to_dev(f->st), o,
+                   f->ctr(C_FLAGS), s);
     sum_u32_pair(f->n_contrib.as<uint32_t>(), f->n_last.as<uint32_t>(), f->L.hdr.pix_total,
                  f->stats.as<unsigned long long>(), s);
     RTG_TRY(check_launch("frame stats"));
@@ -1307,8 +1317,7 @@ static rtg_status map_graph_build(rtg_ctx* ctx, const rtg_gaussians* g, const rt
     rs = enqueue_project(f, false, cs);
     if (rs == RTG_OK) rs = enqueue_bin(f, false, cs);
     if (rs == RTG_OK) {
-        RenderOut o{rgb, depth, nullptr, nullptr, f->T_final.as<float>(), f->n_last.as<uint32_t>(),
-                    f->n_contrib.as<uint32_t>()};
+        RenderOut o{rgb, depth, nullptr, nullptr, f->T_final.as<float>(), f->n_last.as<uint32_t>(), nullptr};
         render_forward(st.tile_w, st.tile_h, st.batch, f->views.as<ViewDev>(), n_views, f->L.hdr.tiles_total,
                        f->ranges.as<uint2>(), f->tile_ord.as<uint32_t>(), f->sorted_irec(), f->records(), to_dev(st), o, f->ctr(C_FLAGS), cs);
         if (eq4)

@@ -31,6 +31,7 @@ struct Header {
 struct SetDev {
     float T_min, alpha_min, alpha_max, z_near, eps2d;
     float log2_amin;  // log2(alpha_min)
+    float band_e, band_c;  // binary64 re-decision band of alpha around alpha_min (amin_band)
     int32_t isotropic;  // 1: one log-radius per Gaussian, no quaternion, r_2D = f r / d
 };
 
@@ -61,8 +62,8 @@ struct alignas(16) EmitRec {
 //          is G = exp2(-|w|^2) = exp(-d^T Sigma_2D^-1 d / 2) (no cancellation
 //          between terms for elongated splats);
 //          pixel box of alpha >= alpha_min: x = u0 | u1 << 16, y = v0 | v1 << 16;
-//   q64  = binary64 Sigma_2D^-1 (xx, xy, yy, 0), read only to re-take the
-//          alpha_min decision in binary64 when binary32 alpha is near it;
+//   q64  = binary64 Sigma_2D^-1 (xx, xy, yy) and 2 ln(o / alpha_min), read only to re-take
+//          the alpha_min decision in binary64 when binary32 alpha is near it;
 //   attr = (r, g, b, binary32 camera depth, whose bits are the sort key);
 //          written only for frames that composite colour and depth (not
 //          for scoring);
@@ -166,7 +167,7 @@ struct RenderOut {
     float *rgb, *depth, *alpha, *unc;
     float* T_final;      // per pixel
     uint32_t* n_last;    // per pixel: list position after the last contributor
-    uint32_t* n_contrib; // per pixel: number of contributing splats
+    uint32_t* n_contrib; // per pixel: number of contributing splats (then nothing else is written)
 };
 
 // out[0] += sum a[i], out[1] += sum b[i] over i < n (64-bit).

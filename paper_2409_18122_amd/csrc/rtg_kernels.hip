@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 namespace rtg {
 
@@ -256,13 +257,13 @@ __device__ inline bool project_exact(const GPre& P, const ViewDev& V, const SetD
 // through X and Y, the largest |dx| and |dy| in question) and by a relative
 // 1e-4; the extents are widened by a relative 1e-3 plus 1e-3 pixel.
 // Returns false if the rows [r0, r1] miss the support.
-__device__ __forceinline__ bool support_span(float4 g0, float4 g1, float log2_amin, float X, int r0, int r1,
+// m = (a, b, c, log2 o).
+__device__ __forceinline__ bool support_span(float mx, float my, float4 m, float log2_amin, float X, int r0, int r1,
                                              float& xl, float& xr) {
-    const float a = g1.x, b = g1.y, c = g1.z;
-    const float mx = g0.x + g0.z, my = g0.y + g0.w;
+    const float a = m.x, b = m.y, c = m.z;
     const float dy0 = (float)r0 - my, dy1 = (float)r1 - my;
     const float Y = fmaxf(fabsf(dy0), fabsf(dy1));
-    const float l = (__builtin_amdgcn_logf(g1.w) - log2_amin) * 1.0001f + 0.004f + 4e-7f * fmaf(fabsf(b), X, c * Y);
+    const float l = (m.w - log2_amin) * 1.0001f + 0.004f + 4e-7f * fmaf(fabsf(b), X, c * Y);
     const float A = fmaf(a, a, b * b);
     const float ac = a * c;
     if (!(A > 0.0f) || !(ac > 0.0f) || !(l > 0.0f) || !(A < 3e38f)) {  // not expected: no culling
@@ -291,17 +292,12 @@ __device__ __forceinline__ bool support_span(float4 g0, float4 g1, float log2_am
 // Whether a splat's support can reach a pixel of the rectangle [c0, c1] x
 // [r0, r1] (a prefilter; the per-pixel tests decide).  The mean (mx, my) and
 // the rectangle are in any common pixel frame.
-__device__ __forceinline__ bool support_meets_rect_xy(float mx, float my, float4 g1, float log2_amin, int c0,
-                                                      int c1, int r0, int r1) {
+__device__ __forceinline__ bool support_meets_rect(float mx, float my, float4 m, float log2_amin, int c0, int c1, int r0,
+                                                   int r1) {
     const float X = fmaxf(fabsf((float)c0 - mx), fabsf((float)c1 - mx));
     float xl, xr;
-    if (!support_span(make_float4(mx, my, 0.0f, 0.0f), g1, log2_amin, X, r0, r1, xl, xr)) return false;
+    if (!support_span(mx, my, m, log2_amin, X, r0, r1, xl, xr)) return false;
     return xl <= (float)c1 && xr >= (float)c0;
-}
-
-__device__ __forceinline__ bool support_meets_rect(float4 g0, float4 g1, float log2_amin, int c0, int c1, int r0,
-                                                   int r1) {
-    return support_meets_rect_xy(g0.x + g0.z, g0.y + g0.w, g1, log2_amin, c0, c1, r0, r1);
 }
 
 // Per-record constants of the support rows: on a slice at offset dy the
@@ -1101,7 +1097,7 @@ __global__ __launch_bounds__(PE_THREADS) void k_project_emit(GaussDev g, const V
             double sl = sqrt(0.5 * LOG2E);
             const float4 g1 = make_float4((float)(sl / c00), (float)(-sl * c10 / (c00 * c11)), (float)(sl / c11),
                                           (float)P.o);
-            rec.q64[pos] = make_double4(q.cyy / det, -q.cxy / det, q.cxx / det, 0.0);
+            rec.q64[pos] = make_double4(q.cyy / det, -q.cxy / det, q.cxx / det, P.rho2);
             float depth = (float)q.t[2];
             const int64_t gi = i;
             if (write_attr) {
@@ -1570,111 +1566,73 @@ __device__ __forceinline__ bool box_meets(uint2 b, int c0, int c1, int r0, int r
 // Where the support-ellipse prefilter runs.  It pays in scoring (many
 // elongated splats seen close up from arbitrary poses); on mapping frames
 // the box test alone is faster in the forward and backward passes.
-constexpr bool FWD_ELL = false, BWD_ELL = false, SCORE_ELL = true;
-
-// For a staged batch of `cnt` splats, bit k of m[k / 64] is set when splat k
-// can reach the calling wave's pixel rectangle (wave-uniform result): its box
-// meets the rectangle and, with ELL, so does its support ellipse.
-template <int NT, bool ELL>
-__device__ __forceinline__ void wave_masks(const uint2* s_pb, const float4* s_g0, const float4* s_g1,
-                                           float log2_amin, int cnt, int c0, int c1, int r0, int r1,
-                                           uint64_t (&m)[(NT + 63) / 64]) {
-    const int lane = (int)lane_id();
-#pragma unroll
-    for (int c = 0; c < (NT + 63) / 64; c++) {
-        const int e = c * 64 + lane;
-        bool hit = e < cnt && box_meets(s_pb[e], c0, c1, r0, r1);
-        if (ELL && hit) hit = support_meets_rect(s_g0[e], s_g1[e], log2_amin, c0, c1, r0, r1);
-        m[c] = __ballot(hit);
-    }
-}
-// The same selection as a list: the indices of the staged splats that can
-// reach the wave's pixel rectangle, in ascending order, written to list[0, n)
-// (n returned, wave-uniform).  A loop over the list needs no scalar
-// bit-scanning per splat.
-template <int NT, bool ELL>
-__device__ __forceinline__ int wave_list(const uint2* s_pb, const float4* s_g0, const float4* s_g1,
-                                         float log2_amin, int cnt, int c0, int c1, int r0, int r1,
-                                         uint16_t* list) {
-    const int lane = (int)lane_id();
-    int n = 0;
-#pragma unroll
-    for (int c = 0; c < (NT + 63) / 64; c++) {
-        const int e = c * 64 + lane;
-        bool hit = e < cnt && box_meets(s_pb[e], c0, c1, r0, r1);
-        if (ELL && hit) hit = support_meets_rect(s_g0[e], s_g1[e], log2_amin, c0, c1, r0, r1);
-        const uint64_t m = __ballot(hit);
-        if (hit) list[n + (int)__popcll(m & lanemask_lt())] = (uint16_t)e;
-        n += (int)__popcll(m);
-    }
-    return n;
-}
-
-// Next P set bits of a wave-uniform mask (entries past the last are -1).
-template <int P>
-__device__ __forceinline__ void pop_n(uint64_t& mm, int base, int (&ks)[P]) {
-#pragma unroll
-    for (int q = 0; q < P; q++) {
-        if (mm) {
-            ks[q] = base + (int)__builtin_ctzll(mm);
-            mm &= mm - 1;
-        } else {
-            ks[q] = -1;
-        }
-    }
-}
+constexpr bool FWD_ELL = false, SCORE_ELL = true;
 
 // Splats evaluated per step of the front-to-back loops: their alphas are
 // independent of the pixel state, so they overlap; the updates follow in order.
 constexpr int FWD_STEP = 2;
 // The scoring loop's (it keeps only T and one sum per pixel).
 constexpr int SCORE_STEP = 2;
-// Splats per step of the back-to-front backward loop (four measured slower:
-// the registers cut occupancy); the reduction below is written for two.
-constexpr int BWD_STEP = 2;
-// Relative band around alpha_min inside which the skip decision is re-taken
-// in binary64 (far wider than the binary32 error of alpha).
-constexpr float REFINE = 2e-3f;
+// Half width of the band around alpha_min inside which a splat's skip decision is re-taken in binary64:
+// twice the rounding of its binary32 alpha or more.  With m the staged mean (relative to the block's origin, so a
+// pixel's offset is below |m| + 32) and M = [[a, 0], [b, c]], the whitened offset w = M d is off by at most
+// 5 2^-24 E, E = (a + |b|) (|m_x| + 32) + c (|m_y| + 32), so near the threshold, where |w|^2 = log2(o /
+// alpha_min), alpha is off by a relative 2 ln 2 sqrt(log2(1 / alpha_min)) 5 2^-24 E, plus a few 2^-24 for the
+// squares, the exponential and the opacity: st.band_e E + st.band_c (absolute; band_coefficients).
+// A relative 2e-3 for every splat, which covers needles whose mean is thousands of pixels away, sent one
+// alpha in 1,400 to the binary64 branch: every third step of the backward's 512 alphas.
+__device__ __forceinline__ float amin_band(float mx, float my, float a, float b, float c, const SetDev& st) {
+    const float E = fmaf(a + fabsf(b), fabsf(mx) + 32.0f, c * (fabsf(my) + 32.0f));
+    return fmaf(st.band_e, E, st.band_c);
+}
 
-// Whether binary32 alpha a lies in that band: |a - alpha_min| <= band, with
-// band = REFINE alpha_min (a subtraction and a compare of the magnitude).
+// Whether binary32 alpha a lies in that band.
 __device__ __forceinline__ bool near_amin(float a, float amin, float band) { return fabsf(a - amin) <= band; }
 
+// A uniform value in a vector register: an instruction that reads a scalar register takes four cycles
+// a wave where one of vector registers and constants takes two (additions, products and their fusions).
+__device__ __forceinline__ float in_vgpr(float x) {
+    asm("" : "+v"(x));
+    return x;
+}
+
 // The alpha_min test: a splat with alpha < alpha_min at a pixel is skipped
-// there.  Where binary32 alpha lies in [alpha_min (1 - REFINE), alpha_min
-// (1 + REFINE)] the decision is re-taken in binary64 from the binary64 conic
+// there.  Where binary32 alpha lies within the splat's band of alpha_min
+// the decision is re-taken in binary64 from the binary64 conic
 // (kept64), as the definition states it.  No pixel box test is needed: the
 // box is the exact bounding box of the support, so outside it alpha <
 // alpha_min already.  The loops take the rare binary64 branch once per
 // step, for all the splats of the step.
 
-__device__ __forceinline__ bool kept64(float4 g0, float4 g1, const double4* __restrict__ q64, uint32_t r, float px,
-                                       float py, const SetDev& st) {
-    const float amin = st.alpha_min;
+// alpha >= alpha_min, i.e. o exp(-power / 2) >= alpha_min (alpha_max is above it), is taken as power <= 2 ln(o /
+// alpha_min), the bound that the projection formed for the support box (q64.w): no exponential, whose
+// temporaries set the compositing kernels' register count.
+__device__ __forceinline__ bool kept64(float4 g0, const double4* __restrict__ q64, uint32_t r, float px, float py) {
     const double4 q = q64[r];
     const double dx = ((double)px - (double)g0.x) - (double)g0.z;
     const double dy = ((double)py - (double)g0.y) - (double)g0.w;
     const double pw = (q.x * dx * dx + 2.0 * q.y * dx * dy) + q.z * dy * dy;
-    const double ad = fmin((double)st.alpha_max, (double)g1.w * exp(-0.5 * pw));
-    return ad >= (double)amin;
+    return pw <= q.w;
 }
 
 // Staged form of a splat for the pair loops of the forward and scoring
 // kernels: p = (mean x, mean y relative to the block origin, M00, M10),
-// q = (M11, opacity, u, log2 opacity).  Slot NB of the staged arrays holds
-// the null splat (opacity 0, log2 opacity -3e38): alpha 0 at every pixel, far
-// from alpha_min's band, so it never contributes.
-__device__ __forceinline__ void stage_splat(const EmitRec& e, int ox, int oy, float4& p, float4& q) {
+// q = (M11, opacity or its log2 (LOG), u, band of alpha_min).  Slot NB of the staged arrays holds
+// the null splat (opacity 0, log2 opacity -3e38, band 0): alpha 0 at every pixel, so it never
+// contributes.
+template <bool LOG>
+__device__ __forceinline__ void stage_splat(const EmitRec& e, int ox, int oy, const SetDev& st, float4& p, float4& q) {
     const float4 m = rel_mean(e.g0, ox, oy);
     p = make_float4(m.x, m.y, e.g1.x, e.g1.y);
-    q = make_float4(e.g1.z, e.g1.w, __uint_as_float(e.unc), __builtin_amdgcn_logf(e.g1.w));
+    q = make_float4(e.g1.z, LOG ? __builtin_amdgcn_logf(e.g1.w) : e.g1.w, __uint_as_float(e.unc),
+                    amin_band(m.x, m.y, e.g1.x, e.g1.y, e.g1.z, st));
 }
 
-template <int NB>
+template <int NB, bool LOG>
 __device__ __forceinline__ void stage_null_splat(float4* s_p, float4* s_q) {
     if (threadIdx.x == 0) {
         s_p[NB] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        s_q[NB] = make_float4(0.0f, 0.0f, 0.0f, -3e38f);
+        s_q[NB] = make_float4(0.0f, LOG ? -3e38f : 0.0f, 0.0f, 0.0f);
     }
 }
 
@@ -1697,7 +1655,7 @@ __device__ __forceinline__ int splat_list(const uint2* s_pb, const float4* s_p, 
         bool hit = e < cnt && box_meets(s_pb[e], c0 + ox, c1 + ox, r0 + oy, r1 + oy);
         if (ELL && hit) {
             const float4 p = s_p[e], q = s_q[e];
-            hit = support_meets_rect_xy(p.x, p.y, make_float4(p.z, p.w, q.x, q.y), log2_amin, c0, c1, r0, r1);
+            hit = support_meets_rect(p.x, p.y, make_float4(p.z, p.w, q.x, q.y), log2_amin, c0, c1, r0, r1);
         }
         const uint64_t m = __ballot(hit);
         if (hit) list[n + (int)__popcll(m & lanemask_lt())] = (uint32_t)(e * sizeof(float4));
@@ -1712,23 +1670,28 @@ __device__ __forceinline__ int splat_list(const uint2* s_pb, const float4* s_p, 
 // alpha_min (its binary32 alpha lies within the band, below the binary64
 // value), one it drops with alpha 0.
 __device__ __forceinline__ float redecide(float a, const Records& rec, uint32_t r, int u, int v, const SetDev& st) {
-    const EmitRec& e = rec.emit[r];
-    return kept64(e.g0, e.g1, rec.q64, r, (float)u, (float)v, st) ? fmaxf(a, st.alpha_min) : 0.0f;
+    return kept64(rec.emit[r].g0, rec.q64, r, (float)u, (float)v) ? fmaxf(a, st.alpha_min) : 0.0f;
 }
 
 // B splats are staged per batch (B <= TW * TH; threads below B load them).
-// Register budget: at most 80 VGPRs, six waves per SIMD (a 640x480 frame of
-// 16x16 tiles brings 4.7 waves per SIMD, larger frames many more).
 // UNC: the uncertainty image is requested (otherwise it is not composited).
+// COUNT: only the number of contributing splats per pixel is wanted.
 //
 // Front to back over the wave's list, FWD_STEP splats per step: their alphas
 // are independent of the pixel state, the updates follow in order.  A pixel
 // whose next transmittance would fall below T_min stops there; its T is then
 // kept negated (|T| is the final transmittance), which no later update
-// passes, so the loop carries no per-pixel flags.  A splat below alpha_min
-// enters with alpha 0 (T unchanged, exactly) and is not counted.
-template <int TW, int TH, int B, bool UNC>
-__global__ __launch_bounds__(TW * TH, 6) void k_render_fwd(const ViewDev* __restrict__ views, int n_views,
+// passes, so the loop carries no per-pixel flags; the pixels still live are those of the last
+// update's comparison, a scalar mask.  A splat below alpha_min
+// enters with alpha 0 (T unchanged, exactly).
+//
+// Bound by instruction issue (cycles per wave: additions, products and their fusions 2; comparisons, selects,
+// minima and maxima, and anything with a scalar register 4; exp2 8).  So the thresholds sit in vector
+// registers, a batch whose splats are all at most alpha_max opaque leaves the clamp out, and the
+// contributors are counted only for the work counters.  8 keyframes of 1280x720, with the narrower band
+// of the binary64 branch and 64 instead of 80 VGPRs (eight waves per SIMD): 1,172 -> 1,027 us.
+template <int TW, int TH, int B, bool UNC, bool COUNT = false>
+__global__ __launch_bounds__(TW * TH, 8) void k_render_fwd(const ViewDev* __restrict__ views, int n_views,
                                                         const uint2* __restrict__ ranges,
                                                         const uint32_t* __restrict__ tile_order,
                                                         const uint32_t* __restrict__ inst_rec,
@@ -1739,13 +1702,13 @@ __global__ __launch_bounds__(TW * TH, 6) void k_render_fwd(const ViewDev* __rest
     static_assert(32 % TW == 0 && 16 % TH == 0, "tiles must divide the 32 x 16 origin block");
     static_assert(FWD_STEP == 2, "the list is padded for steps of two");
     if (flags && *flags) return;
-    __shared__ float4 s_p[B + 1], s_q[B + 1], s_at[B + 1];
-    __shared__ uint32_t s_r[B];
+    __shared__ float4 s_p[B + 1], s_q[B + 1], s_at[COUNT ? 1 : B + 1];
+    __shared__ uint32_t s_r[B + 1];
     __shared__ uint2 s_pb[B];
     __shared__ __align__(8) uint32_t s_list[NT / 64 * (B + 2)];
-    stage_null_splat<B>(s_p, s_q);
-    if (threadIdx.x == 0) s_at[B] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    const uint32_t tile = tile_order ? tile_order[blockIdx.x] : blockIdx.x;
+    stage_null_splat<B, false>(s_p, s_q);
+    if (!COUNT && threadIdx.x == 0) s_at[B] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const uint32_t tile = tile_order[blockIdx.x];
     const uint32_t vi = view_of_tile(views, n_views, tile);
     const ViewDev& V = views[vi];
     const int W = V.W, H = V.H;
@@ -1759,8 +1722,7 @@ __global__ __launch_bounds__(TW * TH, 6) void k_render_fwd(const ViewDev* __rest
     const int wr0 = ty * TH + (int)(threadIdx.x >> 6) * (64 / TW) - oy, wr1 = wr0 + 64 / TW - 1;
     const bool inside = u < W && v < H;
     const float lx = (float)(u - ox), ly = (float)(v - oy);
-    const float amin = st.alpha_min, amax = st.alpha_max, tmin = st.T_min;
-    const float band = REFINE * amin;
+    const float amin = in_vgpr(st.alpha_min), tmin = in_vgpr(st.T_min), amax = st.alpha_max;
     const char* sp = reinterpret_cast<const char*>(s_p);
     const char* sq = reinterpret_cast<const char*>(s_q);
     const char* sa = reinterpret_cast<const char*>(s_at);
@@ -1770,75 +1732,90 @@ __global__ __launch_bounds__(TW * TH, 6) void k_render_fwd(const ViewDev* __rest
     for (uint32_t b = rg.x; b < rg.y; b += B) {
         if (__syncthreads_count(T > 0.0f) == 0) break;
         uint32_t idx = b + threadIdx.x;
+        bool opaque = false;
         if (threadIdx.x < (uint32_t)B && idx < rg.y) {
             uint32_t r = inst_rec[idx];
             s_r[threadIdx.x] = r;
             const EmitRec e = rec.emit[r];
             s_pb[threadIdx.x] = e.pbox;
-            stage_splat(e, ox, oy, s_p[threadIdx.x], s_q[threadIdx.x]);
-            s_at[threadIdx.x] = rec.attr[r];
+            opaque = e.g1.w > amax;
+            stage_splat<false>(e, ox, oy, st, s_p[threadIdx.x], s_q[threadIdx.x]);
+            if (!COUNT) s_at[threadIdx.x] = rec.attr[r];
         }
-        __syncthreads();
+        const bool clamped = __builtin_amdgcn_readfirstlane(__syncthreads_or(opaque));
         const int cnt = (int)min<uint32_t>(B, rg.y - b);
         uint32_t* my = s_list + (threadIdx.x >> 6) * (B + 2);
         int nl = 0;
-        if (__ballot(T > 0.0f))
+        uint64_t alive = __ballot(T > 0.0f);
+        if (alive)
             nl = splat_list<B, FWD_ELL>(s_pb, s_p, s_q, st.log2_amin, cnt, wc0, wc1, wr0, wr1, ox, oy, my);
         __syncthreads();  // the wave's list is in LDS
         // LDS offset of the last splat this lane took in this batch
         uint32_t lastoff = 0xffffffffu;
-        for (int i = 0; i < nl; i += FWD_STEP) {
-            if (!__ballot(T > 0.0f)) break;
-            uint32_t ko[FWD_STEP];
-            float as[FWD_STEP];
-            bool need = false;
+        auto walk = [&](auto clamp) {
+            for (int i = 0; i < nl && alive; i += FWD_STEP) {
+                uint32_t ko[FWD_STEP];
+                float as[FWD_STEP], bs[FWD_STEP];
+                bool need = false;
 #pragma unroll
-            for (int q = 0; q < FWD_STEP; q++) {
-                ko[q] = my[i + q];
-                const float4 pp = *reinterpret_cast<const float4*>(sp + ko[q]);
-                const float4 qq = *reinterpret_cast<const float4*>(sq + ko[q]);
-                float G, dx, dy, w1, w2;
-                as[q] = splat_alpha(pp.x, pp.y, make_float4(pp.z, pp.w, qq.x, qq.y), lx, ly, amax, G, dx, dy, w1,
-                                    w2);
-                need = need | near_amin(as[q], amin, band);
-            }
-            if (__ballot(need)) {
-#pragma unroll
-                for (int q = 0; q < FWD_STEP; q++)
-                    if (near_amin(as[q], amin, band) & (ko[q] < B * sizeof(float4)))
-                        as[q] = redecide(as[q], rec, s_r[ko[q] / sizeof(float4)], u, v, st);
-            }
-#pragma unroll
-            for (int q = 0; q < FWD_STEP; q++) {
-                const bool ok = as[q] >= amin;
-                const float a0 = ok ? as[q] : 0.0f;
-                const float Tn = fmaf(-a0, T, T);
-                const bool live = Tn >= tmin;
-                const bool use = ok & live;
-                // weight 0 where the splat is skipped (a0 = 0) or the pixel
-                // stops: fmaf(x, 0, c) = c for the finite staged attributes,
-                // so the sums need no per-channel select
-                const float w = live ? a0 * T : 0.0f;
-                const float4 at = *reinterpret_cast<const float4*>(sa + ko[q]);
-                c0 = fmaf(at.x, w, c0);
-                c1 = fmaf(at.y, w, c1);
-                c2 = fmaf(at.z, w, c2);
-                dd = fmaf(at.w, w, dd);
-                if (UNC) {
-                    const float uk = *reinterpret_cast<const float*>(sq + ko[q] + 8);
-                    uu = fmaf(uk, w, uu);
+                for (int q = 0; q < FWD_STEP; q++) {
+                    ko[q] = my[i + q];
+                    const float4 pp = *reinterpret_cast<const float4*>(sp + ko[q]);
+                    const float4 qq = *reinterpret_cast<const float4*>(sq + ko[q]);
+                    float G, dx, dy, w1, w2;
+                    as[q] = splat_alpha<decltype(clamp)::value>(pp.x, pp.y, make_float4(pp.z, pp.w, qq.x, qq.y), lx, ly,
+                                                                amax, G, dx, dy, w1, w2);
+                    bs[q] = qq.w;
+                    need = need | near_amin(as[q], amin, bs[q]);
                 }
-                lastoff = use ? ko[q] : lastoff;
-                ncontrib += use ? 1u : 0u;
-                T = live ? Tn : -fabsf(T);
+                if (__ballot(need)) {
+#pragma unroll
+                    for (int q = 0; q < FWD_STEP; q++)
+                        if (near_amin(as[q], amin, bs[q]))
+                            as[q] = redecide(as[q], rec, s_r[ko[q] / sizeof(float4)], u, v, st);
+                }
+#pragma unroll
+                for (int q = 0; q < FWD_STEP; q++) {
+                    const bool ok = as[q] >= amin;
+                    const float a0 = ok ? as[q] : 0.0f;
+                    const float Tn = fmaf(-a0, T, T);
+                    const bool live = Tn >= tmin;
+                    const bool use = ok & live;
+                    if constexpr (COUNT) {
+                        ncontrib += use ? 1u : 0u;
+                    } else {
+                        // weight 0 where the splat is skipped (a0 = 0) or the pixel
+                        // stops: fmaf(x, 0, c) = c for the finite staged attributes,
+                        // so the sums need no per-channel select
+                        const float w = live ? a0 * T : 0.0f;
+                        const float4 at = *reinterpret_cast<const float4*>(sa + ko[q]);
+                        c0 = fmaf(at.x, w, c0);
+                        c1 = fmaf(at.y, w, c1);
+                        c2 = fmaf(at.z, w, c2);
+                        dd = fmaf(at.w, w, dd);
+                        if (UNC) {
+                            const float uk = *reinterpret_cast<const float*>(sq + ko[q] + 8);
+                            uu = fmaf(uk, w, uu);
+                        }
+                        lastoff = use ? ko[q] : lastoff;
+                    }
+                    T = live ? Tn : -fabsf(T);
+                    if (q + 1 == FWD_STEP) alive = __ballot(live);
+                }
             }
-        }
-        if (lastoff != 0xffffffffu) last = b - rg.x + 1 + lastoff / (uint32_t)sizeof(float4);
+        };
+        if (clamped) walk(BoolC<true>{});
+        else walk(BoolC<false>{});
+        if (!COUNT && lastoff != 0xffffffffu) last = b - rg.x + 1 + lastoff / (uint32_t)sizeof(float4);
     }
     if (!inside) return;
     T = fabsf(T);
     const uint64_t P = (uint64_t)W * H;
     const uint64_t pix = V.pix_off + (uint64_t)v * W + u;
+    if constexpr (COUNT) {
+        out.n_contrib[pix] = ncontrib;
+        return;
+    }
     if (out.rgb) {
         float* base = out.rgb + 3 * V.pix_off + (uint64_t)v * W + u;
         base[0] = c0;
@@ -1850,7 +1827,6 @@ __global__ __launch_bounds__(TW * TH, 6) void k_render_fwd(const ViewDev* __rest
     if (out.unc) out.unc[pix] = uu;
     if (out.T_final) out.T_final[pix] = T;
     if (out.n_last) out.n_last[pix] = last;
-    if (out.n_contrib) out.n_contrib[pix] = ncontrib;
 }
 
 // ----------------------------------------------------------------- loss
@@ -1928,105 +1904,15 @@ __global__ __launch_bounds__(SP_THREADS) void k_sum_partials(const double* __res
 // Reverse mode of the compositing, walking each tile back to front; the
 // transmittance before splat i is recovered as T_{i+1} / (1 - a_i).
 
-// Sum over the 64 lanes of a wave with DPP moves (result valid in lane 63,
-// returned to every lane).  Rows of 16: quad swaps, rotations by 4 and 8,
-// then row broadcasts 15 and 31 accumulate rows into row 3.
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ float dpp_mov(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xf, false));
+// Orders a wave's LDS stores and loads (a compiler's matter: the hardware keeps them in order).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-__device__ __forceinline__ float wave_sum_dpp(float x) {
-    x += dpp_mov<0xb1>(x);        // quad_perm [1, 0, 3, 2]
-    x += dpp_mov<0x4e>(x);        // quad_perm [2, 3, 0, 1]
-    x += dpp_mov<0x124>(x);       // row_ror 4
-    x += dpp_mov<0x128>(x);       // row_ror 8
-    x += dpp_mov<0x142, 0xa>(x);  // row_bcast 15 into rows 1 and 3
-    x += dpp_mov<0x143, 0xc>(x);  // row_bcast 31 into rows 2 and 3
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
-}
-
-// Sums each of n per-lane values over the wave (the same DPP steps as
-// wave_sum_dpp, applied to all values step by step so they overlap).
-template <int N>
-__device__ __forceinline__ void wave_sum_dpp_n(float* x) {
-#pragma unroll
-    for (int i = 0; i < N; i++) x[i] += dpp_mov<0xb1>(x[i]);
-#pragma unroll
-    for (int i = 0; i < N; i++) x[i] += dpp_mov<0x4e>(x[i]);
-#pragma unroll
-    for (int i = 0; i < N; i++) x[i] += dpp_mov<0x124>(x[i]);
-#pragma unroll
-    for (int i = 0; i < N; i++) x[i] += dpp_mov<0x128>(x[i]);
-#pragma unroll
-    for (int i = 0; i < N; i++) x[i] += dpp_mov<0x142, 0xa>(x[i]);
-#pragma unroll
-    for (int i = 0; i < N; i++) x[i] += dpp_mov<0x143, 0xc>(x[i]);
-#pragma unroll
-    for (int i = 0; i < N; i++) x[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[i]), 63));
-}
-
-// Sums 20 per-lane values over the wave by recursive halving: at each of six
-// steps a lane keeps half of its values, sends the other half to its partner
-// and adds the partner's copy of the kept half.  Partners must agree on every
-// earlier choice, so the DPP pairings that flip several lane bits come first:
-// row_mirror (decided by lane bit 3), row_half_mirror (bit 2), then quad
-// swaps xor 2 (bit 1) and xor 1 (bit 0), then the row swaps of gfx950 across
-// 16 lanes (bit 4) and 32 lanes (sum).  Lane l ends with the total of value
-// v = 10 b3 + 5 b2 + 3 b1 + 2 b0 + b4, valid when 2 b0 + b4 < (b1 ? 2 : 3)
-// (else v = -1); lanes l and l + 32 hold the same total.
-//
-// v_permlane16_swap(x, y) exchanges the odd 16-lane rows of x with the even
-// rows of y, so the two results add up, in every lane, to x[l] + x[l ^ 16] on
-// even rows and y[l ^ 16] + y[l] on odd rows; v_permlane32_swap(x, x) likewise
-// gives x[l] + x[l ^ 32].  Both are VALU moves, not LDS round trips.
-__device__ __forceinline__ float wave_sum_halving20(const float* x, int lane, int& v) {
-    const bool b0 = lane & 1, b1 = (lane >> 1) & 1, b2 = (lane >> 2) & 1, b3 = (lane >> 3) & 1,
-               b4 = (lane >> 4) & 1;
-    float a[10], c[5], d[3], e[2];
-#pragma unroll
-    for (int j = 0; j < 10; j++) {
-        const float keep = b3 ? x[10 + j] : x[j], send = b3 ? x[j] : x[10 + j];
-        a[j] = keep + dpp_mov<0x140>(send);  // row_mirror
-    }
-#pragma unroll
-    for (int j = 0; j < 5; j++) {
-        const float keep = b2 ? a[5 + j] : a[j], send = b2 ? a[j] : a[5 + j];
-        c[j] = keep + dpp_mov<0x141>(send);  // row_half_mirror
-    }
-#pragma unroll
-    for (int j = 0; j < 3; j++) {  // halves {0, 1, 2} and {3, 4, pad}
-        const float hi = j + 3 < 5 ? c[j + 3] : 0.0f;
-        const float keep = b1 ? hi : c[j], send = b1 ? c[j] : hi;
-        d[j] = keep + dpp_mov<0x4e>(send);  // quad_perm [2, 3, 0, 1]
-    }
-#pragma unroll
-    for (int j = 0; j < 2; j++) {  // halves {0, 1} and {2, pad}
-        const float hi = j + 2 < 3 ? d[j + 2] : 0.0f;
-        const float keep = b0 ? hi : d[j], send = b0 ? d[j] : hi;
-        e[j] = keep + dpp_mov<0xb1>(send);  // quad_perm [1, 0, 3, 2]
-    }
-    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(e[0]), __float_as_uint(e[1]), false, false);
-    const float f = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
-    const int pos = 2 * (int)b0 + (int)b4;
-    v = pos < (b1 ? 2 : 3) ? 10 * (int)b3 + 5 * (int)b2 + 3 * (int)b1 + pos : -1;
-    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(f), __float_as_uint(f), false, false);
-    return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
-}
-
-// Highest set bit of a wave-uniform mask array, cleared; -1 if none.
-template <int NW>
-__device__ __forceinline__ int pop_high(uint64_t (&m)[NW]) {
-    // static indices only, so that m stays in registers
-    int k = -1;
-#pragma unroll
-    for (int c = 0; c < NW; c++)
-        if (m[c]) k = c * 64 + 63 - (int)__builtin_clzll(m[c]);
-#pragma unroll
-    for (int c = 0; c < NW; c++)
-        if (k >= 0 && c == (k >> 6)) m[c] &= ~(1ull << (k & 63));
-    return k;
-}
+// Words between the rows of the backward's reduction in LDS: rows r to r + 15 start 4 banks apart each, so
+// 16-byte reads of 16 rows meet no bank twice.
+constexpr int RED_STRIDE = 68;
 
 // One pixel's step of the reverse compositing recursion for a kept splat i.
 // With T = T_{i+1} (transmittance behind it), T_i = T / (1 - a_i) and the
@@ -2038,7 +1924,7 @@ __device__ __forceinline__ int pop_high(uint64_t (&m)[NW]) {
 // 1 - a_i is a normal number well away from zero and the hardware reciprocal
 // (within 1 ulp) stands in for the correctly rounded division; T only scales
 // gradient terms here and decides nothing.
-// Per-lane sums acc (the record's gradient slots, in this order), with
+// The sums over the pixels (the record's gradient slots, in this order), with
 // t = dL/da a_g, where a_g = o G is the splat's alpha where it is not clamped
 // at alpha_max (then da/dpower = -a_g / 2 and da/do = a_g / o) and 0 where it
 // is (no gradient flows through the clamp):
@@ -2051,12 +1937,12 @@ __device__ __forceinline__ int pop_high(uint64_t (&m)[NW]) {
 //   6..9: sum g_ch w (colour and depth).
 // A splat with a = 0 and a_g = 0 leaves T (1 / (1 - 0) = 1 exactly), D and
 // every sum unchanged, for finite pixel gradients and colours.
+// Returns t and adds the colour and depth sums to col.
 // AU: the alpha and uncertainty images carry gradients too (colour 1 and u
 // in GA; otherwise their terms are left out altogether).
-template <bool AU, bool FIRST = false>
-__device__ __forceinline__ void bwd_pixel(float a, float ag, float dx, float dy, float4 at, float ui, float gr,
-                                          float gg, float gb, float gd, float ga, float gu, float& T, float& D,
-                                          float* acc) {
+template <bool AU, bool FIRST>
+__device__ __forceinline__ float bwd_pixel(float a, float ag, float4 at, float ui, float gr, float gg, float gb,
+                                           float gd, float ga, float gu, float& T, float& D, float* col) {
     const float inv = __builtin_amdgcn_rcpf(1.0f - a);
     const float Ti = T * inv;
     const float w = a * Ti;
@@ -2071,41 +1957,31 @@ __device__ __forceinline__ void bwd_pixel(float a, float ag, float dx, float dy,
     const float da = fmaf(Ti, GA, -(D * inv));
     D = fmaf(w, GA, D);
     T = Ti;
-    const float t0 = da * ag;
-    const float t1 = t0 * dx, t2 = t0 * dy;
-    if constexpr (FIRST) {
-        acc[6] = gr * w;
-        acc[7] = gg * w;
-        acc[8] = gb * w;
-        acc[9] = gd * w;
-        acc[5] = t0;
-        acc[0] = t1;
-        acc[1] = t2;
-        acc[2] = t1 * dx;
-        acc[3] = t1 * dy;
-        acc[4] = t2 * dy;
-    } else {
-        acc[6] = fmaf(gr, w, acc[6]);
-        acc[7] = fmaf(gg, w, acc[7]);
-        acc[8] = fmaf(gb, w, acc[8]);
-        acc[9] = fmaf(gd, w, acc[9]);
-        acc[5] += t0;
-        acc[0] += t1;
-        acc[1] += t2;
-        acc[2] = fmaf(t1, dx, acc[2]);
-        acc[3] = fmaf(t1, dy, acc[3]);
-        acc[4] = fmaf(t2, dy, acc[4]);
-    }
+    col[0] = FIRST ? gr * w : fmaf(gr, w, col[0]);
+    col[1] = FIRST ? gg * w : fmaf(gg, w, col[1]);
+    col[2] = FIRST ? gb * w : fmaf(gb, w, col[2]);
+    col[3] = FIRST ? gd * w : fmaf(gd, w, col[3]);
+    return da * ag;
 }
 
-// NW waves per tile; the tile's 8x8 pixel blocks are dealt to the waves in
-// row-major order (PPT blocks each) and a lane owns one pixel per block.
-// Splats are staged per batch for the whole workgroup; a wave visits only
-// the splats whose support can reach its blocks (ballot masks per batch).  Per
-// splat, the lane sums its pixels' contributions, the wave reduces them once
-// with DPP and one lane adds the 10 totals to the record's binary64 gradient.
-template <int TW, int TH, int NW, bool AU>
-__global__ __launch_bounds__(64 * NW, AU ? 1 : 3) void k_render_bwd(const ViewDev* __restrict__ views, int n_views,
+// One wave takes a tile, or one of the NSUB bands of rows a tile is cut into (a workgroup each), and a
+// lane PPT neighbouring pixels of one row.  The staging lanes keep only the splats whose box meets the
+// band and write them compacted, in ascending order, to LDS; the walk back to front is a countdown over them,
+// two per step.  Slot B holds the null splat: position 0xffffffff (no pixel takes it), zero geometry and
+// colour.
+//
+// Bound by instruction issue (cycles per wave as at k_render_fwd; a DPP addition 4, a row swap 8).  A lane's
+// pixels share their row, so the offset dy and its product are formed
+// once a splat, and the sums over d follow from three moments of t along the row: with A = dx of the first
+// pixel, sum t dx = A s0 + s1, sum t dx^2 = A (sum t dx + s1) + s2, where s_k = sum_j j^k t_j, and dy is a
+// factor of the rest: 13 instructions for four pixels instead of 26 to 32 when every pixel forms its
+// own products.  The rounding stays that of sums of their terms (A + j is the offset itself).
+// The 20 sums of a step are added up over the lanes through LDS, which is otherwise idle: about 90 cycles of vector
+// instructions; halving them lane by lane with DPP additions and selects took about 250.
+// 8 keyframes of 1280x720, with the narrower band of the binary64 branch and four waves per SIMD (128 VGPRs,
+// 158 before): 2,264 -> 2,000 us, of which the atomics are 70 us; one 640x480 frame in two bands: 134 -> 106 us.
+template <int TW, int TH, int NSUB, bool AU>
+__global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __restrict__ views, int n_views,
                                                         const uint2* __restrict__ ranges,
                                                         const uint32_t* __restrict__ tile_order,
                                                         const uint32_t* __restrict__ inst_rec, Records rec,
@@ -2116,213 +1992,17 @@ __global__ __launch_bounds__(64 * NW, AU ? 1 : 3) void k_render_bwd(const ViewDe
                                                         const float* __restrict__ d_alpha,
                                                         const float* __restrict__ d_unc, double* __restrict__ g2d,
                                                         const uint32_t* __restrict__ flags) {
-    constexpr int NB8 = TW * TH / 64;
-    constexpr int PPT = NB8 / NW;
-    constexpr int B = 64 * NW;
-    static_assert(PPT >= 1 && PPT * NW == NB8, "waves must split the 8x8 blocks evenly");
-    if (flags && *flags) return;
-    __shared__ float4 s_g0[B], s_g1[B], s_at[B];
-    __shared__ float s_u[B];
-    __shared__ uint32_t s_r[B];
-    __shared__ uint2 s_pb[B];
-    __shared__ uint32_t s_max;
-    const uint32_t tile = tile_order ? tile_order[blockIdx.x] : blockIdx.x;
-    const uint32_t vi = view_of_tile(views, n_views, tile);
-    const ViewDev& V = views[vi];
-    const int W = V.W, H = V.H;
-    const uint32_t lt = tile - V.tile_off;
-    const int tx = (int)(lt % (uint32_t)V.tiles_x), ty = (int)(lt / (uint32_t)V.tiles_x);
-    const uint2 rg = ranges[tile];
-    const uint64_t P = (uint64_t)W * H;
-    const int lane = (int)(threadIdx.x & 63), wave = NW == 1 ? 0 : (int)(threadIdx.x >> 6);
-
-    // pixel j of this lane: (px0 + bx(j), py0 + by(j)) relative to the block
-    // origin, block offsets that are constants when the tile has one wave
-    const int ox = origin_x(tx * TW), oy = origin_y(ty * TH);
-    const float px0 = (float)(tx * TW - ox + (lane & 7)), py0 = (float)(ty * TH - oy + (lane >> 3));
-    auto bx = [&](int j) { return (float)(((wave * PPT + j) % (TW / 8)) * 8); };
-    auto by = [&](int j) { return (float)(((wave * PPT + j) / (TW / 8)) * 8); };
-    auto ux = [&](int j) { return tx * TW + ((wave * PPT + j) % (TW / 8)) * 8 + (lane & 7); };
-    auto vy = [&](int j) { return ty * TH + ((wave * PPT + j) / (TW / 8)) * 8 + (lane >> 3); };
-    float T[PPT];
-    uint32_t last[PPT];
-    float gr[PPT], gg[PPT], gb[PPT], gd[PPT], ga[PPT], gu[PPT];
-    float D[PPT];
-    uint32_t mylast = 0;
-    int wc0 = 1 << 30, wc1 = -1, wr0 = 1 << 30, wr1 = -1;  // the wave's pixel rectangle
-#pragma unroll
-    for (int j = 0; j < PPT; j++) {
-        const int blk = wave * PPT + j;
-        const int bx0 = tx * TW + (blk % (TW / 8)) * 8, by0 = ty * TH + (blk / (TW / 8)) * 8;
-        wc0 = min(wc0, bx0);
-        wc1 = max(wc1, bx0 + 7);
-        wr0 = min(wr0, by0);
-        wr1 = max(wr1, by0 + 7);
-        const int u = bx0 + (lane & 7), v = by0 + (lane >> 3);
-        T[j] = 1.0f;
-        last[j] = 0;
-        gr[j] = gg[j] = gb[j] = gd[j] = ga[j] = gu[j] = 0.0f;
-        D[j] = 0.0f;
-        if (u < W && v < H) {
-            const uint64_t pix = V.pix_off + (uint64_t)v * W + u;
-            T[j] = T_final[pix];
-            last[j] = n_last[pix];
-            if (d_rgb) {
-                const float* cb = d_rgb + 3 * V.pix_off + (uint64_t)v * W + u;
-                gr[j] = cb[0];
-                gg[j] = cb[P];
-                gb[j] = cb[2 * P];
-            }
-            if (d_depth) gd[j] = d_depth[pix];
-            if (AU && d_alpha) ga[j] = d_alpha[pix];
-            if (AU && d_unc) gu[j] = d_unc[pix];
-        }
-        mylast = max(mylast, last[j]);
-    }
-    if (threadIdx.x == 0) s_max = 0;
-    __syncthreads();
-    if (mylast) atomicMax(&s_max, mylast);
-    __syncthreads();
-    const uint32_t maxlast = s_max;
-    uint32_t wave_last = mylast;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) wave_last = max(wave_last, (uint32_t)__shfl_xor((int)wave_last, o, 64));
-    const float amax = st.alpha_max;
-    const float band = REFINE * st.alpha_min;
-
-    for (int64_t bend = maxlast; bend > 0; bend -= B) {
-        const int64_t bstart = bend - B > 0 ? bend - B : 0;
-        __syncthreads();
-        {
-            const int64_t e = bstart + threadIdx.x;
-            if (e < bend) {
-                const uint32_t r = inst_rec[rg.x + (uint32_t)e];
-                s_r[threadIdx.x] = r;
-                const EmitRec e = rec.emit[r];
-                s_pb[threadIdx.x] = e.pbox;
-                s_g0[threadIdx.x] = rel_mean(e.g0, ox, oy);
-                s_g1[threadIdx.x] = e.g1;
-                s_at[threadIdx.x] = rec.attr[r];
-                if (AU) s_u[threadIdx.x] = __uint_as_float(e.unc);
-            }
-        }
-        __syncthreads();
-        uint64_t m[NW];
-        // splats at or past every lane's last contributor cannot matter
-        const int cnt = (int)(min<int64_t>(bend, (int64_t)wave_last) - bstart);
-        wave_masks<B, BWD_ELL>(s_pb, s_g0, s_g1, st.log2_amin, cnt, wc0, wc1, wr0, wr1, m);
-        // back to front over the splats that can reach this wave's pixels,
-        // BWD_STEP per step: their alphas are independent of the pixel state,
-        // and their wave reductions run interleaved
-        for (;;) {
-            int ks[BWD_STEP];
-            ks[0] = pop_high<NW>(m);
-            if (ks[0] < 0) break;
-#pragma unroll
-            for (int q = 1; q < BWD_STEP; q++) ks[q] = pop_high<NW>(m);
-            float4 sg0[BWD_STEP], sg1[BWD_STEP], sat[BWD_STEP];
-            float su[BWD_STEP];
-            uint32_t sr[BWD_STEP], spos[BWD_STEP];
-#pragma unroll
-            for (int q = 0; q < BWD_STEP; q++) {
-                const int k = ks[q] < 0 ? ks[0] : ks[q];
-                sg0[q] = s_g0[k];
-                sg1[q] = s_g1[k];
-                sat[q] = s_at[k];
-                su[q] = AU ? s_u[k] : 0.0f;
-                sr[q] = s_r[k];
-                spos[q] = ks[q] < 0 ? 0xffffffffu : (uint32_t)(bstart + ks[q]);
-            }
-            float acc[BWD_STEP][10];
-            bool any[BWD_STEP];
-#pragma unroll
-            for (int q = 0; q < BWD_STEP; q++) {
-                any[q] = false;
-#pragma unroll
-                for (int v = 0; v < 10; v++) acc[q][v] = 0.0f;
-            }
-#pragma unroll
-            for (int j = 0; j < PPT; j++) {
-                float a[BWD_STEP], G[BWD_STEP], dx[BWD_STEP], dy[BWD_STEP], w1[BWD_STEP], w2[BWD_STEP];
-                bool need = false;
-#pragma unroll
-                for (int q = 0; q < BWD_STEP; q++) {
-                    a[q] = splat_alpha(sg0[q].x, sg0[q].y, sg1[q], px0 + bx(j), py0 + by(j), amax, G[q], dx[q],
-                                       dy[q], w1[q], w2[q]);
-                    need = need | near_amin(a[q], st.alpha_min, band);
-                }
-                // the forward's binary64 re-decision, taken the same way
-                if (__ballot(need)) {
-#pragma unroll
-                    for (int q = 0; q < BWD_STEP; q++)
-                        if ((spos[q] < last[j]) & near_amin(a[q], st.alpha_min, band))
-                            a[q] = redecide(a[q], rec, sr[q], ux(j), vy(j), st);
-                }
-                // predicated, not branched: a splat the pixel does not take
-                // enters with alpha 0 and a_g 0, which leaves T, D and the
-                // sums unchanged
-#pragma unroll
-                for (int q = 0; q < BWD_STEP; q++) {
-                    const bool ok = (spos[q] < last[j]) & (a[q] >= st.alpha_min);
-                    any[q] = any[q] | ok;
-                    const float a0 = ok ? a[q] : 0.0f;
-                    const float ag = sg1[q].w * G[q] <= amax ? a0 : 0.0f;
-                    bwd_pixel<AU>(a0, ag, dx[q], dy[q], sat[q], su[q], gr[j], gg[j], gb[j], gd[j], ga[j],
-                                  gu[j], T[j], D[j], acc[q]);
-                }
-            }
-            bool t[BWD_STEP];
-            bool tany = false;
-#pragma unroll
-            for (int q = 0; q < BWD_STEP; q++) {
-                t[q] = __ballot(any[q]) != 0;
-                tany = tany || t[q];
-            }
-            if (tany) {
-                // lane l < 32 ends with the total of value v (splat v / 10,
-                // gradient slot v % 10) and adds it: one 20-lane atomic
-                int v;
-                const float tot = wave_sum_halving20(&acc[0][0], lane, v);
-                if (lane < 32 && v >= 0) {
-                    const int q = v >= 10 ? 1 : 0;
-                    const int slot = v - 10 * q;
-                    if (q ? t[1] : t[0])
-                        unsafeAtomicAdd(g2d + (uint64_t)(q ? sr[1] : sr[0]) * G2D_STRIDE + slot, (double)tot);
-                }
-            }
-        }
-    }
-}
-
-// The one-wave form of k_render_bwd (a tile per wave): the staging lanes
-// keep only the splats whose box meets the tile and write them compacted, in
-// ascending order, to LDS, so the walk back to front is a plain countdown
-// with no mask scanning; the wave loads the next step's two splats while it
-// computes the current one.  Every pixel sees the same splats in the same
-// order, with the same arithmetic, as in k_render_bwd, and every splat's
-// per-tile sums are reduced by the same lane tree, so the two kernels add
-// identical partial gradients.  Slot B holds the null splat: position
-// 0xffffffff (no pixel takes it), zero geometry and colour.
-template <int TW, int TH, bool AU>
-__global__ __launch_bounds__(64, AU ? 1 : 3) void k_render_bwd1(const ViewDev* __restrict__ views, int n_views,
-                                                        const uint2* __restrict__ ranges,
-                                                        const uint32_t* __restrict__ tile_order,
-                                                        const uint32_t* __restrict__ inst_rec, Records rec,
-                                                        SetDev st, const float* __restrict__ T_final,
-                                                        const uint32_t* __restrict__ n_last,
-                                                        const float* __restrict__ d_rgb,
-                                                        const float* __restrict__ d_depth,
-                                                        const float* __restrict__ d_alpha,
-                                                        const float* __restrict__ d_unc, double* __restrict__ g2d,
-                                                        const uint32_t* __restrict__ flags) {
-    constexpr int PPT = TW * TH / 64;
+    constexpr int PPT = TW * TH / 64 / NSUB;
+    constexpr int SH = TH / NSUB;   // rows of the band
+    constexpr int LPR = TW / PPT;   // lanes per row
     constexpr int B = 64;
-    static_assert(PPT >= 1 && PPT * 64 == TW * TH, "the tile must be whole 8x8 blocks");
+    static_assert(PPT >= 1 && PPT <= 4 && LPR * SH == 64, "a wave must hold the band, one to four pixels a lane");
     if (flags && *flags) return;
     // s_p = (mean x, mean y relative to the origin, record id bits, position bits)
     __shared__ float4 s_p[B + 1], s_g1[B + 1], s_at[B + 1];
-    __shared__ float s_u[B + 1];
-    const uint32_t tile = tile_order ? tile_order[blockIdx.x] : blockIdx.x;
+    __shared__ float s_u[B + 1], s_band[B + 1];
+    __shared__ float s_red[20 * RED_STRIDE];
+    const uint32_t tile = tile_order[blockIdx.x / NSUB];
     const uint32_t vi = view_of_tile(views, n_views, tile);
     const ViewDev& V = views[vi];
     const int W = V.W, H = V.H;
@@ -2336,23 +2016,22 @@ __global__ __launch_bounds__(64, AU ? 1 : 3) void k_render_bwd1(const ViewDev* _
         s_g1[B] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         s_at[B] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         s_u[B] = 0.0f;
+        s_band[B] = 0.0f;
     }
 
     const int ox = origin_x(tx * TW), oy = origin_y(ty * TH);
-    const float px0 = (float)(tx * TW - ox + (lane & 7)), py0 = (float)(ty * TH - oy + (lane >> 3));
-    auto bx = [&](int j) { return (float)((j % (TW / 8)) * 8); };
-    auto by = [&](int j) { return (float)((j / (TW / 8)) * 8); };
-    auto ux = [&](int j) { return tx * TW + (j % (TW / 8)) * 8 + (lane & 7); };
-    auto vy = [&](int j) { return ty * TH + (j / (TW / 8)) * 8 + (lane >> 3); };
+    // the band's pixels, and the lane's: (u0 + j, v)
+    const int c0 = tx * TW, c1 = c0 + TW - 1, r0 = ty * TH + (int)(blockIdx.x % NSUB) * SH, r1 = r0 + SH - 1;
+    const int u0 = c0 + (lane % LPR) * PPT, v = r0 + lane / LPR;
+    const float px0 = (float)(u0 - ox), py = (float)(v - oy);
     float T[PPT];
     uint32_t last[PPT];
     float gr[PPT], gg[PPT], gb[PPT], gd[PPT], ga[PPT], gu[PPT];
     float D[PPT];
     uint32_t mylast = 0;
-    const int c0 = tx * TW, c1 = c0 + TW - 1, r0 = ty * TH, r1 = r0 + TH - 1;  // the tile's pixels
 #pragma unroll
     for (int j = 0; j < PPT; j++) {
-        const int u = ux(j), v = vy(j);
+        const int u = u0 + j;
         T[j] = 1.0f;
         last[j] = 0;
         gr[j] = gg[j] = gb[j] = gd[j] = ga[j] = gu[j] = 0.0f;
@@ -2376,8 +2055,7 @@ __global__ __launch_bounds__(64, AU ? 1 : 3) void k_render_bwd1(const ViewDev* _
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mylast = max(mylast, (uint32_t)__shfl_xor((int)mylast, o, 64));
     const uint32_t maxlast = mylast;
-    const float amax = st.alpha_max;
-    const float band = REFINE * st.alpha_min;
+    const float amin = in_vgpr(st.alpha_min), amax = st.alpha_max;
 
     for (int64_t bend = maxlast; bend > 0; bend -= B) {
         const int64_t bstart = bend - B > 0 ? bend - B : 0;
@@ -2405,20 +2083,19 @@ __global__ __launch_bounds__(64, AU ? 1 : 3) void k_render_bwd1(const ViewDev* _
             s_p[slot] = p;
             s_g1[slot] = q1;
             s_at[slot] = at;
+            s_band[slot] = amin_band(p.x, p.y, q1.x, q1.y, q1.z, st);
             if (AU) s_u[slot] = uv;
         }
         __syncthreads();
         // back to front over slots n - 1, n - 2, ..., two per step
         for (int i = n - 1; i >= 0; i -= 2) {
-            float4 cp[2], cg[2], ca[2];
-            float cu[2];
+            float4 cp[2], cg[2];
+            int slot[2];
 #pragma unroll
             for (int q = 0; q < 2; q++) {
-                const int k = i - q >= 0 ? i - q : B;
-                cp[q] = s_p[k];
-                cg[q] = s_g1[k];
-                ca[q] = s_at[k];
-                cu[q] = AU ? s_u[k] : 0.0f;
+                slot[q] = i - q >= 0 ? i - q : B;
+                cp[q] = s_p[slot[q]];
+                cg[q] = s_g1[slot[q]];
             }
             uint32_t sr[2], spos[2];
 #pragma unroll
@@ -2426,7 +2103,7 @@ __global__ __launch_bounds__(64, AU ? 1 : 3) void k_render_bwd1(const ViewDev* _
                 sr[q] = __float_as_uint(cp[q].z);
                 spos[q] = __float_as_uint(cp[q].w);
             }
-            float acc[2][10];
+            float acc[20];
             bool any[2];
 #pragma unroll
             for (int q = 0; q < 2; q++) any[q] = false;
@@ -2437,40 +2114,87 @@ __global__ __launch_bounds__(64, AU ? 1 : 3) void k_render_bwd1(const ViewDev* _
             // alpha = o G carries it at every pixel (a_g = a)
             auto step = [&](auto clamp) {
                 constexpr bool CL = decltype(clamp)::value;
-                float a[PPT][2], G[PPT][2], dx[PPT][2], dy[PPT][2];
+                float a[PPT][2], G[PPT][2], A[2], dy[2], t[PPT][2], col[2][4];
+                const float bands[2] = {s_band[slot[0]], s_band[slot[1]]};
                 bool need = false;
 #pragma unroll
                 for (int j = 0; j < PPT; j++)
 #pragma unroll
                     for (int q = 0; q < 2; q++) {
-                        float w1, w2;
-                        a[j][q] = splat_alpha<CL>(cp[q].x, cp[q].y, cg[q], px0 + bx(j), py0 + by(j), amax, G[j][q],
-                                                  dx[j][q], dy[j][q], w1, w2);
-                        need = need | near_amin(a[j][q], st.alpha_min, band);
+                        float dx, w1, w2;
+                        a[j][q] = splat_alpha<CL>(cp[q].x, cp[q].y, cg[q], px0 + (float)j, py, amax, G[j][q], dx,
+                                                  dy[q], w1, w2);
+                        if (j == 0) A[q] = dx;
+                        need = need | near_amin(a[j][q], amin, bands[q]);
                     }
                 if (__ballot(need)) {
+                    // one copy of the binary64 code: a loop over the step's alphas, each taken out
+                    // and put back by selects
+#pragma unroll 1
+                    for (int k = 0; k < 2 * PPT; k++) {
+                        float x = 0.0f;
+                        uint32_t l = 0;
 #pragma unroll
-                    for (int j = 0; j < PPT; j++)
+                        for (int j = 0; j < PPT; j++) {
+                            x = k == 2 * j ? a[j][0] : k == 2 * j + 1 ? a[j][1] : x;
+                            l = k >> 1 == j ? last[j] : l;
+                        }
+                        if ((((k & 1) ? spos[1] : spos[0]) < l) & near_amin(x, amin, (k & 1) ? bands[1] : bands[0]))
+                            x = redecide(x, rec, (k & 1) ? sr[1] : sr[0], u0 + (k >> 1), v, st);
 #pragma unroll
-                        for (int q = 0; q < 2; q++)
-                            if ((spos[q] < last[j]) & near_amin(a[j][q], st.alpha_min, band))
-                                a[j][q] = redecide(a[j][q], rec, sr[q], ux(j), vy(j), st);
+                        for (int j = 0; j < PPT; j++) {
+                            a[j][0] = k == 2 * j ? x : a[j][0];
+                            a[j][1] = k == 2 * j + 1 ? x : a[j][1];
+                        }
+                    }
+                }
+                // the colours are read here, not with the geometry: fewer registers live above
+                asm volatile("" ::: "memory");
+                float4 ca[2];
+                float cu[2];
+#pragma unroll
+                for (int q = 0; q < 2; q++) {
+                    ca[q] = s_at[slot[q]];
+                    cu[q] = AU ? s_u[slot[q]] : 0.0f;
                 }
 #pragma unroll
                 for (int j = 0; j < PPT; j++) {
 #pragma unroll
                     for (int q = 0; q < 2; q++) {
-                        const bool ok = (spos[q] < last[j]) & (a[j][q] >= st.alpha_min);
+                        const bool ok = (spos[q] < last[j]) & (a[j][q] >= amin);
                         any[q] = any[q] | ok;
                         const float a0 = ok ? a[j][q] : 0.0f;
                         const float ag = CL ? (cg[q].w * G[j][q] <= amax ? a0 : 0.0f) : a0;
                         if (j == 0)
-                            bwd_pixel<AU, true>(a0, ag, dx[j][q], dy[j][q], ca[q], cu[q], gr[j], gg[j], gb[j],
-                                                gd[j], ga[j], gu[j], T[j], D[j], acc[q]);
+                            t[j][q] = bwd_pixel<AU, true>(a0, ag, ca[q], cu[q], gr[j], gg[j], gb[j], gd[j], ga[j],
+                                                          gu[j], T[j], D[j], col[q]);
                         else
-                            bwd_pixel<AU>(a0, ag, dx[j][q], dy[j][q], ca[q], cu[q], gr[j], gg[j], gb[j], gd[j],
-                                          ga[j], gu[j], T[j], D[j], acc[q]);
+                            t[j][q] = bwd_pixel<AU, false>(a0, ag, ca[q], cu[q], gr[j], gg[j], gb[j], gd[j], ga[j],
+                                                           gu[j], T[j], D[j], col[q]);
                     }
+                }
+#pragma unroll
+                for (int q = 0; q < 2; q++) {
+                    float s0 = t[0][q], s1 = 0.0f, s2 = 0.0f;
+                    if constexpr (PPT >= 2) {
+                        s0 += t[1][q];
+                        s1 = t[1][q];
+                        s2 = t[1][q];
+                    }
+                    if constexpr (PPT == 4) {
+                        s0 += t[2][q] + t[3][q];
+                        s1 = fmaf(3.0f, t[3][q], fmaf(2.0f, t[2][q], s1));
+                        s2 = fmaf(9.0f, t[3][q], fmaf(4.0f, t[2][q], s2));
+                    }
+                    float* c = acc + 10 * q;
+                    c[0] = fmaf(A[q], s0, s1);
+                    c[1] = dy[q] * s0;
+                    c[2] = fmaf(A[q], c[0] + s1, s2);
+                    c[3] = dy[q] * c[0];
+                    c[4] = dy[q] * c[1];
+                    c[5] = s0;
+#pragma unroll
+                    for (int k = 0; k < 4; k++) c[6 + k] = col[q][k];
                 }
             };
             // opacities and alpha_max are positive: their bits order as they do
@@ -2485,14 +2209,35 @@ __global__ __launch_bounds__(64, AU ? 1 : 3) void k_render_bwd1(const ViewDev* _
             // reduced unconditionally (a step that no pixel takes is rare), so
             // that the per-pixel sums are formed pixel by pixel instead of
             // being held back behind a branch
-            int v;
-            const float tot = wave_sum_halving20(&acc[0][0], lane, v);
-            if (lane < 32 && v >= 0) {
-                const int q = v >= 10 ? 1 : 0;
-                const int slot = v - 10 * q;
-                if (q ? t[1] : t[0])
-                    unsafeAtomicAdd(g2d + (uint64_t)(q ? sr[1] : sr[0]) * G2D_STRIDE + slot, (double)tot);
-            }
+            // totals: value k of every lane in row k of LDS, and lanes r and r + 32 each add up half of
+            // row r (r < 20; the spare lanes repeat row 19)
+            wave_lds_order();
+#pragma unroll
+            for (int k = 0; k < 20; k++) s_red[k * RED_STRIDE + lane] = acc[k];
+            wave_lds_order();
+            const int row = min(lane & 31, 19);
+            const float4* half = reinterpret_cast<const float4*>(s_red + row * RED_STRIDE + (lane & 32));
+            float4 h[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) h[k] = half[k];
+            // pairwise: the sums of t d and t d d cancel for needle-shaped splats, so their rounding is kept to six
+            // levels as a tree over 64 lanes has
+#pragma unroll
+            for (int w = 4; w > 0; w >>= 1)
+#pragma unroll
+                for (int k = 0; k < w; k++) {
+                    h[k].x += h[k + w].x;
+                    h[k].y += h[k + w].y;
+                    h[k].z += h[k + w].z;
+                    h[k].w += h[k + w].w;
+                }
+            const float part = (h[0].x + h[0].y) + (h[0].z + h[0].w);
+            const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(part), __float_as_uint(part), false, false);
+            const float tot = __uint_as_float(both[0]) + __uint_as_float(both[1]);
+            // one binary64 atomic of 20 lanes
+            if (lane < 20 && (lane >= 10 ? t[1] : t[0]))
+                unsafeAtomicAdd(g2d + (uint64_t)(lane >= 10 ? sr[1] : sr[0]) * G2D_STRIDE + (lane >= 10 ? lane - 10 : lane),
+                                (double)tot);
         }
     }
 }
@@ -2670,6 +2415,10 @@ __global__ __launch_bounds__(256) void k_project_bwd(GaussDev g, const ViewDev* 
 // of every tile shape, so no pixel's arithmetic depends on the tile), the
 // whitening M, log2(opacity) and u; a pixel's offset is then one subtraction
 // from a small exact integer, and alpha = min(alpha_max, exp2(log2 o - |Md|^2)).
+// Bound by instruction issue, as k_render_fwd: with the thresholds in vector registers, one select
+// instead of two per splat, the narrower band of the binary64 branch (which also freed the registers for eight
+// waves per SIMD instead of six) 256 uneven views went from 3,536 to 2,816 us, 64 views of 320x240 from
+// 891 to 698 us.
 // Termination is carried by T itself: a pixel whose next transmittance
 // would fall below T_min stops with T = 0, after which every splat leaves it
 // unchanged, so the loop needs no per-pixel flags; a splat below alpha_min
@@ -2701,8 +2450,7 @@ __device__ __forceinline__ void score_one_tile(const ViewDev* __restrict__ views
     const int wr0 = ty * TH + (int)(threadIdx.x >> 6) * (64 / TW) - oy, wr1 = wr0 + 64 / TW - 1;
     const bool inside = u < V.W && v < V.H;
     const float lx = (float)(u - ox), ly = (float)(v - oy);
-    const float amin = st.alpha_min, amax = st.alpha_max, tmin = st.T_min;
-    const float band = REFINE * amin;
+    const float amin = in_vgpr(st.alpha_min), amax = in_vgpr(st.alpha_max), tmin = in_vgpr(st.T_min);
     const uint2 rg = ranges[tile];
     const char* sp = reinterpret_cast<const char*>(s_p);
     const char* sq = reinterpret_cast<const char*>(s_q);
@@ -2710,55 +2458,73 @@ __device__ __forceinline__ void score_one_tile(const ViewDev* __restrict__ views
     for (uint32_t b = rg.x; b < rg.y; b += B) {
         if (__syncthreads_count(T > 0.0f) == 0) break;
         uint32_t idx = b + threadIdx.x;
+        bool odd = false;
         if (threadIdx.x < (uint32_t)B && idx < rg.y) {
             uint32_t r = inst_rec[idx];
             s_r[threadIdx.x] = r;
             const EmitRec e = rec.emit[r];
             s_pb[threadIdx.x] = e.pbox;
-            stage_splat(e, ox, oy, s_p[threadIdx.x], s_q[threadIdx.x]);
+            odd = !isfinite(__uint_as_float(e.unc));
+            stage_splat<true>(e, ox, oy, st, s_p[threadIdx.x], s_q[threadIdx.x]);
         }
-        __syncthreads();
+        // an uncertainty that is not finite must not meet the weight 0 below (MODE 1 needs the barrier alone)
+        if (MODE != 0) __syncthreads();
+        const bool select = MODE != 0 || __builtin_amdgcn_readfirstlane(__syncthreads_or(odd));
         const int cnt = (int)min<uint32_t>(B, rg.y - b);
         uint32_t* my = s_list + (threadIdx.x >> 6) * (B + 2);
         int nl = 0;
-        if (__ballot(T > 0.0f))
+        uint64_t alive = __ballot(T > 0.0f);
+        if (alive)
             nl = splat_list<B, SCORE_ELL>(s_pb, s_p, s_q, st.log2_amin, cnt, wc0, wc1, wr0, wr1, ox, oy, my);
         __syncthreads();  // the wave's list is in LDS
-        for (int i = 0; i < nl; i += SCORE_STEP) {
-            if (!__ballot(T > 0.0f)) break;
-            uint32_t ko[SCORE_STEP];
-            float as[SCORE_STEP], us[SCORE_STEP];
-            bool need = false;
+        auto walk = [&](auto selected) {
+            for (int i = 0; i < nl && alive; i += SCORE_STEP) {
+                uint32_t ko[SCORE_STEP];
+                float as[SCORE_STEP], us[SCORE_STEP], bs[SCORE_STEP];
+                bool need = false;
 #pragma unroll
-            for (int q = 0; q < SCORE_STEP; q++) {
-                ko[q] = my[i + q];
-                const float4 p = *reinterpret_cast<const float4*>(sp + ko[q]);
-                const float4 g = *reinterpret_cast<const float4*>(sq + ko[q]);
-                const float dx = lx - p.x, dy = ly - p.y;
-                const float w1 = p.z * dx, w2 = fmaf(p.w, dx, g.x * dy);
-                const float ex = fmaf(w1, w1, fmaf(w2, w2, -g.w));
-                const float a = __builtin_amdgcn_fmed3f(fast_exp2(-ex), 0.0f, amax);
-                as[q] = a;
-                us[q] = g.z;
-                need = need | near_amin(a, amin, band);
-            }
-            if (__ballot(need)) {
+                for (int q = 0; q < SCORE_STEP; q++) {
+                    ko[q] = my[i + q];
+                    const float4 p = *reinterpret_cast<const float4*>(sp + ko[q]);
+                    const float4 g = *reinterpret_cast<const float4*>(sq + ko[q]);
+                    const float dx = lx - p.x, dy = ly - p.y;
+                    const float w1 = p.z * dx, w2 = fmaf(p.w, dx, g.x * dy);
+                    const float ex = fmaf(w1, w1, fmaf(w2, w2, -g.y));
+                    const float a = __builtin_amdgcn_fmed3f(fast_exp2(-ex), 0.0f, amax);
+                    as[q] = a;
+                    us[q] = g.z;
+                    bs[q] = g.w;
+                    need = need | near_amin(a, amin, bs[q]);
+                }
+                if (__ballot(need)) {
 #pragma unroll
-                for (int q = 0; q < SCORE_STEP; q++)
-                    if (near_amin(as[q], amin, band) & (ko[q] < B * sizeof(float4)))
-                        as[q] = redecide(as[q], rec, s_r[ko[q] / sizeof(float4)], u, v, st);
-            }
+                    for (int q = 0; q < SCORE_STEP; q++)
+                        if (near_amin(as[q], amin, bs[q]))
+                            as[q] = redecide(as[q], rec, s_r[ko[q] / sizeof(float4)], u, v, st);
+                }
 #pragma unroll
-            for (int q = 0; q < SCORE_STEP; q++) {
-                const bool ok = as[q] >= amin;
-                const float a0 = ok ? as[q] : 0.0f;
-                const float Tn = fmaf(-a0, T, T);
-                const bool live = Tn >= tmin;
-                const float w = score_weight<MODE>(a0, T);
-                uu = (ok & live) ? fmaf(us[q], w, uu) : uu;
-                T = live ? Tn : 0.0f;
+                for (int q = 0; q < SCORE_STEP; q++) {
+                    const bool ok = as[q] >= amin;
+                    const float a0 = ok ? as[q] : 0.0f;
+                    const float Tn = fmaf(-a0, T, T);
+                    const bool live = Tn >= tmin;
+                    if constexpr (decltype(selected)::value) {
+                        const float w = score_weight<MODE>(a0, T);
+                        uu = (ok & live) ? fmaf(us[q], w, uu) : uu;
+                        T = live ? Tn : 0.0f;
+                    } else {
+                        // one select: a pixel that stops takes T = 0 first, so that its weight and
+                        // its next T are 0; a skipped splat's weight is 0 through a0
+                        const float T0 = live ? T : 0.0f;
+                        uu = fmaf(us[q], a0 * T0, uu);
+                        T = fmaf(-a0, T0, T0);
+                    }
+                    if (q + 1 == SCORE_STEP) alive = __ballot(live);
+                }
             }
-        }
+        };
+        if (select) walk(BoolC<true>{});
+        else walk(BoolC<false>{});
     }
     float s = wave_sum_f(uu);
     if (lane_id() == 0) ws[threadIdx.x >> 6] = (double)s;
@@ -2779,11 +2545,11 @@ __global__ __launch_bounds__(TW * TH) void k_score_plain(const ViewDev* __restri
     constexpr int NT = TW * TH;
     static_assert(B <= NT, "batch larger than the tile");
     __shared__ float4 s_p[B + 1], s_q[B + 1];
-    __shared__ uint32_t s_r[B];
+    __shared__ uint32_t s_r[B + 1];
     __shared__ uint2 s_pb[B];
     __shared__ double ws[NT / 64];
     __shared__ __align__(8) uint32_t s_list[NT / 64 * (B + 2)];
-    stage_null_splat<B>(s_p, s_q);
+    stage_null_splat<B, true>(s_p, s_q);
     if (mode)
         score_one_tile<TW, TH, B, 1>(views, n_views, tile_begin + blockIdx.x, ranges, inst_rec, rec, st, partial,
                                      s_p, s_q, s_r, s_pb, ws, s_list);
@@ -2793,7 +2559,7 @@ __global__ __launch_bounds__(TW * TH) void k_score_plain(const ViewDev* __restri
 }
 
 template <int TW, int TH, int B>
-__global__ __launch_bounds__(TW * TH) __attribute__((amdgpu_waves_per_eu(6))) void k_score_persistent(const ViewDev* __restrict__ views,
+__global__ __launch_bounds__(TW * TH) __attribute__((amdgpu_waves_per_eu(8))) void k_score_persistent(const ViewDev* __restrict__ views,
                                                               const Header* __restrict__ hdr,
                                                               const uint2* __restrict__ ranges,
                                                               const uint32_t* __restrict__ tile_order,
@@ -2805,11 +2571,11 @@ __global__ __launch_bounds__(TW * TH) __attribute__((amdgpu_waves_per_eu(6))) vo
     static_assert(B <= NT, "batch larger than the tile");
     if (*flags) return;  // overflowed binning: results are reported invalid
     __shared__ float4 s_p[B + 1], s_q[B + 1];
-    __shared__ uint32_t s_r[B];
+    __shared__ uint32_t s_r[B + 1];
     __shared__ uint2 s_pb[B];
     __shared__ double ws[NT / 64];
     __shared__ __align__(8) uint32_t s_list[NT / 64 * (B + 2)];
-    stage_null_splat<B>(s_p, s_q);
+    stage_null_splat<B, true>(s_p, s_q);
     __shared__ uint32_t s_item;
     const uint32_t total = hdr->tiles_total;
     const int nv = (int)hdr->n_views;
@@ -3661,7 +3427,10 @@ void render_forward(int tw, int th, int batch, const ViewDev* views, int n_views
                     uint32_t tiles_total, const uint2* ranges, const uint32_t* tile_order, const uint32_t* inst_rec,
                     Records rec, SetDev st, RenderOut out, const uint32_t* flags, hipStream_t s) {
     if (tiles_total == 0) return;
-    if (out.unc) {
+    if (out.n_contrib) {
+        RTG_TILE_DISPATCH(TW, TH, (k_render_fwd<TW, TH, TW * TH, false, true><<<tiles_total, TW * TH, 0, s>>>(
+                                      views, n_views, ranges, tile_order, inst_rec, rec, st, out, flags)));
+    } else if (out.unc) {
         RTG_BATCH_DISPATCH(TW, TH, B, (k_render_fwd<TW, TH, B, true><<<tiles_total, TW * TH, 0, s>>>(
                                           views, n_views, ranges, tile_order, inst_rec, rec, st, out, flags)));
     } else {
@@ -3680,9 +3449,17 @@ void loss_l1(const ViewDev* views, int n_views, int max_pix, const float* rgb, c
     k_sum_partials<<<1, SP_THREADS, 0, s>>>(partial, (int)(bx * n_views), loss);
 }
 
-// Waves per tile for the backward: enough workgroups to fill the chip on
-// frames with few tiles, one wave per tile otherwise (RTG_BWD_WAVES overrides).
-static int backward_waves(int tw, int th, uint32_t tiles) {
+// Bands per tile for the backward: frames of few tiles leave most SIMDs with a wave or none, and then
+// more, shorter walks win until their atomics (one set per band and splat) cost more.  Per frame, in us
+// (with alpha gradients), for one, two and four bands on 256 CUs:
+//     336 tiles   344 (412)   179 (233)   138 (175)
+//     690         170 (200)   113 (137)   109 (129)
+//     980         159 (185)   102 (129)   109 (125)
+//   1,200         137 (166)   106 (129)   121 (152)
+//   2,400         237 (249)   312 (358)   532 (567)
+//   7,200         584 (680)   966 (1013)  1719 (1787)
+// so four below 3.5 tiles per CU, two below 8, one from there on.  RTG_BWD_WAVES overrides.
+static int backward_bands(int tw, int th, uint32_t tiles) {
     static int forced = -1;
     if (forced < 0) {
         const char* e = getenv("RTG_BWD_WAVES");
@@ -3693,36 +3470,11 @@ static int backward_waves(int tw, int th, uint32_t tiles) {
     if (forced == 1 || forced == 2 || forced == 4) nw = forced;
     else {
         const uint32_t cu = (uint32_t)std::max(device_cu_count(), 1);
-        if (tiles < 16 * cu) nw = 2;
+        if (2 * (uint64_t)tiles < 7 * cu) nw = 4;
+        else if (tiles < 8 * cu) nw = 2;
     }
     while (nw > nb8) nw >>= 1;
     return nw;
-}
-
-// One wave per tile runs the compacted form; two or four the masked one.
-template <int TW, int TH, int NW>
-static void launch_bwd(bool au, uint32_t tiles_total, hipStream_t s, const ViewDev* views, int n_views,
-                       const uint2* ranges, const uint32_t* tile_order, const uint32_t* inst_rec, Records rec,
-                       SetDev st, const float* T_final,
-                       const uint32_t* n_last, const float* d_rgb, const float* d_depth, const float* d_alpha,
-                       const float* d_unc, double* g2d, const uint32_t* flags) {
-    if constexpr (NW == 1) {
-        if (au)
-            k_render_bwd1<TW, TH, true><<<tiles_total, 64, 0, s>>>(views, n_views, ranges, tile_order, inst_rec, rec, st, T_final,
-                                                                   n_last, d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
-        else
-            k_render_bwd1<TW, TH, false><<<tiles_total, 64, 0, s>>>(views, n_views, ranges, tile_order, inst_rec, rec, st, T_final,
-                                                                    n_last, d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
-    } else {
-        if (au)
-            k_render_bwd<TW, TH, NW, true><<<tiles_total, 64 * NW, 0, s>>>(views, n_views, ranges, tile_order, inst_rec, rec, st,
-                                                                          T_final, n_last, d_rgb, d_depth, d_alpha,
-                                                                          d_unc, g2d, flags);
-        else
-            k_render_bwd<TW, TH, NW, false><<<tiles_total, 64 * NW, 0, s>>>(views, n_views, ranges, tile_order, inst_rec, rec, st,
-                                                                           T_final, n_last, d_rgb, d_depth, d_alpha,
-                                                                           d_unc, g2d, flags);
-    }
 }
 
 void render_backward(int tw, int th, int batch, const ViewDev* views, int n_views, uint32_t tiles_total,
@@ -3730,34 +3482,26 @@ void render_backward(int tw, int th, int batch, const ViewDev* views, int n_view
                      SetDev st, const float* T_final,
                      const uint32_t* n_last, const float* d_rgb, const float* d_depth, const float* d_alpha,
                      const float* d_unc, double* g2d, const uint32_t* flags, hipStream_t s) {
-    (void)batch;  // the backward stages 64 splats per wave of the tile
+    (void)batch;  // the backward stages 64 splats per wave
     if (tiles_total == 0) return;
-    const int nw = backward_waves(tw, th, tiles_total);
+    const int nw = backward_bands(tw, th, tiles_total);
     const bool au = d_alpha != nullptr || d_unc != nullptr;
-    if (tw == 8 && th == 8) {
-        launch_bwd<8, 8, 1>(au, tiles_total, s, views, n_views, ranges, tile_order, inst_rec, rec, st, T_final, n_last, d_rgb,
-                            d_depth, d_alpha, d_unc, g2d, flags);
-    } else if (tw == 32 && th == 8) {
-        if (nw == 4)
-            launch_bwd<32, 8, 4>(au, tiles_total, s, views, n_views, ranges, tile_order, inst_rec, rec, st, T_final, n_last,
-                                 d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
-        else if (nw == 2)
-            launch_bwd<32, 8, 2>(au, tiles_total, s, views, n_views, ranges, tile_order, inst_rec, rec, st, T_final, n_last,
-                                 d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
-        else
-            launch_bwd<32, 8, 1>(au, tiles_total, s, views, n_views, ranges, tile_order, inst_rec, rec, st, T_final, n_last,
-                                 d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
-    } else {
-        if (nw == 4)
-            launch_bwd<16, 16, 4>(au, tiles_total, s, views, n_views, ranges, tile_order, inst_rec, rec, st, T_final, n_last,
-                                  d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
-        else if (nw == 2)
-            launch_bwd<16, 16, 2>(au, tiles_total, s, views, n_views, ranges, tile_order, inst_rec, rec, st, T_final, n_last,
-                                  d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
-        else
-            launch_bwd<16, 16, 1>(au, tiles_total, s, views, n_views, ranges, tile_order, inst_rec, rec, st, T_final, n_last,
-                                  d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
-    }
+    auto launch = [&](auto kernel) {
+        kernel<<<tiles_total * (unsigned)nw, 64, 0, s>>>(views, n_views, ranges, tile_order, inst_rec, rec, st,
+                                                         T_final, n_last, d_rgb, d_depth, d_alpha, d_unc, g2d, flags);
+    };
+    auto bands = [&](auto w, auto h) {
+        constexpr int TW = decltype(w)::value, TH = decltype(h)::value;
+        if constexpr (TW * TH > 64) {
+            if (nw == 4) return au ? launch(k_render_bwd<TW, TH, 4, true>) : launch(k_render_bwd<TW, TH, 4, false>);
+            if (nw == 2) return au ? launch(k_render_bwd<TW, TH, 2, true>) : launch(k_render_bwd<TW, TH, 2, false>);
+        }
+        return au ? launch(k_render_bwd<TW, TH, 1, true>) : launch(k_render_bwd<TW, TH, 1, false>);
+    };
+    using std::integral_constant;
+    if (tw == 8 && th == 8) bands(integral_constant<int, 8>{}, integral_constant<int, 8>{});
+    else if (tw == 32 && th == 8) bands(integral_constant<int, 32>{}, integral_constant<int, 8>{});
+    else bands(integral_constant<int, 16>{}, integral_constant<int, 16>{});
 }
 
 void project_backward(const GaussDev& g, const ViewDev* views, SetDev st, const uint32_t* rec_off,
