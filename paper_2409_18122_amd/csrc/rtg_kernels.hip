@@ -34,6 +34,12 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 // ------------------------------------------------------------------ fill
 
+// Orders a wave's LDS stores and loads (a compiler's matter: the hardware keeps them in order).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, uint64_t n) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -177,9 +183,31 @@ struct GProj {
     int u0, u1, v0, v1;
 };
 
+// A camera in binary64, from the binary32 values of the table: every lane of a wave may have its own camera, and five
+// 16-byte loads visit a quarter of the cache lines that the table's binary64 copy would.
+struct Cam {
+    double R[9], T[3], fx, fy, cx, cy;
+    int W, H;
+};
+
+__device__ __forceinline__ Cam load_cam(const ViewDev* v) {
+    static_assert(offsetof(ViewDev, Rf) % 16 == 0 && sizeof(ViewDev) % 16 == 0 &&
+                      offsetof(ViewDev, W) == offsetof(ViewDev, Rf) + 64, "the camera's 18 words in five 16-byte loads");
+    const float4* p = reinterpret_cast<const float4*>(v->Rf);
+    const float4 a = p[0], b = p[1], c = p[2], d = p[3];
+    const int2 wh = *reinterpret_cast<const int2*>(&v->W);
+    Cam V;
+    V.R[0] = a.x; V.R[1] = a.y; V.R[2] = a.z; V.R[3] = a.w;
+    V.R[4] = b.x; V.R[5] = b.y; V.R[6] = b.z; V.R[7] = b.w;
+    V.R[8] = c.x; V.T[0] = c.y; V.T[1] = c.z; V.T[2] = c.w;
+    V.fx = d.x; V.fy = d.y; V.cx = d.z; V.cy = d.w;
+    V.W = wh.x; V.H = wh.y;
+    return V;
+}
+
 // Exact binary64 projection.  The camera depth is evaluated in the fixed
 // order ((dx R02 + dy R12) + dz R22): its binary32 rounding is the sort key.
-__device__ inline bool project_exact(const GPre& P, const ViewDev& V, const SetDev& st, GProj& q) {
+__device__ inline bool project_exact(const GPre& P, const Cam& V, const SetDev& st, GProj& q) {
     double dx = P.mu[0] - V.T[0];
     double dy = P.mu[1] - V.T[1];
     double dz = P.mu[2] - V.T[2];
@@ -239,6 +267,117 @@ __device__ inline bool project_exact(const GPre& P, const ViewDev& V, const SetD
     return true;
 }
 
+
+// The binary32 screen of the projection.  Camera coordinates scaled to pixels are affine in the mean,
+// (U, V, z) = (fx t_x + cx t_z, fy t_y + cy t_z, t_z), taken relative to the first camera's centre, so that
+// their rounding follows the spread of map and cameras and not the distance from the world's origin.  With
+// a = U / z the support box's half extent is bounded above through
+// Sigma_xx <= s_max^2 |J_row0|^2 = (s_max / z)^2 (fx^2 + (a - cx)^2), and below by s_min fx / z.
+struct ScreenView {
+    float4 u, v, z;   // coefficients of the offset from the first camera's centre, and the constant
+    float4 kx, ky;    // (cx, fx^2, (W - 1) / 2, slack in pixels), (cy, fy^2, (H - 1) / 2, min(fx, fy))
+};
+
+__device__ __forceinline__ ScreenView screen_view(const ViewDev& V, const float* T0) {
+    ScreenView f;
+    double w[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) w[k] = V.T[k] - (double)T0[k];
+    double U[4], Y[4], Z[4];
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        U[k] = V.fx * V.R[3 * k] + V.cx * V.R[3 * k + 2];
+        Y[k] = V.fy * V.R[3 * k + 1] + V.cy * V.R[3 * k + 2];
+        Z[k] = V.R[3 * k + 2];
+    }
+    U[3] = -(U[0] * w[0] + U[1] * w[1] + U[2] * w[2]);
+    Y[3] = -(Y[0] * w[0] + Y[1] * w[1] + Y[2] * w[2]);
+    Z[3] = -(Z[0] * w[0] + Z[1] * w[1] + Z[2] * w[2]);
+    f.u = make_float4((float)U[0], (float)U[1], (float)U[2], (float)U[3]);
+    f.v = make_float4((float)Y[0], (float)Y[1], (float)Y[2], (float)Y[3]);
+    f.z = make_float4((float)Z[0], (float)Z[1], (float)Z[2], (float)Z[3]);
+    const float fx = fabsf(V.fxf), fy = fabsf(V.fyf), wx = (float)(V.W - 1), wy = (float)(V.H - 1);
+    // an R that is not a rotation, a field of view beyond 71 degrees to a side or far from square pixels would
+    // spoil the bounds: all pairs to binary64 then
+    bool plain = fx <= 2.0f * fy && fy <= 2.0f * fx && fmaxf(fabsf(V.cxf), fabsf(wx - V.cxf)) <= 3.0f * fx &&
+                 fmaxf(fabsf(V.cyf), fabsf(wy - V.cyf)) <= 3.0f * fy;
+#pragma unroll
+    for (int a = 0; a < 3; a++)
+#pragma unroll
+        for (int b = a; b < 3; b++) {
+            const float dot = V.Rf[a] * V.Rf[b] + V.Rf[3 + a] * V.Rf[3 + b] + V.Rf[6 + a] * V.Rf[6 + b];
+            plain = plain && fabsf(dot - (a == b ? 1.0f : 0.0f)) <= 1e-3f;
+        }
+    const float slack = plain ? 0.05f + 4e-4f * fmaxf(fx + 2.0f * fabsf(V.cxf), fy + 2.0f * fabsf(V.cyf)) : INFINITY;
+    f.kx = make_float4(V.cxf, fx * fx, 0.5f * wx, slack);
+    f.ky = make_float4(V.cyf, fy * fy, 0.5f * wy, fminf(fx, fy));
+    return f;
+}
+
+// What the screen knows of a Gaussian.  z is off by less than 3.5e-7 m, m = |offset|_1 + the largest |camera
+// offset|_1, and U, V by that times (f + |c|); err is 2e-6 m.  For z >= 1e3 err the pixel offset a - c is
+// then off by less than 2e-4 (f + 2 |c| + |a - c|) and the extent by less than a relative 1e-3: the
+// slack, 4e-4 |a - c| and 0.003 of the extent cover both.
+struct ScreenGauss {
+    float dx, dy, dz;  // offset from the first camera's centre
+    float hi, lo;      // bounds of rho s_max and rho s_min, rho^2 = 2 ln(o / alpha_min)
+    float ep;          // bound of rho^2 eps2d
+    float zlo, zhi;
+};
+
+// False if the binary64 form is invalid (pre_gauss returns false).
+__device__ __forceinline__ bool screen_gauss(const GaussDev& g, int64_t i, const SetDev& st, const float* T0,
+                                             ScreenGauss& G) {
+    const int64_t n = g.n;
+    const float m0 = g.means[i], m1 = g.means[n + i], m2 = g.means[2 * n + i];
+    const float op = g.opacity[i];
+    const float l0 = g.log_scales[i];
+    bool ok = isfinite(m0) && isfinite(m1) && isfinite(m2) && isfinite(l0) && isfinite(op) && op >= st.alpha_min;
+    float lmax = l0, lmin = l0;
+    if (!st.isotropic) {
+        const float l1 = g.log_scales[n + i], l2 = g.log_scales[2 * n + i];
+        const float q0 = g.quats[i], q1 = g.quats[n + i], q2 = g.quats[2 * n + i], q3 = g.quats[3 * n + i];
+        ok = ok && isfinite(l1) && isfinite(l2) && isfinite(q0) && isfinite(q1) && isfinite(q2) && isfinite(q3) &&
+             (q0 != 0.0f || q1 != 0.0f || q2 != 0.0f || q3 != 0.0f);
+        lmax = fmaxf(l0, fmaxf(l1, l2));
+        lmin = fminf(l0, fminf(l1, l2));
+    }
+    G.dx = m0 - T0[0];
+    G.dy = m1 - T0[1];
+    G.dz = m2 - T0[2];
+    // hardware logarithm and exponential, to about 1e-6 absolute and 1e-5 relative
+    const float rho2 = 1.38629436f * __builtin_amdgcn_logf(op / st.alpha_min);
+    const float rho2_hi = rho2 * 1.0001f + 1e-5f, rho2_lo = fmaxf(rho2 * 0.9999f - 1e-5f, 0.0f);
+    G.hi = __builtin_amdgcn_sqrtf(rho2_hi) * 1.0003f * fast_exp2(1.44269504f * lmax);
+    G.lo = __builtin_amdgcn_sqrtf(rho2_lo) * 0.9997f * fast_exp2(1.44269504f * lmin);
+    G.ep = rho2_hi * st.eps2d;
+    return ok;
+}
+
+// culled: the binary64 projection is certain to reject the pair; certain: it is certain to keep it.  That is
+// when the half extents are above 0.55 and reach half a pixel and every rounding into the image (so that
+// the box holds a pixel of it), and det Sigma cannot round to zero: extents below 1.1e6 (0.03 of them
+// is within the image or the lower bound) and above 0.55 keep (s_max / s_min)^2 below 4e12, so det, at least
+// (s_min f / z)^2 max(Sigma_xx, Sigma_yy), is above 2e-15 Sigma_xx Sigma_yy 30 times over.
+// Neither: the binary64 projection decides.
+__device__ __forceinline__ void screen_pair(const ScreenGauss& G, const ScreenView& V, bool& culled, bool& certain) {
+    const float z = fmaf(V.z.x, G.dx, fmaf(V.z.y, G.dy, fmaf(V.z.z, G.dz, V.z.w)));
+    const float U = fmaf(V.u.x, G.dx, fmaf(V.u.y, G.dy, fmaf(V.u.z, G.dz, V.u.w)));
+    const float Y = fmaf(V.v.x, G.dx, fmaf(V.v.y, G.dy, fmaf(V.v.z, G.dz, V.v.w)));
+    // hardware reciprocal and square root: within an ulp or two
+    const float iz = __builtin_amdgcn_rcpf(z);
+    const float r = G.hi * iz, r2 = r * r;
+    const float ax = U * iz, ay = Y * iz;
+    const float dx = ax - V.kx.x, dy = ay - V.ky.x;
+    const float hx = __builtin_amdgcn_sqrtf(fmaf(r2, fmaf(dx, dx, V.kx.y), G.ep));
+    const float hy = __builtin_amdgcn_sqrtf(fmaf(r2, fmaf(dy, dy, V.ky.y), G.ep));
+    const float sx = fmaf(4e-4f, fabsf(dx), V.kx.w), sy = fmaf(4e-4f, fabsf(dy), V.kx.w);
+    const float gx = fabsf(ax - V.kx.z) - V.kx.z, gy = fabsf(ay - V.ky.z) - V.ky.z;  // beyond the image's edge
+    const float lo = fmaf(G.lo * iz, V.ky.w, -0.56f);
+    const bool far = z >= G.zhi;  // no comparison holds for a NaN: binary64 decides
+    culled = (z <= G.zlo) | (far & ((fmaf(-1.003f, hx, gx) > sx) | (fmaf(-1.003f, hy, gy) > sy)));
+    certain = far & (lo >= 0.0f) & (fmaf(0.03f, hx, gx) < lo - sx) & (fmaf(0.03f, hy, gy) < lo - sy);  // not inf < inf
+}
 
 // ------------------------------------------------------- support extents
 // A splat's support {alpha >= alpha_min} in the whitened form is
@@ -361,51 +500,134 @@ __device__ __noinline__ uint2 support_row(SupportRows S, uint32_t ty, int tws, i
     return make_uint2(first, ((uint32_t)cr >> tws) - first + 1);
 }
 
-constexpr int PC_VIEWS = 256;
+// Few views (one word of them): a thread per Gaussian forms its binary64 form, screens the views and decides each
+// candidate.  The line to the queued kernel below: at 1 and 8 views this one took 9 and 57 us (200 k and 1 M
+// Gaussians), the queue 18 and 75 (its second reading of a Gaussian is not shared by enough views); at
+// 64 and 256 views (500 k and 2 M) this way took 135 and 1,460 us, the queue 94 and 1,040.
+constexpr int PC_FEW = 32;
 
-// STAGED (batches of at most PC_VIEWS views): the cameras' test values are
-// read from LDS; otherwise from the view table in global memory.
-template <bool STAGED>
 __global__ __launch_bounds__(256) void k_project_count(GaussDev g, const ViewDev* __restrict__ views,
-                                                       const Header* __restrict__ hdr, int words,
-                                                       SetDev st, uint32_t* __restrict__ cnt,
-                                                       uint32_t* __restrict__ mask) {
-    // the cameras' test values, staged in LDS (every thread reads the same
-    // camera at a time; from LDS it waits less than from the scalar cache,
-    // which the cameras of a large batch overflow)
-    __shared__ CullView s_vf[STAGED ? PC_VIEWS : 1];
-    int nv = (int)hdr->n_views;
-    if (STAGED) {
-        for (int t = threadIdx.x; t < min(nv, PC_VIEWS); t += blockDim.x) s_vf[t] = cull_view(views[t]);
-        __syncthreads();
-    }
+                                                       const Header* __restrict__ hdr, SetDev st,
+                                                       uint32_t* __restrict__ cnt, uint32_t* __restrict__ mask) {
+    // the cameras' test values, staged in LDS (every thread reads the same camera at a time)
+    __shared__ CullView s_vf[PC_FEW];
+    const int nv = min((int)hdr->n_views, PC_FEW);
+    if ((int)threadIdx.x < nv) s_vf[threadIdx.x] = cull_view(views[threadIdx.x]);
+    __syncthreads();
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.n) return;
     GPre P;
-    bool ok = pre_gauss(g, i, st, P);
-    uint32_t c = 0;
-    for (int w = 0; w < words; w++) {
-        uint32_t vis = 0;
-        int base = 32 * w;
-        if (ok && base < nv) {
-            uint32_t cand = 0;
-            int lim = min(32, nv - base);
-            for (int b = 0; b < lim; b++) {
-                const int vb = base + b;
-                const CullView V = STAGED ? s_vf[vb] : cull_view(views[vb]);
-                if (may_be_visible(P, V, st)) cand |= 1u << b;
-            }
-            while (cand) {
-                int b = __ffs(cand) - 1;
-                cand &= cand - 1;
-                GProj q;
-                if (project_exact(P, views[base + b], st, q)) vis |= 1u << b;
-            }
+    uint32_t vis = 0;
+    if (pre_gauss(g, i, st, P)) {
+        uint32_t cand = 0;
+        for (int b = 0; b < nv; b++)
+            if (may_be_visible(P, s_vf[b], st)) cand |= 1u << b;
+        while (cand) {
+            int b = __ffs(cand) - 1;
+            cand &= cand - 1;
+            GProj q;
+            if (project_exact(P, load_cam(views + b), st, q)) vis |= 1u << b;
         }
-        mask[(int64_t)w * g.n + i] = vis;
-        c += __popc(vis);
     }
-    cnt[i] = c;
+    mask[i] = vis;
+    cnt[i] = __popc(vis);
+}
+
+// Visible views of every Gaussian, as bits (mask[word][Gaussian]) and a count.  VIEWS cameras at a time lie in
+// LDS; the binary32 screen settles most pairs (98% of 2 M Gaussians in 256 views; 7% are visible), and the rest
+// go through a queue of the wave, so that the binary64 projection runs on 64 pairs at once instead of on the one or two
+// lanes of a wave whose pair is open.  Bound by the screen's instructions (about 50 per 64 pairs, two pairs
+// a lane in flight) and, at four waves per SIMD, by the latency of the binary64 part.
+constexpr int PC_VIEWS = 256;
+constexpr int PC_STEP = 2;
+
+// The binary64 decision.  Not inlined: its registers and constants stay out of the screen's loop.
+__device__ __noinline__ bool pair_visible(const GaussDev& g, int64_t i, const ViewDev* V, const SetDev& st) {
+    GPre P;
+    GProj q;
+    return pre_gauss(g, i, st, P) && project_exact(P, load_cam(V), st, q);
+}
+
+template <int VIEWS, int NT>
+__global__ __launch_bounds__(NT, 4) void k_project_count_queued(GaussDev g, const ViewDev* __restrict__ views,
+                                                         const Header* __restrict__ hdr, int words, SetDev st,
+                                                         uint32_t* __restrict__ cnt, uint32_t* __restrict__ mask) {
+    static_assert(VIEWS <= NT && VIEWS % 32 == 0 && VIEWS <= 256, "a thread stages a camera; a queue entry holds 8 bits of it");
+    __shared__ ScreenView s_v[VIEWS];
+    __shared__ uint32_t s_vis[VIEWS / 32][NT];
+    __shared__ uint16_t s_q[NT / 64][64 * (PC_STEP + 1)];  // lane | view << 6
+    __shared__ uint32_t s_spread;           // bits of the largest |camera offset|_1
+    const int nv = (int)hdr->n_views;
+    const int tid = threadIdx.x, wv = tid >> 6, lane = (int)lane_id();
+    const int64_t i0 = (int64_t)blockIdx.x * NT + 64 * wv, i = i0 + lane;
+    float T0[3] = {0.0f, 0.0f, 0.0f};
+    if (nv > 0)
+#pragma unroll
+        for (int k = 0; k < 3; k++) T0[k] = views[0].Tf[k];
+    ScreenGauss G{};
+    const bool ok = i < g.n && screen_gauss(g, i, st, T0, G);
+    uint32_t c = 0;
+    for (int base = 0; base < 32 * words; base += VIEWS) {
+        const int lim = max(0, min(VIEWS, nv - base));
+        if (tid == 0) s_spread = 0u;
+        __syncthreads();
+        if (tid < lim) {
+            const ViewDev& V = views[base + tid];
+            s_v[tid] = screen_view(V, T0);
+            atomicMax(&s_spread, __float_as_uint(fabsf(V.Tf[0] - T0[0]) + fabsf(V.Tf[1] - T0[1]) + fabsf(V.Tf[2] - T0[2])));
+        }
+        __syncthreads();
+        const float err = 2e-6f * (fabsf(G.dx) + fabsf(G.dy) + fabsf(G.dz) + __uint_as_float(s_spread));
+        G.zlo = st.z_near - err;
+        G.zhi = fmaxf(st.z_near + err, 1e3f * err);
+        uint32_t nq = 0;  // queued pairs of the wave
+        for (int w = 0; 32 * w < lim; w++) {
+            s_vis[w][tid] = 0u;
+            uint32_t vis = 0;
+            const int n = min(32, lim - 32 * w);
+            for (int b = 0; b < n; b += PC_STEP) {
+                // the screens of a step first: independent work that hides its latencies
+                bool culled[PC_STEP], certain[PC_STEP];
+#pragma unroll
+                for (int k = 0; k < PC_STEP; k++) screen_pair(G, s_v[32 * w + b + k], culled[k], certain[k]);
+#pragma unroll
+                for (int k = 0; k < PC_STEP; k++) {
+                    const bool here = ok & (b + k < n);
+                    vis |= here & certain[k] ? 1u << (b + k) : 0u;
+                    const bool open = here & !culled[k] & !certain[k];
+                    const uint64_t m = __ballot(open);
+                    if (open) s_q[wv][nq + (uint32_t)__popcll(m & lanemask_lt())] = (uint16_t)(lane | (32 * w + b + k) << 6);
+                    nq += (uint32_t)__popcll(m);
+                }
+                const bool last = 32 * w + b + PC_STEP >= lim;
+                while (nq >= 64u || (last && nq > 0u)) {
+                    const uint32_t take = min(nq, 64u);
+                    wave_lds_order();
+                    uint32_t e = 0;
+                    uint32_t rest[PC_STEP];
+#pragma unroll
+                    for (int k = 0; k < PC_STEP; k++) rest[k] = s_q[wv][64 * (k + 1) + lane];
+                    e = s_q[wv][lane];
+                    const uint32_t src = e & 63u, v = e >> 6;
+                    if ((uint32_t)lane < take && pair_visible(g, i0 + src, views + base + v, st))
+                        atomicOr(&s_vis[v >> 5][64 * wv + src], 1u << (v & 31));
+                    wave_lds_order();
+#pragma unroll
+                    for (int k = 0; k < PC_STEP; k++) s_q[wv][64 * k + lane] = (uint16_t)rest[k];
+                    nq -= take;
+                }
+            }
+            atomicOr(&s_vis[w][tid], vis);
+        }
+        wave_lds_order();
+        for (int w = 0; w < VIEWS / 32 && base / 32 + w < words; w++) {
+            const uint32_t vis = 32 * w < lim ? s_vis[w][tid] : 0u;
+            if (i < g.n) mask[(int64_t)(base / 32 + w) * g.n + i] = vis;
+            c += __popc(vis);
+        }
+        __syncthreads();
+    }
+    if (i < g.n) cnt[i] = c;
 }
 
 // -------------------------------------------------------------- prefix sum
@@ -1084,9 +1306,8 @@ __global__ __launch_bounds__(PE_THREADS) void k_project_emit(GaussDev g, const V
             GPre P;
             if (shared_pre) P = s_pre[i - lo];
             else pre_gauss(g, i, st, P);
-            const ViewDev& V = views[v];
             GProj q;
-            project_exact(P, V, st, q);
+            project_exact(P, load_cam(views + v), st, q);
             float mxh = (float)q.mx, myh = (float)q.my;
             const float4 g0 = make_float4(mxh, myh, (float)(q.mx - (double)mxh), (float)(q.my - (double)myh));
             double det = q.cxx * q.cyy - q.cxy * q.cxy;
@@ -1904,12 +2125,6 @@ __global__ __launch_bounds__(SP_THREADS) void k_sum_partials(const double* __res
 // Reverse mode of the compositing, walking each tile back to front; the
 // transmittance before splat i is recovered as T_{i+1} / (1 - a_i).
 
-// Orders a wave's LDS stores and loads (a compiler's matter: the hardware keeps them in order).
-__device__ __forceinline__ void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Words between the rows of the backward's reduction in LDS: rows r to r + 15 start 4 banks apart each, so
 // 16-byte reads of 16 rows meet no bank twice.
 constexpr int RED_STRIDE = 68;
@@ -2264,7 +2479,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(GaussDev g, const ViewDev* 
     double go = 0.0, gc[3] = {0, 0, 0};
     uint32_t r0 = rec_off[i];
     for (uint32_t r = r0; r < r0 + c; r++) {
-        const ViewDev& V = views[emit[r].view];
+        const Cam V = load_cam(views + emit[r].view);
         GProj q;
         project_exact(P, V, st, q);
         const double* G2 = g2d + (uint64_t)r * G2D_STRIDE;
@@ -3292,10 +3507,10 @@ void project_count(const GaussDev& g, const ViewDev* views, const Header* hdr, i
     if (g.n == 0) return;
     int words = (n_views_cap + 31) / 32;
     // one thread per Gaussian: the grid covers every n below 2^31
-    if (n_views_cap <= PC_VIEWS)
-        k_project_count<true><<<grid_for(g.n, 256, 0xffffffffu), 256, 0, s>>>(g, views, hdr, words, st, cnt, mask);
+    if (n_views_cap <= PC_FEW)
+        k_project_count<<<grid_for(g.n, 256, 0xffffffffu), 256, 0, s>>>(g, views, hdr, st, cnt, mask);
     else
-        k_project_count<false><<<grid_for(g.n, 256, 0xffffffffu), 256, 0, s>>>(g, views, hdr, words, st, cnt, mask);
+        k_project_count_queued<PC_VIEWS, 512><<<grid_for(g.n, 512, 0xffffffffu), 512, 0, s>>>(g, views, hdr, words, st, cnt, mask);
 }
 
 // log2 of a power-of-two tile side (8, 16 or 32)
