@@ -449,10 +449,9 @@ struct SupportRows {
     int all;              // 1: no culling (degenerate form, not expected)
 };
 
-// Pair counting and pair emission both call support_setup and support_row,
-// two non-inlined functions, on the same stored record values (geo0, geo1,
-// pixel box), so they agree exactly.
-__device__ __noinline__ SupportRows support_setup(float4 g0, float4 g1, uint2 pb, float log2_amin) {
+// Pair counting and pair emission both evaluate support_setup and support_row on the same stored record values
+// (geo0, geo1, pixel box); the code is compiled without contraction and reassociation, so they agree exactly.
+__device__ __forceinline__ SupportRows support_setup(float4 g0, float4 g1, uint2 pb, float log2_amin) {
     SupportRows S;
     const float a = g1.x, b = g1.y, c = g1.z;
     S.mx = g0.x + g0.z;
@@ -477,7 +476,7 @@ __device__ __noinline__ SupportRows support_setup(float4 g0, float4 g1, uint2 pb
 
 // Tiles of tile row ty (tiles 2^tws x 2^ths) that a record's support meets
 // inside its pixel box, as (first column, count).
-__device__ __noinline__ uint2 support_row(SupportRows S, uint32_t ty, int tws, int ths) {
+__device__ __forceinline__ uint2 support_row(const SupportRows& S, uint32_t ty, int tws, int ths) {
     const int u0 = (int)(S.pb_x & 0xffffu), u1 = (int)(S.pb_x >> 16);
     const int v0 = (int)(S.pb_y & 0xffffu), v1 = (int)(S.pb_y >> 16);
     const int y0 = max((int)(ty << ths), v0), y1 = min((int)((ty + 1) << ths) - 1, v1);
@@ -1065,23 +1064,6 @@ __global__ __launch_bounds__(NT) void k_rs_scatter(const uint32_t* __restrict__ 
 
 // ---------------------------------------------------------------- binning
 
-// A block covers EM_ITEMS consecutive pairs and each thread EM_RUN
-// consecutive ones.  The depth-ordered records spanning the block are found
-// by one binary search over the pair offsets and their offsets staged in LDS.
-// A record whose support meets every tile of its box is enumerated in
-// row-major order directly.  For the others the block evaluates every tile
-// row of their rectangles once, in parallel (one support_row call per row),
-// into an LDS table of (first column, count) and its prefix; a thread then
-// finds the row of each of its pairs by binary search.  A block whose records
-// have more than EM_ROWS such rows falls back to a per-thread cursor that
-// walks the rows up to its first pair.  Output is written in depth order,
-// EM_RUN pairs per 16-byte store.
-constexpr int EM_THREADS = 256;
-constexpr int EM_RUN = 4;
-constexpr int EM_ITEMS = EM_THREADS * EM_RUN;
-constexpr int EM_ROWS = 2048;
-constexpr int EM_ROWS_PT = EM_ROWS / EM_THREADS;
-
 __device__ __forceinline__ uint32_t last_le(const uint32_t* a, uint32_t n, uint32_t x) {
     // largest i < n with a[i] <= x (a[0] == 0 <= x)
     uint32_t lo = 0, hi = n - 1;
@@ -1112,75 +1094,45 @@ __device__ __forceinline__ uint32_t wave_last_le(const uint32_t* __restrict__ a,
     return lo;
 }
 
-// Position within one record's pairs.
-struct PairCursor {
-    uint32_t r, tile_off, tiles_x, tx0, nx, ty0, ty1;
-    bool full;       // every tile of the box
-    SupportRows S;   // when !full
-    uint32_t li;     // pair index within the record (full)
-    uint32_t ty, first, cnt, rem;  // current support row (!full)
+// The tile rows of a wave's records, laid out one after another and taken 64 at a time, a lane a row.  A
+// record's support constants wait in LDS at its rank among the records that have rows.
+struct RowRec {
+    float4 s0;   // mx, my, dyr, P
+    float4 s1;   // Qc, Bc, pixel box
 };
 
-// Next row with a nonzero count at or after c.ty; false if none is left.
-__device__ __forceinline__ bool cursor_row(PairCursor& c, int tws, int ths) {
-    for (; c.ty <= c.ty1; c.ty++) {
-        const uint2 fc = support_row(c.S, c.ty, tws, ths);
-        if (fc.y) {
-            c.first = fc.x;
-            c.cnt = fc.y;
-            return true;
-        }
-    }
-    return false;
+__device__ __forceinline__ RowRec row_rec(const SupportRows& S) {
+    return {make_float4(S.mx, S.my, S.dyr, S.P), make_float4(S.Qc, S.Bc, __uint_as_float(S.pb_x), __uint_as_float(S.pb_y))};
 }
 
-__device__ __forceinline__ void cursor_open(PairCursor& c, const Records& rec, const ViewDev* views, uint32_t r,
-                                            uint32_t li, int tws, int ths, float log2_amin, uint32_t* flags) {
-    c.r = r;
-    const EmitRec e = rec.emit[r];
-    const uint2 rc = e.rect;
-    c.tx0 = rc.x & 0xffffu;
-    c.nx = (rc.x >> 16) - c.tx0 + 1;
-    c.ty0 = rc.y & 0xffffu;
-    c.ty1 = rc.y >> 16;
-    const ViewDev& V = views[e.view];
-    c.tile_off = V.tile_off;
-    c.tiles_x = (uint32_t)V.tiles_x;
-    c.full = e.ntiles == c.nx * (c.ty1 - c.ty0 + 1);
-    c.li = li;
-    if (c.full) return;
-    c.S = support_setup(e.g0, e.g1, e.pbox, log2_amin);
-    c.ty = c.ty0;
-    uint32_t rem = li;
-    while (cursor_row(c, tws, ths)) {
-        if (rem < c.cnt) {
-            c.rem = rem;
-            return;
-        }
-        rem -= c.cnt;
-        c.ty++;
-    }
-    // a support that meets no tile still owns one pair, its box's first tile;
-    // anything else would be a counting mismatch
-    if (li != 0) atomicOr(flags, FLAG_BIN_MISMATCH);
-    c.full = true;
-    c.nx = 1;
-    c.li = 0;
+__device__ __forceinline__ SupportRows support_rows(const RowRec& r) {
+    SupportRows S;
+    S.mx = r.s0.x;
+    S.my = r.s0.y;
+    S.dyr = r.s0.z;
+    S.P = r.s0.w;
+    S.Qc = r.s1.x;
+    S.Bc = r.s1.y;
+    S.pb_x = __float_as_uint(r.s1.z);
+    S.pb_y = __float_as_uint(r.s1.w);
+    S.all = 0;
+    return S;
 }
 
-__device__ __forceinline__ uint32_t cursor_tile(const PairCursor& c) {
-    if (c.full) return c.tile_off + (c.ty0 + c.li / c.nx) * c.tiles_x + c.tx0 + c.li % c.nx;
-    return c.tile_off + c.ty * c.tiles_x + c.first + c.rem;
+// Lanes mark positions [0, 64 W) of a window (`mark` lanes, distinct positions) and every lane gets the marks of each
+// 64 as a mask: the rank of a lane's owner is then a population count, where a search would be a chain of LDS reads.
+template <int W>
+__device__ __forceinline__ void window_marks(uint32_t* bits, bool mark, uint32_t at, uint64_t (&m)[W]) {
+    wave_lds_order();
+    if (lane_id() < 2 * W) bits[lane_id()] = 0u;
+    wave_lds_order();
+    if (mark) atomicOr(&bits[at >> 5], 1u << (at & 31u));
+    wave_lds_order();
+#pragma unroll
+    for (int w = 0; w < W; w++) m[w] = (uint64_t)bits[2 * w] | (uint64_t)bits[2 * w + 1] << 32;
 }
 
-__device__ __forceinline__ void cursor_next(PairCursor& c, int tws, int ths) {
-    c.li++;
-    if (c.full) return;
-    if (++c.rem < c.cnt) return;
-    c.rem = 0;
-    c.ty++;
-    cursor_row(c, tws, ths);  // the caller knows the record has another pair
-}
+__device__ __forceinline__ uint64_t lanemask_le() { return ~0ull >> (63 - lane_id()); }
 
 // Record emission, one thread per record so that the record arrays are
 // written in contiguous runs: the records of Gaussian i are rec_off[i] ...
@@ -1191,15 +1143,8 @@ __device__ __forceinline__ void cursor_next(PairCursor& c, int tws, int ths) {
 constexpr int PE_THREADS = 256;
 constexpr uint32_t PE_LDS = 2048;
 constexpr uint32_t PE_PRE = 64;
-// Records with more tile rows than this have their rows counted by the
-// whole wave (a wave would otherwise loop as long as its tallest record).
-constexpr uint32_t PE_ROWS_SELF = 4;
 // Visibility mask words a record's view search loads at once.
 constexpr int PE_MASK_WORDS = 8;
-
-__device__ __forceinline__ float readlane_f(float x, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
-}
 
 // Position of the k-th (from 0) set bit of x (k < popcount(x)), by halving.
 __device__ __forceinline__ int nth_set_bit(uint32_t x, uint32_t k) {
@@ -1241,7 +1186,11 @@ __global__ __launch_bounds__(256) void k_chunk_owners(const uint32_t* __restrict
     }
 }
 
-__global__ __launch_bounds__(PE_THREADS) void k_project_emit(GaussDev g, const ViewDev* __restrict__ views,
+// Bound by the instructions of the binary64 form (two divisions and two square roots beyond the projection's own) and
+// its registers: three waves per SIMD; four spill 42 of them (1,870 -> 2,050 us).  With the rows counted by
+// the wave together, where each lane walked up to four of its own and the wave the rest record by record:
+// 256 views of 2 M Gaussians 2,230 -> 1,870 us, 8 frames of 1 M 141 -> 71, one of 300 k 50 -> 24.
+__global__ __launch_bounds__(PE_THREADS, 3) void k_project_emit(GaussDev g, const ViewDev* __restrict__ views,
                                                              int words, SetDev st, int tws, int ths,
                                                              const uint32_t* __restrict__ mask,
                                                              const uint32_t* __restrict__ rec_off,
@@ -1252,6 +1201,11 @@ __global__ __launch_bounds__(PE_THREADS) void k_project_emit(GaussDev g, const V
                                                              uint32_t* __restrict__ flags) {
     __shared__ uint32_t s_off[PE_LDS];
     __shared__ GPre s_pre[PE_PRE];
+    __shared__ RowRec s_rows[PE_THREADS];
+    __shared__ uint2 s_row0[PE_THREADS];    // first row of the record among the wave's, its first tile row
+    __shared__ uint32_t s_nt[PE_THREADS];   // pairs
+    __shared__ uint32_t s_bits[PE_THREADS / 64][2];
+    const int lane = (int)lane_id(), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), wb = 64 * wv;
     const uint32_t Rall = *R_dev;
     if (blockIdx.x == 0 && threadIdx.x == 0 && Rall > rec_cap) atomicOr(flags, FLAG_REC_OVERFLOW);
     const uint32_t R = min(Rall, rec_cap);
@@ -1271,10 +1225,9 @@ __global__ __launch_bounds__(PE_THREADS) void k_project_emit(GaussDev g, const V
         __syncthreads();
         const uint32_t pos = k0 + threadIdx.x;
         const bool valid = pos < k1;
-        // the record's support rows: a record with few tile rows counts its
-        // own; the wave counts the rows of the others together below
         SupportRows S{};
-        uint32_t nt = 0, ty0 = 0, ny = 0;
+        uint32_t ty0 = 0, nrow = 0, ntiles = 1;
+        EmitRec e;
         if (valid) {
             // owner Gaussian: the last one whose first record is at or before pos
             const uint32_t ii = staged ? last_le(s_off, ng, pos) : last_le(rec_off + lo, ng, pos);
@@ -1310,15 +1263,13 @@ __global__ __launch_bounds__(PE_THREADS) void k_project_emit(GaussDev g, const V
             project_exact(P, load_cam(views + v), st, q);
             float mxh = (float)q.mx, myh = (float)q.my;
             const float4 g0 = make_float4(mxh, myh, (float)(q.mx - (double)mxh), (float)(q.my - (double)myh));
-            double det = q.cxx * q.cyy - q.cxy * q.cxy;
-            // Sigma_2D = C C^T (Cholesky); M = sqrt(log2e / 2) C^-1
-            double c00 = sqrt(q.cxx);
-            double c10 = q.cxy / c00;
-            double c11 = sqrt(det / q.cxx);
-            double sl = sqrt(0.5 * LOG2E);
-            const float4 g1 = make_float4((float)(sl / c00), (float)(-sl * c10 / (c00 * c11)), (float)(sl / c11),
-                                          (float)P.o);
-            rec.q64[pos] = make_double4(q.cyy / det, -q.cxy / det, q.cxx / det, P.rho2);
+            const double det = q.cxx * q.cyy - q.cxy * q.cxy;
+            const double idet = 1.0 / det, icxx = 1.0 / q.cxx;
+            // Sigma_2D = C C^T (Cholesky); M = sqrt(log2e / 2) C^-1 = sl [[1 / c00, 0], [-c10 / (c00 c11), 1 / c11]]
+            const double sl = sqrt(0.5 * LOG2E);
+            const double m11 = sl * sqrt(q.cxx * idet);
+            const float4 g1 = make_float4((float)(sl * sqrt(icxx)), (float)(-q.cxy * icxx * m11), (float)m11, (float)P.o);
+            rec.q64[pos] = make_double4(q.cyy * idet, -q.cxy * idet, q.cxx * idet, P.rho2);
             float depth = (float)q.t[2];
             const int64_t gi = i;
             if (write_attr) {
@@ -1327,84 +1278,87 @@ __global__ __launch_bounds__(PE_THREADS) void k_project_emit(GaussDev g, const V
                 else
                     rec.attr[pos] = make_float4(0.0f, 0.0f, 0.0f, depth);
             }
-            uint32_t tx0 = (uint32_t)q.u0 >> tws, tx1 = (uint32_t)q.u1 >> tws;
+            const uint32_t tx0 = (uint32_t)q.u0 >> tws, tx1 = (uint32_t)q.u1 >> tws;
             ty0 = (uint32_t)q.v0 >> ths;
             const uint32_t ty1 = (uint32_t)q.v1 >> ths;
-            ny = ty1 - ty0 + 1;
             const uint2 pb = make_uint2((uint32_t)q.u0 | ((uint32_t)q.u1 << 16),
                                         (uint32_t)q.v0 | ((uint32_t)q.v1 << 16));
             sortkey[pos] = __float_as_uint(depth);
             S = support_setup(g0, g1, pb, st.log2_amin);
-            if (ny <= PE_ROWS_SELF)
-                for (uint32_t ty = ty0; ty <= ty1; ty++) nt += support_row(S, ty, tws, ths).y;
-            EmitRec e;
+            ntiles = (tx1 - tx0 + 1) * (ty1 - ty0 + 1);
+            // the only tile of a box is the record's pair in any case, and a degenerate form is not culled
+            nrow = ntiles > 1u && !S.all ? ty1 - ty0 + 1 : 0u;
             e.g0 = g0;
             e.g1 = g1;
             e.pbox = pb;
             e.rect = make_uint2(tx0 | (tx1 << 16), ty0 | (ty1 << 16));
-            e.ntiles = 0;  // written below
             e.view = (uint32_t)v;
             e.unc = __float_as_uint(g.uncert ? g.uncert[gi] : 0.0f);
             e.gid = i;
-            rec.emit[pos] = e;
             order[pos] = pos;
         }
-        // every lane takes one row of the record at a time; the per-row
-        // counts are integers, so their sum does not depend on the split
-        uint64_t big = __ballot(valid && ny > PE_ROWS_SELF);
-        while (big) {
-            const int src = __builtin_ctzll(big);
-            big &= big - 1;
-            SupportRows B;
-            B.mx = readlane_f(S.mx, src);
-            B.my = readlane_f(S.my, src);
-            B.dyr = readlane_f(S.dyr, src);
-            B.P = readlane_f(S.P, src);
-            B.Qc = readlane_f(S.Qc, src);
-            B.Bc = readlane_f(S.Bc, src);
-            B.pb_x = (uint32_t)__builtin_amdgcn_readlane((int)S.pb_x, src);
-            B.pb_y = (uint32_t)__builtin_amdgcn_readlane((int)S.pb_y, src);
-            B.all = __builtin_amdgcn_readlane(S.all, src);
-            const uint32_t bty0 = (uint32_t)__builtin_amdgcn_readlane((int)ty0, src);
-            const uint32_t bny = (uint32_t)__builtin_amdgcn_readlane((int)ny, src);
-            uint32_t part = 0;
-            for (uint32_t r = lane_id(); r < bny; r += 64) part += support_row(B, bty0 + r, tws, ths).y;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) part += (uint32_t)__shfl_xor((int)part, o, 64);
-            if ((int)lane_id() == src) nt = part;
+        // the pairs of a record, the tiles its support meets: the wave takes the rows of its records 64 at a time
+        // (integer counts, so their sum does not depend on the split)
+        const uint64_t has = __ballot(nrow > 0u);
+        if (has) {
+            const uint32_t first = wave_incl_scan(nrow) - nrow;
+            const uint32_t rows = (uint32_t)__builtin_amdgcn_readlane((int)(first + nrow), 63);
+            const int rank = (int)__popcll(has & lanemask_lt());
+            if (nrow > 0u) {
+                s_rows[wb + rank] = row_rec(S);
+                s_row0[wb + rank] = make_uint2(first, ty0);
+                s_nt[wb + rank] = 0u;
+            }
+            int before = 0;  // records that start before the window
+            for (uint32_t t0 = 0; t0 < rows; t0 += 64) {
+                uint64_t m[1];
+                window_marks<1>(s_bits[wv], nrow > 0u && first - t0 < 64u, first - t0, m);
+                const int own = wb + before + (int)__popcll(m[0] & lanemask_le()) - 1;
+                before += (int)__popcll(m[0]);
+                if (t0 + (uint32_t)lane < rows) {
+                    const uint2 r0 = s_row0[own];
+                    const uint32_t n = support_row(support_rows(s_rows[own]), r0.y + (t0 + (uint32_t)lane - r0.x), tws, ths).y;
+                    if (n) atomicAdd(&s_nt[own], n);
+                }
+            }
+            wave_lds_order();
+            if (nrow > 0u) {
+                ntiles = s_nt[wb + rank];
+                if (ntiles == 0u) {
+                    // a support that meets no tile still owns one pair, its box's first tile
+                    ntiles = 1u;
+                    e.rect = make_uint2((e.rect.x & 0xffffu) * 0x10001u, (e.rect.y & 0xffffu) * 0x10001u);
+                }
+            }
+            wave_lds_order();
         }
         if (valid) {
-            // pairs: the tiles the support meets (a subset of the box's
-            // tiles); at least one, so that every record owns a pair
-            rec.ntiles[pos] = max(nt, 1u);
-            rec.emit[pos].ntiles = max(nt, 1u);
+            e.ntiles = ntiles;
+            rec.ntiles[pos] = ntiles;
+            rec.emit[pos] = e;
         }
     }
 }
 
-// Record offsets per thread for one chunk's EM_ITEMS + 1 entries.
-constexpr int EM_OFF_PT = (EM_ITEMS + 1 + EM_THREADS - 1) / EM_THREADS;
+// Pair emission.  A wave takes a contiguous run of the pairs and walks the depth-ordered records that own them, 64 at a
+// time, a lane a record; then their tile rows, 64 at a time, a lane a row (every row of a record whose pairs are
+// all the tiles of its rectangle, the support's columns of a row otherwise); then the rows' pairs, 128
+// at a time, so that wide rows and tall records cost what their pairs cost.
+// Nothing is staged for a whole block, so no barrier holds a wave up.  Bound by the gather of the records in depth
+// order (a cache line for 64 bytes) and the pairs' stores.  192 M pairs of 256 views: 2,300 us with blocks that tabulated
+// the rows of 1,024 pairs and found each pair's record and row by binary search in LDS, 1,350 now (2 x 768 MB
+// written); 39.7 M pairs of 8 frames 408 -> 110; 1.0 M of one frame 17.6 -> 14.5.
+constexpr int EM_THREADS = 256;
+constexpr int EM_WAVES = EM_THREADS / 64;
+constexpr uint32_t EM_RUN = 256;  // the smallest run of a wave
+constexpr unsigned EM_BLOCKS = 16384;
 
-// Loads (issues) a chunk's record offsets from its first record lo and the
-// ids of the records the thread sets up; entries past the last record read as
-// "after every pair" (offsets) and 0 (ids).
-__device__ __forceinline__ void em_load_chunk(const uint32_t* __restrict__ inst_off,
-                                              const uint32_t* __restrict__ order, uint32_t R, uint32_t lo,
-                                              uint32_t (&off)[EM_OFF_PT], uint32_t (&rid)[EM_RUN]) {
-    const uint32_t navail = min<uint32_t>(EM_ITEMS + 1, R - lo);
-#pragma unroll
-    for (int m = 0; m < EM_OFF_PT; m++) {
-        const uint32_t q = threadIdx.x + m * EM_THREADS;
-        off[m] = q < navail ? inst_off[lo + q] : 0xffffffffu;
-    }
-#pragma unroll
-    for (int q = 0; q < EM_RUN; q++) {
-        const uint32_t jr = threadIdx.x * EM_RUN + q;
-        rid[q] = jr < R - lo ? order[lo + jr] : 0u;
-    }
-}
+struct EmitMeta {
+    uint32_t tile, tiles_x;  // the rectangle's first tile; tiles per row of the view
+    uint32_t tx, ty0;        // tx0 | nx << 16; first tile row, or 0xffffffff if every tile of the rectangle is a pair
+};
 
-__global__ __launch_bounds__(EM_THREADS, 4) void k_emit_instances(const uint32_t* __restrict__ order,
+__global__ __launch_bounds__(EM_THREADS, 6) void k_emit_instances(const uint32_t* __restrict__ order,
                                                                const uint32_t* __restrict__ R_dev, uint32_t rec_cap,
                                                                const uint32_t* __restrict__ K_dev, Records rec,
                                                                const ViewDev* __restrict__ views,
@@ -1414,16 +1368,11 @@ __global__ __launch_bounds__(EM_THREADS, 4) void k_emit_instances(const uint32_t
                                                                uint32_t* __restrict__ inst_rec,
                                                                uint2* __restrict__ ranges, uint32_t tiles_cap,
                                                                uint32_t* __restrict__ flags) {
-    __shared__ uint32_t s_off[EM_ITEMS + 1];
-    __shared__ uint32_t s_roff[EM_ITEMS + 1];  // first table row of each record (prefix of row counts)
-    __shared__ uint32_t s_row[EM_ROWS];        // first tile column | pairs of the row << 16
-    __shared__ uint32_t s_rpre[EM_ROWS + 1];   // pairs of all table rows before this one
-    // per record of the chunk: its id, its first tile row's global tile id
-    // minus tx0, tx0 | nx << 16, and its view's tiles per row
-    __shared__ uint32_t s_rid[EM_ITEMS], s_tbase[EM_ITEMS], s_tx[EM_ITEMS];
-    __shared__ uint16_t s_tpr[EM_ITEMS];
-    __shared__ uint32_t ws[SC_THREADS / 64];
-    __shared__ uint32_t s_lo;
+    __shared__ RowRec s_rows[EM_THREADS];
+    __shared__ EmitMeta s_meta[EM_THREADS];
+    __shared__ uint4 s_own[EM_THREADS];   // record id, first row among the wave's, the next record's first row and first pair
+    __shared__ uint4 s_run[EM_THREADS];   // rows with pairs: first pair, its tile, record id
+    __shared__ uint32_t s_bits[EM_WAVES][4];
     // every tile starts empty; k_tile_ranges later fills the occupied ones
     // (nothing reads the ranges in between), and an overflow leaves them empty
     for (uint32_t t = blockIdx.x * EM_THREADS + threadIdx.x; t < tiles_cap; t += gridDim.x * EM_THREADS)
@@ -1434,188 +1383,93 @@ __global__ __launch_bounds__(EM_THREADS, 4) void k_emit_instances(const uint32_t
     if (threadIdx.x == 0 && blockIdx.x == 0 && Kall > inst_cap) atomicOr(flags, FLAG_INST_OVERFLOW);
     const uint32_t K = min(Kall, inst_cap);
     if (R == 0) return;
-    // each block takes one contiguous run of whole EM_ITEMS chunks, so that
-    // the records of a chunk follow those of the previous one: one search in
-    // global memory per block, then one coalesced load of the next EM_ITEMS + 1
-    // record offsets per chunk
-    const uint32_t per = (uint32_t)(((uint64_t)K + (uint64_t)gridDim.x * EM_ITEMS - 1) /
-                                    ((uint64_t)gridDim.x * EM_ITEMS)) * EM_ITEMS;
-    const uint32_t kbeg = (uint32_t)min<uint64_t>((uint64_t)blockIdx.x * per, K);
-    const uint32_t kend = (uint32_t)min<uint64_t>((uint64_t)kbeg + per, K);
-    if (kbeg >= kend) return;
-    if (threadIdx.x < 64) {
-        const uint32_t lo0 = wave_last_le(inst_off, R, kbeg);
-        if (threadIdx.x == 0) s_lo = lo0;
-    }
-    __syncthreads();
-    uint32_t lo_chunk = s_lo;
-    // the first chunk's record offsets and ids; every chunk then issues the
-    // next one's loads before it sets up its own records, so that they arrive
-    // while it works
-    uint32_t pf_off[EM_OFF_PT], pf_rid[EM_RUN];
-    em_load_chunk(inst_off, order, R, lo_chunk, pf_off, pf_rid);
-    for (uint32_t k0 = kbeg; k0 < kend; k0 += EM_ITEMS) {
-        const uint32_t k1 = min(k0 + EM_ITEMS, kend);  // exclusive
-        const uint32_t lo = lo_chunk;
-        __syncthreads();
-        // the offsets of the records from the first one spanning the chunk
-        // (every record owns at least one pair, so at most EM_ITEMS records
-        // span it); entries past the last record read as "after every pair"
-        const uint32_t navail = min<uint32_t>(EM_ITEMS + 1, R - lo);
-#pragma unroll
-        for (int m = 0; m < EM_OFF_PT; m++) {
-            const uint32_t q = threadIdx.x + m * EM_THREADS;
-            if (q < EM_ITEMS + 1) s_off[q] = pf_off[m];
+    const uint32_t lane = lane_id(), wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), wb = 64 * wv;
+    const uint64_t waves = (uint64_t)gridDim.x * EM_WAVES;
+    const uint64_t per = (((uint64_t)K + waves - 1) / waves + EM_RUN - 1) / EM_RUN * EM_RUN;
+    const uint64_t w0 = ((uint64_t)blockIdx.x * EM_WAVES + wv) * per;
+    const uint32_t kbeg = (uint32_t)min<uint64_t>(w0, K), kend = (uint32_t)min<uint64_t>(w0 + per, K);
+    if (kbeg >= kend) return;  // no barrier below
+    uint32_t base = kbeg;      // first pair of the next row
+    for (uint32_t r0 = wave_last_le(inst_off, R, kbeg); r0 < R && base < kend; r0 += 64) {
+        const uint32_t idx = r0 + lane;
+        const uint32_t off = idx < R ? inst_off[idx] : 0xffffffffu;
+        const uint32_t end = idx + 1 < R ? inst_off[idx + 1] : Kall;
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
+        const bool valid = idx < R && off < kend;
+        uint32_t nrow = 0;
+        wave_lds_order();
+        if (valid) {
+            const uint32_t rid = order[idx];
+            const EmitRec e = rec.emit[rid];
+            const ViewDev& V = views[e.view];
+            const uint32_t tx0 = e.rect.x & 0xffffu, ty0 = e.rect.y & 0xffffu;
+            const uint32_t nx = (e.rect.x >> 16) - tx0 + 1;
+            nrow = (e.rect.y >> 16) - ty0 + 1;
+            EmitMeta md;
+            md.tiles_x = (uint32_t)V.tiles_x;
+            md.tile = V.tile_off + ty0 * (uint32_t)V.tiles_x;
+            md.tx = tx0 | (nx << 16);
+            md.ty0 = e.ntiles == nx * nrow ? 0xffffffffu : ty0;
+            s_meta[wb + lane] = md;
+            s_rows[wb + lane] = row_rec(support_setup(e.g0, e.g1, e.pbox, log2_amin));
+            s_own[wb + lane].x = rid;
         }
-        __syncthreads();
-        const uint32_t nrec = last_le(s_off, navail, k1 - 1) + 1;
-        lo_chunk = lo + last_le(s_off, navail, k1);  // the next chunk's first record
-        uint32_t rids[EM_RUN];
-#pragma unroll
-        for (int q = 0; q < EM_RUN; q++) rids[q] = pf_rid[q];
-        if (k1 < kend) em_load_chunk(inst_off, order, R, lo_chunk, pf_off, pf_rid);
-        // table rows of the records (EM_RUN records per thread): every tile
-        // row of a record that is not enumerated directly
-        uint32_t nr[EM_RUN];
-        uint32_t nsum = 0;
-#pragma unroll
-        for (int q = 0; q < EM_RUN; q++) {
-            const uint32_t jr = threadIdx.x * EM_RUN + q;
-            nr[q] = 0;
-            if (jr < nrec) {
-                const uint32_t rid = rids[q];
-                const EmitRec e = rec.emit[rid];
-                const uint32_t tx0 = e.rect.x & 0xffffu, ty0 = e.rect.y & 0xffffu;
-                const uint32_t nx = (e.rect.x >> 16) - tx0 + 1;
-                const uint32_t ny = (e.rect.y >> 16) - ty0 + 1;
-                nr[q] = e.ntiles == nx * ny ? 0u : ny;
-                const ViewDev& V = views[e.view];
-                s_rid[jr] = rid;
-                s_tbase[jr] = V.tile_off + ty0 * (uint32_t)V.tiles_x;
-                s_tx[jr] = tx0 | (nx << 16);
-                s_tpr[jr] = (uint16_t)V.tiles_x;
-            }
-            nsum += nr[q];
+        const uint32_t next = wave_incl_scan(nrow), first = next - nrow;
+        if (valid) {
+            s_own[wb + lane].y = first;
+            s_own[wb + lane].z = next;
+            s_own[wb + lane].w = end;
         }
-        uint32_t total_rows;
-        uint32_t rbase = block_excl_scan(nsum, ws, total_rows);
-#pragma unroll
-        for (int q = 0; q < EM_RUN; q++) {
-            const uint32_t jr = threadIdx.x * EM_RUN + q;
-            if (jr < nrec) s_roff[jr] = rbase;
-            rbase += nr[q];
-        }
-        if (threadIdx.x == 0) s_roff[nrec] = total_rows;
-        const bool staged = total_rows <= (uint32_t)EM_ROWS;
-        if (staged) {
-            __syncthreads();
-            for (uint32_t t = threadIdx.x; t < total_rows; t += EM_THREADS) {
-                const uint32_t jr = last_le(s_roff, nrec, t);
-                const EmitRec e = rec.emit[s_rid[jr]];
-                const SupportRows S = support_setup(e.g0, e.g1, e.pbox, log2_amin);
-                const uint2 fc = support_row(S, (e.rect.y & 0xffffu) + (t - s_roff[jr]), tws, ths);
-                s_row[t] = fc.x | (fc.y << 16);
+        const uint32_t rows = (uint32_t)__builtin_amdgcn_readlane((int)next, 63);
+        uint32_t before = 0;  // records that start before the window
+        for (uint32_t t0 = 0; t0 < rows && base < kend; t0 += 64) {
+            uint64_t m[1];
+            window_marks<1>(s_bits[wv], valid && first - t0 < 64u, first - t0, m);
+            const uint32_t own = wb + before + (uint32_t)__popcll(m[0] & lanemask_le()) - 1u;
+            before += (uint32_t)__popcll(m[0]);
+            const uint32_t t = t0 + lane;
+            uint32_t n = 0, tile = 0, rid = 0, own_next = 0, own_end = 0;
+            if (t < rows) {
+                const EmitMeta md = s_meta[own];
+                const uint4 o = s_own[own];
+                rid = o.x;
+                own_next = o.z;
+                own_end = o.w;
+                const uint32_t r = t - o.y;
+                uint2 fc;
+                if (md.ty0 == 0xffffffffu) fc = make_uint2(md.tx & 0xffffu, md.tx >> 16);
+                else fc = support_row(support_rows(s_rows[own]), md.ty0 + r, tws, ths);
+                n = fc.y;
+                tile = md.tile + r * md.tiles_x + fc.x;
             }
-            __syncthreads();
-            // exclusive prefix of the row counts over the whole table
-            uint32_t c[EM_ROWS_PT];
-            uint32_t csum = 0;
-#pragma unroll
-            for (int q = 0; q < EM_ROWS_PT; q++) {
-                const uint32_t t = threadIdx.x * EM_ROWS_PT + q;
-                c[q] = t < total_rows ? s_row[t] >> 16 : 0u;
-                csum += c[q];
-            }
-            uint32_t all;
-            uint32_t pre = block_excl_scan(csum, ws, all);
-#pragma unroll
-            for (int q = 0; q < EM_ROWS_PT; q++) {
-                const uint32_t t = threadIdx.x * EM_ROWS_PT + q;
-                if (t < total_rows) s_rpre[t] = pre;
-                pre += c[q];
-            }
-            if (threadIdx.x == 0) s_rpre[total_rows] = all;
-        }
-        __syncthreads();
-        const uint32_t kb = k0 + threadIdx.x * EM_RUN;
-        if (kb >= k1) continue;
-        uint32_t tk[EM_RUN], tr[EM_RUN];
-        const int n = (int)min<uint32_t>(EM_RUN, k1 - kb);
-        if (staged) {
-            uint32_t j = last_le(s_off, nrec, kb);
-            uint32_t jc = 0xffffffffu, r = 0, base = 0, t0 = 0, t1 = 0, tx0 = 0, nx = 1, tb = 0, tiles_x = 0;
-#pragma unroll
-            for (int q = 0; q < EM_RUN; q++) {
-                if (q >= n) break;
-                const uint32_t kq = kb + q;
-                while (j + 1 < nrec && kq >= s_off[j + 1]) j++;
-                if (j != jc) {
-                    jc = j;
-                    r = s_rid[j];
-                    tx0 = s_tx[j] & 0xffffu;
-                    nx = s_tx[j] >> 16;
-                    tb = s_tbase[j];
-                    tiles_x = s_tpr[j];
-                    t0 = s_roff[j];
-                    t1 = s_roff[j + 1];
-                    base = s_rpre[t0];
+            const uint32_t upto = wave_incl_scan(n), pos = base + upto - n;
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+            // a record's rows have to end where the next record's pairs begin
+            if (t < rows && t + 1 == own_next && pos + n != own_end) atomicOr(flags, FLAG_BIN_MISMATCH);
+            const uint64_t some = __ballot(n > 0u);
+            if (n > 0u) s_run[wb + (uint32_t)__popcll(some & lanemask_lt())] = make_uint4(pos, tile, rid, 0u);
+            const uint32_t p1 = min(base + total, kend);
+            for (uint32_t p0 = max(base, kbeg); p0 < p1; p0 += 128) {
+                // the rows that start in the window, at its second pair or later
+                const uint32_t at = pos - p0;
+                uint64_t mk[2];
+                window_marks<2>(s_bits[wv], n > 0u && pos > p0 && at < 128u, at, mk);
+                const uint32_t started = (uint32_t)__popcll(__ballot(n > 0u && pos <= p0));
+                const uint32_t c0 = wb + started - 1u + (uint32_t)__popcll(mk[0] & lanemask_le());
+                const uint32_t c1 = wb + started - 1u + (uint32_t)__popcll(mk[0]) + (uint32_t)__popcll(mk[1] & lanemask_le());
+                const uint32_t p = p0 + lane, q = p + 64;
+                if (p < p1) {
+                    const uint4 run = s_run[c0];
+                    tile_key[p] = run.y + (p - run.x);
+                    inst_rec[p] = run.z;
                 }
-                const uint32_t li = kq - s_off[j];
-                uint32_t tile;
-                if (t0 == t1) {  // every tile of the rectangle
-                    tile = tb + (li / nx) * tiles_x + tx0 + li % nx;
-                } else if (s_rpre[t1] == base) {
-                    // a support that meets no tile still owns one pair, its
-                    // box's first tile; anything else is a counting mismatch
-                    if (li != 0) atomicOr(flags, FLAG_BIN_MISMATCH);
-                    tile = tb + tx0;
-                } else {
-                    // the last row whose pairs start at or before li (empty
-                    // rows share the next row's start, so it is not empty)
-                    uint32_t a = t0, b = t1 - 1;
-                    while (a < b) {
-                        const uint32_t m = a + (b - a + 1) / 2;
-                        if (s_rpre[m] - base <= li) a = m;
-                        else b = m - 1;
-                    }
-                    const uint32_t row = s_row[a];
-                    const uint32_t col = (row & 0xffffu) + (li - (s_rpre[a] - base));
-                    if (li - (s_rpre[a] - base) >= (row >> 16)) atomicOr(flags, FLAG_BIN_MISMATCH);
-                    tile = tb + (a - t0) * tiles_x + col;
+                if (q < p1) {
+                    const uint4 run = s_run[c1];
+                    tile_key[q] = run.y + (q - run.x);
+                    inst_rec[q] = run.z;
                 }
-                tk[q] = tile;
-                tr[q] = r;
             }
-        } else {
-            uint32_t j = last_le(s_off, nrec, kb);
-            PairCursor c;
-            cursor_open(c, rec, views, order[lo + j], kb - s_off[j], tws, ths, log2_amin, flags);
-#pragma unroll
-            for (int q = 0; q < EM_RUN; q++) {
-                if (q >= n) break;
-                if (q > 0) {
-                    if (j + 1 < nrec && kb + q >= s_off[j + 1]) {
-                        j++;
-                        cursor_open(c, rec, views, order[lo + j], 0, tws, ths, log2_amin, flags);
-                    } else {
-                        cursor_next(c, tws, ths);
-                    }
-                }
-                tk[q] = cursor_tile(c);
-                tr[q] = c.r;
-            }
-        }
-        if (n == EM_RUN) {
-#pragma unroll
-            for (int q = 0; q < EM_RUN; q += 4) {
-                *reinterpret_cast<uint4*>(tile_key + kb + q) = make_uint4(tk[q], tk[q + 1], tk[q + 2], tk[q + 3]);
-                *reinterpret_cast<uint4*>(inst_rec + kb + q) = make_uint4(tr[q], tr[q + 1], tr[q + 2], tr[q + 3]);
-            }
-        } else {
-            for (int q = 0; q < n; q++) {
-                tile_key[kb + q] = tk[q];
-                inst_rec[kb + q] = tr[q];
-            }
+            base += total;
         }
     }
 }
@@ -3617,7 +3471,7 @@ void emit_instances(const uint32_t* order, const uint32_t* R_dev, uint32_t rec_c
                     Records rec, const ViewDev* views, const uint32_t* inst_off, int tw, int th, SetDev st,
                     uint32_t inst_cap, uint32_t* tile_key, uint32_t* inst_rec, uint2* ranges, uint32_t tiles_cap,
                     uint32_t* flags, hipStream_t s) {
-    unsigned grid = grid_for(std::max<uint32_t>(inst_cap, 1), EM_ITEMS, 16384);
+    const unsigned grid = grid_for(std::max<uint32_t>(inst_cap, 1), EM_WAVES * EM_RUN, EM_BLOCKS);
     k_emit_instances<<<grid, EM_THREADS, 0, s>>>(order, R_dev, rec_cap, K_dev, rec, views, inst_off, ilog2(tw),
                                                  ilog2(th), st.log2_amin, inst_cap, tile_key, inst_rec, ranges,
                                                  tiles_cap, flags);
