@@ -487,22 +487,14 @@ rtg_status enqueue_project(rtg_frame* f, bool eager, hipStream_t s) {
     }
     project_emit(gd, views, hdr, f->views_cap, sd, f->st.tile_w, f->st.tile_h, f->mask.as<uint32_t>(),
                  f->cnt.as<uint32_t>(), f->rec_off.as<uint32_t>(), f->ctr(C_REC), f->rec_cap, f->records(),
-                 f->skey.as<uint32_t>(), f->order.as<uint32_t>(), !f->scoring, f->chunk_g.as<uint32_t>(),
+                 f->skey.as<uint32_t>(), !f->scoring, f->chunk_g.as<uint32_t>(),
                  f->ctr(C_FLAGS), s);
     return check_launch("projection emit");
 }
 
-// Digit widths of the two sorts (measured): the 32-bit depth keys in 4 passes
-// of 8 bits; tile keys (ceil(log2 tiles) bits) in passes of up to 8 bits too.
-// 11-bit tile digits (one pass up to 2048 tiles) were as fast on a 640x480
-// frame and 1-2% slower on batches of views: their scatter spreads a block's
-// pairs over 2048 buckets, so more writes are partial cache lines.
-constexpr int DEPTH_SORT_DIGIT = 8;
-constexpr int TILE_SORT_DIGIT = 8;
-
 rtg_status enqueue_bin(rtg_frame* f, bool eager, hipStream_t s) {
     const uint32_t rc = std::max<uint32_t>(f->rec_cap, 1);
-    SortWs ws{f->sort_hist.as<uint32_t>(), f->scan_ws.as<uint32_t>()};
+    SortWs ws{f->sort_hist.as<uint32_t>()};
     if (eager) {
         // the histogram table must fit the larger of the two sorts; size it for the records now
         RTG_TRY(f->sort_hist.ensure(f->ctx, sizeof(uint32_t) * sort_hist_words(rc)));
@@ -510,10 +502,10 @@ rtg_status enqueue_bin(rtg_frame* f, bool eager, hipStream_t s) {
     }
     {
         Timer tm(f->ctx, 1, s);
-        // the last pass also lays the records' pair counts out in depth order
+        // the records' positions, and their pair counts laid out in depth order
         // (into inst_off), so that the scan below reads them in sequence
         f->order_in_alt = radix_sort(f->skey.as<uint32_t>(), f->order.as<uint32_t>(), f->skey2.as<uint32_t>(),
-                                     f->order2.as<uint32_t>(), f->ctr(C_REC), rc, 32, DEPTH_SORT_DIGIT, ws, s,
+                                     f->order2.as<uint32_t>(), f->ctr(C_REC), rc, 32, ws, s,
                                      f->ntiles.as<uint32_t>(), f->inst_off.as<uint32_t>());
     }
     scan_u32(f->inst_off.as<uint32_t>(), nullptr, f->inst_off.as<uint32_t>(), f->ctr(C_REC), rc, f->ctr(C_INST),
@@ -534,7 +526,7 @@ rtg_status enqueue_bin(rtg_frame* f, bool eager, hipStream_t s) {
                    f->ctr(C_FLAGS), s);
     int tbits = bits_for(std::max<uint32_t>(f->tiles_cap, 2));
     f->inst_in_alt = radix_sort(f->tkey.as<uint32_t>(), f->irec.as<uint32_t>(), f->tkey2.as<uint32_t>(),
-                                f->irec2.as<uint32_t>(), f->ctr(C_INST), kc, tbits, TILE_SORT_DIGIT, ws, s);
+                                f->irec2.as<uint32_t>(), f->ctr(C_INST), kc, tbits, ws, s);
     tile_ranges(f->sorted_tkey(), f->ctr(C_INST), kc, f->ranges.as<uint2>(), f->tiles_cap, f->ctr(C_FLAGS), s);
     tile_order(f->ranges.as<uint2>(), f->hdr.as<Header>(), f->tiles_cap, f->tile_ord_ws.as<uint32_t>(),
                f->tile_ord.as<uint32_t>(), s);

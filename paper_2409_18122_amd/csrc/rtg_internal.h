@@ -116,7 +116,7 @@ constexpr int PE_CHUNK = 256;  // records per block step of the record emission
 inline size_t pe_chunk_words(uint32_t rec_cap) { return 2 * ((size_t)rec_cap / PE_CHUNK + 2); }
 void project_emit(const GaussDev& g, const ViewDev* views, const Header* hdr, int n_views_cap,
                   SetDev st, int tw, int th, const uint32_t* mask, const uint32_t* cnt, const uint32_t* rec_off,
-                  const uint32_t* R_dev, uint32_t rec_cap, Records rec, uint32_t* sortkey, uint32_t* order,
+                  const uint32_t* R_dev, uint32_t rec_cap, Records rec, uint32_t* sortkey,
                   bool write_attr, uint32_t* chunk_g, uint32_t* flags, hipStream_t s);
 
 // Exclusive prefix sum of in[0..n) (n = min(*n_dev, cap)) into out; *total =
@@ -129,20 +129,15 @@ int scan_blocks(uint64_t cap);
 void scan_u32(const uint32_t* in, const uint32_t* gather, uint32_t* out, const uint32_t* n_dev,
               uint32_t cap, uint32_t* total, uint32_t* flags, ScanWs ws, hipStream_t s);
 
-// Stable LSD radix sort of (key, value) pairs on bits [0, nbits) of the key.
-// Result lands in (k1, v1) if the number of 8-bit passes is odd, else (k0, v0);
-// returns 1 or 0 accordingly.
+// Stable LSD radix sort of (key, value) pairs on bits [0, nbits) of the key; returns 1 if the result is in
+// (k1, v1), 0 if it is in (k0, v0).  With count, the values are the items' positions (v0 need not be filled) and
+// gout[i] = count[value at sorted position i].
 struct SortWs {
     uint32_t* hist;     // sort_hist_words(cap) entries
-    uint32_t* partial;  // scan workspace: >= 1024 + 1 entries
 };
-int sort_blocks(uint64_t cap, int db);
 size_t sort_hist_words(uint64_t cap);
-// Stable sort of (key, value) pairs on the low nbits of the keys, in passes of
-// at most max_db (<= 11) bits; returns 1 if the result is in (k1, v1).  With
-// gsrc, the last pass also writes gout[i] = gsrc[value at sorted position i].
 int radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uint32_t* n_dev,
-               uint32_t cap, int nbits, int max_db, SortWs ws, hipStream_t s, const uint32_t* gsrc = nullptr,
+               uint32_t cap, int nbits, SortWs ws, hipStream_t s, const uint32_t* count = nullptr,
                uint32_t* gout = nullptr);
 
 // Instances of the depth-ordered records: tile keys and record ids, one per

@@ -768,38 +768,31 @@ __global__ __launch_bounds__(SC_THREADS) void k_scan_down(const uint32_t* in,
 }
 
 // ------------------------------------------------------------- radix sort
-// Stable LSD sort with digits of up to 11 bits (2048 bins).  A fixed grid of
-// blocks splits the input into equal chunks; per pass: per-block digit
-// histograms (upsweep, one LDS atomic add per item into per-wave tables), the
-// offsets of every (digit, block), and a scatter in
-// which every wave ranks its items with 64-lane ballots (peers with the same
-// digit), preserving input order within the block; with 8-bit digits the
-// block then sorts its tile in LDS and writes each digit's run from
-// consecutive lanes.  Up to 128 blocks compute their offsets themselves from
-// the block-major histogram table; more blocks scan a digit-major table with
-// the multi-block scan.
-
-// 16 items per lane (a 4096-item tile per block step of 256 threads): each
-// digit's run per step is twice as long as with 8, so fewer of the scatter's
-// writes are partial cache lines (measured 3% faster on 192M pairs, 6% on
-// 40M).  Inputs of at least RS_BIG_ITEMS take blocks of 512 threads (8192-item
-// tiles, runs twice as long again); smaller ones keep 256, which gives them
-// twice as many blocks.
+// Stable LSD sort with digits of up to 8 bits.  A fixed grid of blocks splits the input into equal chunks; per
+// pass: per-block digit histograms (upsweep, one LDS atomic add per item into per-wave tables), the offsets of
+// every (digit, block), and a scatter in which every wave ranks its items with 64-lane ballots (peers with the
+// same digit), preserving input order within the block; the block then sorts its tile in LDS and writes each
+// digit's run from consecutive lanes.  Up to RS_FUSED_BLOCKS blocks add up their offsets themselves from the
+// block-major table (5.6 us for the scatter of 2 k items, launch included); for more blocks k_rs_columns scans a
+// digit-major table: 196 blocks that each read the whole table took 13.7 us, with the third launch 4.4 + 7.5.
+//
+// Items per lane and tile: 16 on large inputs (a digit's run per step is twice as long as with 8, so fewer of
+// the scatter's writes are partial cache lines: measured 3% faster on 192 M pairs, 6% on 40 M); 4 or 8 where
+// those fit RS_MAX_BLOCKS blocks, because a pass over a small input is a chain of latencies (1.0 M pairs: 16 per lane
+// 16.3 us a scatter, 8 11.3; 1.5 M: 17.9 and 12.6; 200 k: 15 and, with 4, 7.5).  Inputs of at least RS_BIG_ITEMS
+// take blocks of 512 threads (runs twice as long again); smaller ones keep 256, which gives them twice as many blocks.
 constexpr int RS_THREADS = 256;
 constexpr int RS_THREADS_BIG = 512;
 constexpr int RS_IPT = 16;
-constexpr int RS_SEG = 64 * RS_IPT;         // items per wave per tile
-constexpr int RS_TILE = RS_THREADS * RS_IPT;  // items per block per tile (256 threads)
 constexpr int RS_MAX_BLOCKS = 1024;
 constexpr uint64_t RS_BIG_ITEMS = (uint64_t)RS_MAX_BLOCKS * RS_THREADS_BIG * RS_IPT;
-constexpr int RS_FUSED_BLOCKS = 128;
-constexpr int RS_MAX_DB = 11;
+constexpr int RS_FUSED_BLOCKS = 32;
+constexpr int RS_DB = 8;
 
-template <int DB>
 __device__ __forceinline__ uint64_t digit_peers(uint32_t d, uint64_t valid) {
     uint64_t m = valid;
 #pragma unroll
-    for (int b = 0; b < DB; b++) {
+    for (int b = 0; b < RS_DB; b++) {
         uint32_t bit = (d >> b) & 1u;
         uint64_t bal = __ballot(bit);
         m &= bit ? bal : ~bal;
@@ -816,20 +809,33 @@ __device__ __forceinline__ void rs_chunk(uint32_t n, uint32_t& begin, uint32_t& 
     end = (uint32_t)min<uint64_t>(b + per, n);
 }
 
-// Digit of this pass: `bits` (<= DB) bits from `shift`.
-// hist layout: digit-major [d][block] when block_major == 0 (scanned as a
-// whole), block-major [block][d] otherwise (read directly by the scatter).
-template <int DB, int NT>
+// Exclusive sum over the NT threads of a block.
+template <int NT>
+__device__ __forceinline__ uint32_t rs_block_excl(uint32_t x, uint32_t* ws) {
+    const uint32_t inc = wave_incl_scan(x);
+    const int wv = threadIdx.x >> 6;
+    if (lane_id() == 63) ws[wv] = inc;
+    __syncthreads();
+    uint32_t base = inc - x;
+#pragma unroll
+    for (int w = 0; w < NT / 64; w++)
+        if (w < wv) base += ws[w];
+    __syncthreads();
+    return base;
+}
+
+// Digit of this pass: `bits` (<= RS_DB) bits from `shift`.
+// hist layout: block-major [block][d] when block_major, digit-major [d][block] otherwise.
+template <int NT, int IPT>
 __global__ __launch_bounds__(NT) void k_rs_upsweep(const uint32_t* __restrict__ keys,
-                                                           const uint32_t* __restrict__ n_dev, uint32_t cap,
-                                                           int shift, int bits, uint32_t* __restrict__ hist,
-                                                           int block_major) {
-    constexpr int NB = 1 << DB;
-    constexpr int WAVES = NT / 64, TILE = NT * RS_IPT;
+                                                   const uint32_t* __restrict__ n_dev, uint32_t cap, int shift,
+                                                   int bits, uint32_t* __restrict__ hist, int block_major) {
+    constexpr int NB = 1 << RS_DB;
+    constexpr int WAVES = NT / 64, TILE = NT * IPT;
     // each wave counts into CP copies of its table (lane l into copy l % CP),
     // so that a skewed digit (few tiles or views dominating a pass) does not
     // serialise a whole wave's atomics on one LDS word
-    constexpr int CP = DB <= 8 ? 4 : 1;
+    constexpr int CP = 4;
     __shared__ uint32_t h[WAVES * CP][NB];
     const int tid = threadIdx.x, wv = tid >> 6;
     const int cp = wv * CP + (int)(lane_id() % CP);
@@ -839,18 +845,18 @@ __global__ __launch_bounds__(NT) void k_rs_upsweep(const uint32_t* __restrict__ 
     uint32_t n = min(*n_dev, cap);
     uint32_t begin, end;
     rs_chunk<TILE>(n, begin, end);
-    // the scatter's tiling: RS_IPT coalesced loads per lane in flight, then
-    // their RS_IPT additions to the wave's table
+    // the scatter's tiling: IPT coalesced loads per lane in flight, then
+    // their IPT additions to the wave's table
     for (uint32_t t0 = begin; t0 < end; t0 += TILE) {
-        const uint32_t seg = t0 + wv * RS_SEG;
-        uint32_t k[RS_IPT];
+        const uint32_t seg = t0 + wv * (64 * IPT);
+        uint32_t k[IPT];
 #pragma unroll
-        for (int j = 0; j < RS_IPT; j++) {
+        for (int j = 0; j < IPT; j++) {
             const uint32_t idx = seg + j * 64 + lane_id();
             k[j] = idx < end ? keys[idx] : 0u;
         }
 #pragma unroll
-        for (int j = 0; j < RS_IPT; j++) {
+        for (int j = 0; j < IPT; j++) {
             const uint32_t idx = seg + j * 64 + lane_id();
             if (idx < end) atomicAdd(&h[cp][(k[j] >> shift) & mask], 1u);
         }
@@ -867,198 +873,165 @@ __global__ __launch_bounds__(NT) void k_rs_upsweep(const uint32_t* __restrict__ 
     }
 }
 
-// STAGE: a tile's items are first placed at their block-local sorted positions
-// in LDS and written out in that order, so that consecutive lanes write the
-// consecutive addresses of a digit's run; otherwise each item is written from
-// where its wave ranked it.
-template <int DB, bool STAGE, int NT>
-__global__ __launch_bounds__(NT) void k_rs_scatter(const uint32_t* __restrict__ kin,
-                                                           const uint32_t* __restrict__ vin,
-                                                           uint32_t* __restrict__ kout,
-                                                           uint32_t* __restrict__ vout,
-                                                           const uint32_t* __restrict__ n_dev, uint32_t cap,
-                                                           int shift, int bits, const uint32_t* __restrict__ hist,
-                                                           int block_major, const uint32_t* __restrict__ gsrc,
-                                                           uint32_t* __restrict__ gout) {
-    constexpr int NB = 1 << DB;
-    constexpr int WAVES = NT / 64, TILE = NT * RS_IPT;
-    constexpr int DPT = NB / NT > 0 ? NB / NT : 1;  // digits per thread
+// Exclusive sums, in place, of each digit's nb <= RS_MAX_BLOCKS block counts (a block per digit), and the digit's total.
+__global__ __launch_bounds__(256) void k_rs_columns(uint32_t* __restrict__ hist, int nb, uint32_t* __restrict__ totals) {
+    static_assert(RS_MAX_BLOCKS == 4 * 256, "four blocks' counts per thread");
+    __shared__ uint32_t ws[4];
+    uint32_t* col = hist + (uint64_t)blockIdx.x * nb;
+    const int i0 = 4 * (int)threadIdx.x;
+    uint32_t c[4], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        c[j] = i0 + j < nb ? col[i0 + j] : 0u;
+        sum += c[j];
+    }
+    uint32_t run = rs_block_excl<256>(sum, ws);
+    if (threadIdx.x == 255) totals[blockIdx.x] = run + sum;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        if (i0 + j < nb) col[i0 + j] = run;
+        run += c[j];
+    }
+}
+
+// Values of a sort that orders the items' positions and lays out their counts in that order: the first pass makes
+// them (no values are read), as the position, with the count in the spare bits above `pb` position bits (the largest
+// value there stands for a count that does not fit); the last pass takes them apart, and looks up the
+// few counts that did not fit.  pb = 32: no spare bits, every count is looked up.
+struct RsCounts {
+    const uint32_t* count;  // null: plain values
+    int pb;
+};
+
+template <int NT, int IPT>
+__global__ __launch_bounds__(NT, 4) void k_rs_scatter(const uint32_t* __restrict__ kin,
+                                                   const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
+                                                   uint32_t* __restrict__ vout, const uint32_t* __restrict__ n_dev,
+                                                   uint32_t cap, int shift, int bits,
+                                                   const uint32_t* __restrict__ hist,
+                                                   const uint32_t* __restrict__ totals, RsCounts rc,
+                                                   uint32_t* __restrict__ gout) {
+    constexpr int NB = 1 << RS_DB;
+    constexpr int WAVES = NT / 64, TILE = NT * IPT;
+    static_assert(NB <= NT && TILE >= 4 * NB, "a thread per digit; the staging buffer holds four partial tables");
     __shared__ uint32_t wh[WAVES][NB];
-    __shared__ uint32_t bbase[NB];
+    __shared__ uint32_t bbase[NB], lst[NB], tcnt[NB];
     __shared__ uint32_t ws[WAVES];
-    constexpr int SB = STAGE ? NB : 1, ST = STAGE ? TILE : 1;
-    __shared__ uint32_t lst[SB], tcnt[SB];
-    __shared__ uint32_t s_k[ST], s_v[ST];
+    __shared__ uint32_t s_k[TILE], s_v[TILE];  // the tile in sorted order
     const int tid = threadIdx.x, wv = tid >> 6;
     const uint32_t lane = lane_id();
     const uint32_t mask = (1u << bits) - 1u;
     uint32_t n = min(*n_dev, cap);
     uint32_t begin, end;
     rs_chunk<TILE>(n, begin, end);
-    if (block_major) {
-        // offset of digit d for this block = count of smaller digits in all
-        // blocks + count of digit d in earlier blocks; thread tid owns the
-        // DPT consecutive digits from tid * DPT
-        uint32_t tot[DPT], pre[DPT];
+    if (begin >= end) return;
+    const uint32_t sat = rc.pb < 32 ? (1u << (32 - rc.pb)) - 1u : 0u;
+    uint32_t k[IPT], v[IPT];
+    auto load = [&](uint32_t seg) {
 #pragma unroll
-        for (int j = 0; j < DPT; j++) tot[j] = pre[j] = 0;
-        if (tid * DPT < NB) {
-            // independent loads, unrolled so that many are in flight
-#pragma unroll(DPT == 1 ? 32 : 8)
-            for (uint32_t b = 0; b < gridDim.x; b++) {
-                uint32_t c[DPT];
-                if constexpr (DPT % 4 == 0) {
-#pragma unroll
-                    for (int j = 0; j < DPT; j += 4) {
-                        const uint4 q = *reinterpret_cast<const uint4*>(hist + (uint64_t)b * NB + tid * DPT + j);
-                        c[j] = q.x;
-                        c[j + 1] = q.y;
-                        c[j + 2] = q.z;
-                        c[j + 3] = q.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < DPT; j++) c[j] = hist[(uint64_t)b * NB + tid * DPT + j];
-                }
-                const bool earlier = b < blockIdx.x;
-#pragma unroll
-                for (int j = 0; j < DPT; j++) {
-                    tot[j] += c[j];
-                    pre[j] += earlier ? c[j] : 0u;
-                }
-            }
+        for (int j = 0; j < IPT; j++) {
+            const uint32_t idx = seg + j * 64 + lane;
+            const bool valid = idx < end;
+            k[j] = valid ? kin[idx] : 0u;
+            if (vin) v[j] = valid ? vin[idx] : 0u;
+            else v[j] = valid && rc.pb < 32 ? idx | min(rc.count[idx], sat) << rc.pb : idx;
         }
-        uint32_t mine = 0;
-#pragma unroll
-        for (int j = 0; j < DPT; j++) mine += tot[j];
-        const uint32_t inc = wave_incl_scan(mine);
-        if (lane == 63) ws[wv] = inc;
+    };
+    load(begin + wv * (64 * IPT));  // in flight while the offsets are formed
+    // offset of digit d for this block = count of smaller digits in all blocks + count of digit d in earlier blocks
+    if (totals) {
+        const uint32_t base = rs_block_excl<NT>(tid < NB ? totals[tid] : 0u, ws);
+        if (tid < NB) bbase[tid] = base + hist[(uint64_t)tid * gridDim.x + blockIdx.x];
+    } else if constexpr (NT == NB) {
+        // each wave adds up every fourth block's counts, four digits a lane, many loads in flight
+        uint4 tot = make_uint4(0u, 0u, 0u, 0u), pre = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll 16
+        for (uint32_t b = wv; b < gridDim.x; b += WAVES) {
+            const uint4 c = *reinterpret_cast<const uint4*>(hist + (uint64_t)b * NB + 4 * lane);
+            const uint32_t earlier = b < blockIdx.x ? 0xffffffffu : 0u;
+            tot.x += c.x;
+            tot.y += c.y;
+            tot.z += c.z;
+            tot.w += c.w;
+            pre.x += c.x & earlier;
+            pre.y += c.y & earlier;
+            pre.z += c.z & earlier;
+            pre.w += c.w & earlier;
+        }
+        reinterpret_cast<uint4*>(&wh[wv][0])[lane] = tot;
+        reinterpret_cast<uint4*>(s_k + wv * NB)[lane] = pre;
         __syncthreads();
-        uint32_t base = inc - mine;
+        uint32_t t = 0, q = 0;
 #pragma unroll
-        for (int w = 0; w < WAVES; w++)
-            if (w < wv) base += ws[w];
-        if (tid * DPT < NB) {
-#pragma unroll
-            for (int j = 0; j < DPT; j++) {
-                bbase[tid * DPT + j] = base + pre[j];
-                base += tot[j];
-            }
+        for (int w = 0; w < WAVES; w++) {
+            t += wh[w][tid];
+            q += s_k[w * NB + tid];
         }
-    } else {
-        for (int d = tid; d < NB; d += NT) bbase[d] = hist[(uint64_t)d * gridDim.x + blockIdx.x];
+        bbase[tid] = rs_block_excl<NT>(t, ws) + q;
     }
     for (uint32_t t0 = begin; t0 < end; t0 += TILE) {
+        __syncthreads();
         for (int i = tid; i < WAVES * NB; i += NT) (&wh[0][0])[i] = 0;
         __syncthreads();
-        uint32_t seg = t0 + wv * RS_SEG;
-        uint32_t k[RS_IPT], v[RS_IPT], pos[RS_IPT];
+        const uint32_t seg = t0 + wv * (64 * IPT);
+        uint32_t pos[IPT];
+        if (t0 != begin) load(seg);
 #pragma unroll
-        for (int j = 0; j < RS_IPT; j++) {
-            uint32_t idx = seg + j * 64 + lane;
-            bool valid = idx < end;
-            k[j] = valid ? kin[idx] : 0u;
-            v[j] = valid ? vin[idx] : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < RS_IPT; j++) {
+        for (int j = 0; j < IPT; j++) {
             uint32_t idx = seg + j * 64 + lane;
             bool valid = idx < end;
             uint32_t d = (k[j] >> shift) & mask;
             uint64_t vm = __ballot(valid);
-            uint64_t m = digit_peers<DB>(d, vm);
+            uint64_t m = digit_peers(d, vm);
             uint32_t before = valid ? wh[wv][d] : 0u;
             pos[j] = before + (uint32_t)__popcll(m & lanemask_lt());
             if (valid && lane == (uint32_t)__builtin_ctzll(m)) wh[wv][d] = before + (uint32_t)__popcll(m);
         }
         __syncthreads();
-        if constexpr (!STAGE) {
-            for (int d = tid; d < NB; d += NT) {
-                uint32_t run = bbase[d];
+        // per digit: the waves' offsets inside the tile's run of the digit, and the run's length and start
+        uint32_t run = 0;
+        if (tid < NB) {
 #pragma unroll
-                for (int w = 0; w < WAVES; w++) {
-                    uint32_t c = wh[w][d];
-                    wh[w][d] = run;
-                    run += c;
-                }
-                bbase[d] = run;
+            for (int w = 0; w < WAVES; w++) {
+                uint32_t c = wh[w][tid];
+                wh[w][tid] = run;
+                run += c;
             }
-            __syncthreads();
+            tcnt[tid] = run;
+        }
+        const uint32_t start = rs_block_excl<NT>(run, ws);
+        if (tid < NB) lst[tid] = start;
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < RS_IPT; j++) {
-                uint32_t idx = seg + j * 64 + lane;
-                if (idx < end) {
-                    uint32_t d = (k[j] >> shift) & mask;
-                    uint32_t dst = wh[wv][d] + pos[j];
-                    kout[dst] = k[j];
-                    vout[dst] = v[j];
-                    if (gsrc) gout[dst] = gsrc[v[j]];
-                }
+        for (int j = 0; j < IPT; j++) {
+            uint32_t idx = seg + j * 64 + lane;
+            if (idx < end) {
+                uint32_t d = (k[j] >> shift) & mask;
+                const uint32_t lp = lst[d] + wh[wv][d] + pos[j];
+                s_k[lp] = k[j];
+                s_v[lp] = v[j];
             }
-        } else {
-            // per digit: the waves' offsets inside the tile's run of the digit, and the run length
-            for (int d = tid; d < NB; d += NT) {
-                uint32_t run = 0;
-#pragma unroll
-                for (int w = 0; w < WAVES; w++) {
-                    uint32_t c = wh[w][d];
-                    wh[w][d] = run;
-                    run += c;
-                }
-                tcnt[d] = run;
-            }
-            __syncthreads();
-            // lst[d]: start of digit d's run in the tile's sorted order (thread tid owns
-            // the DPT consecutive digits from tid * DPT)
-            {
-                uint32_t c[DPT];
-                uint32_t mine = 0;
-#pragma unroll
-                for (int j = 0; j < DPT; j++) {
-                    c[j] = tid * DPT < NB ? tcnt[tid * DPT + j] : 0u;
-                    mine += c[j];
-                }
-                const uint32_t inc = wave_incl_scan(mine);
-                if (lane == 63) ws[wv] = inc;
-                __syncthreads();
-                uint32_t base = inc - mine;
-#pragma unroll
-                for (int w = 0; w < WAVES; w++)
-                    if (w < wv) base += ws[w];
-                if (tid * DPT < NB) {
-#pragma unroll
-                    for (int j = 0; j < DPT; j++) {
-                        lst[tid * DPT + j] = base;
-                        base += c[j];
-                    }
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < RS_IPT; j++) {
-                uint32_t idx = seg + j * 64 + lane;
-                if (idx < end) {
-                    uint32_t d = (k[j] >> shift) & mask;
-                    uint32_t lp = lst[d] + wh[wv][d] + pos[j];
-                    s_k[lp] = k[j];
-                    s_v[lp] = v[j];
-                }
-            }
-            __syncthreads();
-            const uint32_t tn = min<uint32_t>(TILE, end - t0);
-            for (uint32_t i = tid; i < tn; i += NT) {
-                const uint32_t kk = s_k[i];
-                const uint32_t d = (kk >> shift) & mask;
-                const uint32_t dst = bbase[d] + (i - lst[d]);
-                const uint32_t vv = s_v[i];
-                kout[dst] = kk;
-                vout[dst] = vv;
-                if (gsrc) gout[dst] = gsrc[vv];
-            }
-            __syncthreads();
-            for (int d = tid; d < NB; d += NT) bbase[d] += tcnt[d];
         }
         __syncthreads();
+        const uint32_t tn = min<uint32_t>(TILE, end - t0);
+        for (uint32_t i = tid; i < tn; i += NT) {
+            const uint32_t kk = s_k[i];
+            const uint32_t d = (kk >> shift) & mask;
+            const uint32_t dst = bbase[d] + (i - lst[d]);
+            uint32_t vv = s_v[i];
+            kout[dst] = kk;
+            if (gout) {
+                uint32_t c = sat;
+                if (rc.pb < 32) {
+                    c = vv >> rc.pb;
+                    vv &= (1u << rc.pb) - 1u;
+                }
+                gout[dst] = c == sat ? rc.count[vv] : c;
+            }
+            vout[dst] = vv;
+        }
+        __syncthreads();
+        if (tid < NB) bbase[tid] += tcnt[tid];
     }
 }
 
@@ -1195,8 +1168,7 @@ __global__ __launch_bounds__(PE_THREADS, 3) void k_project_emit(GaussDev g, cons
                                                              const uint32_t* __restrict__ mask,
                                                              const uint32_t* __restrict__ rec_off,
                                                              const uint32_t* __restrict__ R_dev, uint32_t rec_cap,
-                                                             Records rec, uint32_t* __restrict__ sortkey,
-                                                             uint32_t* __restrict__ order, int write_attr,
+                                                             Records rec, uint32_t* __restrict__ sortkey, int write_attr,
                                                              const uint32_t* __restrict__ chunk_g,
                                                              uint32_t* __restrict__ flags) {
     __shared__ uint32_t s_off[PE_LDS];
@@ -1295,7 +1267,6 @@ __global__ __launch_bounds__(PE_THREADS, 3) void k_project_emit(GaussDev g, cons
             e.view = (uint32_t)v;
             e.unc = __float_as_uint(g.uncert ? g.uncert[gi] : 0.0f);
             e.gid = i;
-            order[pos] = pos;
         }
         // the pairs of a record, the tiles its support meets: the wave takes the rows of its records 64 at a time
         // (integer counts, so their sum does not depend on the split)
@@ -3376,14 +3347,14 @@ static int ilog2(int x) {
 
 void project_emit(const GaussDev& g, const ViewDev* views, const Header* hdr, int n_views_cap, SetDev st,
                   int tw, int th, const uint32_t* mask, const uint32_t* cnt, const uint32_t* rec_off,
-                  const uint32_t* R_dev, uint32_t rec_cap, Records rec, uint32_t* sortkey, uint32_t* order,
+                  const uint32_t* R_dev, uint32_t rec_cap, Records rec, uint32_t* sortkey,
                   bool write_attr, uint32_t* chunk_g, uint32_t* flags, hipStream_t s) {
     (void)hdr;
     if (g.n == 0 || rec_cap == 0) return;
     int words = (n_views_cap + 31) / 32;
     k_chunk_owners<<<grid_for(g.n, 256, 16384), 256, 0, s>>>(cnt, rec_off, g.n, R_dev, rec_cap, chunk_g);
     k_project_emit<<<grid_for(rec_cap, PE_THREADS, 32768), PE_THREADS, 0, s>>>(
-        g, views, words, st, ilog2(tw), ilog2(th), mask, rec_off, R_dev, rec_cap, rec, sortkey, order,
+        g, views, words, st, ilog2(tw), ilog2(th), mask, rec_off, R_dev, rec_cap, rec, sortkey,
         write_attr ? 1 : 0, chunk_g, flags);
 }
 
@@ -3401,65 +3372,70 @@ void scan_u32(const uint32_t* in, const uint32_t* gather, uint32_t* out, const u
     k_scan_down<<<nb, SC_THREADS, 0, s>>>(in, gather, out, n_dev, cap, ws.partial, total, flags);
 }
 
-// Grid of a pass with digits of db bits: one block per tile of input, up to
-// RS_MAX_BLOCKS.  Wide digits make the per-block offset computation cost
-// 2^db x blocks loads per block, so for them inputs of up to
-// RS_FUSED_BLOCKS * 8 tiles use at most RS_FUSED_BLOCKS blocks, each walking
-// several tiles, and need no separate offset scan.
-static int sort_blocks_tile(uint64_t cap, int db, int tile) {
-    uint64_t t = (cap + tile - 1) / tile;
-    if (t < 1) t = 1;
-    if (db > 8 && t <= (uint64_t)RS_FUSED_BLOCKS * 8) return (int)std::min<uint64_t>(t, RS_FUSED_BLOCKS);
-    return (int)std::min<uint64_t>(t, RS_MAX_BLOCKS);
+// The form of a pass over at most cap items: items per lane, threads and blocks (one per tile, up to RS_MAX_BLOCKS).
+struct RsForm {
+    int ipt, threads, blocks;
+};
+
+static RsForm sort_form(uint64_t cap) {
+    const uint64_t small = (uint64_t)RS_MAX_BLOCKS * RS_THREADS;
+    RsForm f;
+    f.ipt = cap <= 4 * small ? 4 : cap <= 8 * small ? 8 : RS_IPT;
+    f.threads = cap >= RS_BIG_ITEMS ? RS_THREADS_BIG : RS_THREADS;
+    const uint64_t tile = (uint64_t)f.ipt * f.threads;
+    f.blocks = (int)std::min<uint64_t>(std::max<uint64_t>((cap + tile - 1) / tile, 1), RS_MAX_BLOCKS);
+    return f;
 }
 
-// The block count of the 256-thread form (at least that of the 512-thread one).
-int sort_blocks(uint64_t cap, int db) { return sort_blocks_tile(cap, db, RS_TILE); }
-
+// Histograms (a table per block) and the digits' totals, for every input of up to cap items: the smallest tile
+// bounds the blocks of any.
 size_t sort_hist_words(uint64_t cap) {
-    return (size_t)(1u << RS_MAX_DB) * (size_t)std::max(sort_blocks(cap, 8), sort_blocks(cap, RS_MAX_DB));
+    const uint64_t tile = 4 * RS_THREADS;
+    return ((size_t)1 << RS_DB) * (size_t)(std::min<uint64_t>((cap + tile - 1) / tile + 1, RS_MAX_BLOCKS) + 1);
 }
 
-template <int DB, int NT>
-static void rs_pass(uint32_t* ki, uint32_t* vi, uint32_t* ko, uint32_t* vo, const uint32_t* n_dev, uint32_t cap,
-                    int shift, int bits, SortWs ws, const uint32_t* gsrc, uint32_t* gout, hipStream_t s) {
-    const int nb = sort_blocks_tile(cap, DB, NT * RS_IPT);
-    const int fused = nb <= RS_FUSED_BLOCKS;
-    k_rs_upsweep<DB, NT><<<nb, NT, 0, s>>>(ki, n_dev, cap, shift, bits, ws.hist, fused);
+template <int NT, int IPT>
+static void rs_pass(uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint32_t* vo, const uint32_t* n_dev, uint32_t cap,
+                    int shift, int bits, int nb, SortWs ws, RsCounts rc, uint32_t* gout, hipStream_t s) {
+    const bool fused = NT == RS_THREADS && nb <= RS_FUSED_BLOCKS;
+    k_rs_upsweep<NT, IPT><<<nb, NT, 0, s>>>(ki, n_dev, cap, shift, bits, ws.hist, fused);
+    uint32_t* totals = nullptr;
     if (!fused) {
-        // table of 2^DB * nb counts, a size known here: the multi-block scan,
-        // in place
-        const uint32_t count = (uint32_t)((1u << DB) * nb);
-        int sb = scan_blocks(count);
-        k_scan_reduce<<<sb, SC_THREADS, 0, s>>>(ws.hist, nullptr, nullptr, count, ws.partial);
-        k_scan_down<<<sb, SC_THREADS, 0, s>>>(ws.hist, nullptr, ws.hist, nullptr, count, ws.partial, nullptr,
-                                              nullptr);
+        totals = ws.hist + ((size_t)nb << RS_DB);
+        k_rs_columns<<<1 << RS_DB, 256, 0, s>>>(ws.hist, nb, totals);
     }
-    // 8-bit passes stage their scatter in LDS; the 11-bit one writes directly (its
-    // per-wave tables already take 32 KB of LDS)
-    k_rs_scatter<DB, DB == 8, NT><<<nb, NT, 0, s>>>(ki, vi, ko, vo, n_dev, cap, shift, bits, ws.hist, fused,
-                                                     gsrc, gout);
+    k_rs_scatter<NT, IPT><<<nb, NT, 0, s>>>(ki, vi, ko, vo, n_dev, cap, shift, bits, ws.hist, totals, rc, gout);
 }
 
-// The nbits are split into the fewest passes of at most max_db bits, as
-// evenly as possible; passes of up to 8 bits use 256 bins.
+// The nbits are split into the fewest passes of at most RS_DB bits, as evenly as possible.  Two 9-bit passes in place
+// of three over 192 M pairs took 1,220 us each (the 8-bit ones 700 to 930): twice the buckets, half the runs.
 int radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uint32_t* n_dev, uint32_t cap,
-               int nbits, int max_db, SortWs ws, hipStream_t s, const uint32_t* gsrc, uint32_t* gout) {
-    max_db = std::max(1, std::min(max_db, RS_MAX_DB));
-    const int passes = std::max(1, (nbits + max_db - 1) / max_db);
+               int nbits, SortWs ws, hipStream_t s, const uint32_t* count, uint32_t* gout) {
+    const RsForm f = sort_form(cap);
+    const int passes = std::max(1, (nbits + RS_DB - 1) / RS_DB);
+    RsCounts rc{count, 32};
+    if (count) {
+        int pb = 1;
+        while (((uint64_t)1 << pb) < cap) pb++;
+        if (pb <= 29) rc.pb = pb;  // at least three bits for the counts
+    }
     uint32_t *ki = k0, *vi = v0, *ko = k1, *vo = v1;
     int shift = 0;
     for (int p = 0; p < passes; p++) {
-        const int bits = nbits / passes + (p < nbits % passes ? 1 : 0);
-        const bool last = p + 1 == passes;
-        const uint32_t* gs = last ? gsrc : nullptr;
-        uint32_t* go = last ? gout : nullptr;
-        if (bits <= 8 && cap >= RS_BIG_ITEMS)
-            rs_pass<8, RS_THREADS_BIG>(ki, vi, ko, vo, n_dev, cap, shift, std::max(bits, 1), ws, gs, go, s);
-        else if (bits <= 8)
-            rs_pass<8, RS_THREADS>(ki, vi, ko, vo, n_dev, cap, shift, std::max(bits, 1), ws, gs, go, s);
-        else
-            rs_pass<RS_MAX_DB, RS_THREADS>(ki, vi, ko, vo, n_dev, cap, shift, bits, ws, gs, go, s);
+        const int bits = std::max(nbits / passes + (p < nbits % passes ? 1 : 0), 1);
+        const uint32_t* vin = count && p == 0 ? nullptr : vi;
+        uint32_t* go = p + 1 == passes ? gout : nullptr;
+        auto pass = [&](auto nt, auto ipt) {
+            rs_pass<decltype(nt)::value, decltype(ipt)::value>(ki, vin, ko, vo, n_dev, cap, shift, bits, f.blocks, ws, rc,
+                                                               go, s);
+        };
+        using std::integral_constant;
+        using Small = integral_constant<int, RS_THREADS>;
+        using Big = integral_constant<int, RS_THREADS_BIG>;
+        if (f.threads == RS_THREADS_BIG) pass(Big{}, integral_constant<int, RS_IPT>{});
+        else if (f.ipt == 4) pass(Small{}, integral_constant<int, 4>{});
+        else if (f.ipt == 8) pass(Small{}, integral_constant<int, 8>{});
+        else pass(Small{}, integral_constant<int, RS_IPT>{});
         shift += bits;
         uint32_t* t = ki; ki = ko; ko = t;
         t = vi; vi = vo; vo = t;
