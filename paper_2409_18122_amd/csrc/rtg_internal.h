@@ -105,29 +105,31 @@ constexpr uint32_t FLAG_COUNT_OVERFLOW = 8u;
 
 void fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s);
 
-// cnt[i] = visible views of Gaussian i; mask[w * n + i] bit b = view 32w+b.
+// cnt[i] = visible views of Gaussian i; mask[w * n + i] bit b = view 32w+b.  Also clears zero[0, n_zero)
+// (n_zero <= 256), the counters that the later stages write.
 void project_count(const GaussDev& g, const ViewDev* views, const Header* hdr, int n_views_cap,
-                   SetDev st, uint32_t* cnt, uint32_t* mask, hipStream_t s);
+                   SetDev st, uint32_t* cnt, uint32_t* mask, uint32_t* zero, int n_zero, hipStream_t s);
 // Writes records at rec_off[i] .. for the visible views of Gaussian i (attr
 // only when write_attr).
 // chunk_g: workspace of pe_chunk_words(rec_cap) entries (the owners of each
-// chunk's first and last records, found before the records are written).
+// chunk's first and last records), filled already if owners (scan_u32).
 constexpr int PE_CHUNK = 256;  // records per block step of the record emission
 inline size_t pe_chunk_words(uint32_t rec_cap) { return 2 * ((size_t)rec_cap / PE_CHUNK + 2); }
 void project_emit(const GaussDev& g, const ViewDev* views, const Header* hdr, int n_views_cap,
                   SetDev st, int tw, int th, const uint32_t* mask, const uint32_t* cnt, const uint32_t* rec_off,
                   const uint32_t* R_dev, uint32_t rec_cap, Records rec, uint32_t* sortkey,
-                  bool write_attr, uint32_t* chunk_g, uint32_t* flags, hipStream_t s);
+                  bool write_attr, uint32_t* chunk_g, bool owners, uint32_t* flags, hipStream_t s);
 
-// Exclusive prefix sum of in[0..n) (n = min(*n_dev, cap)) into out; *total =
-// the full sum.  If gather != NULL the input is in[gather[i]].  A sum of 2^31
-// or more sets FLAG_COUNT_OVERFLOW in *flags (nullable) and gives *total = 0.
+// Exclusive prefix sum of in[0..n) into out, n = min(*n_dev, cap), or cap if n_dev is null; *total =
+// the full sum.  A sum of 2^31 or more sets FLAG_COUNT_OVERFLOW in *flags (nullable) and gives *total = 0.
+// mirror (nullable, pinned host memory): [0] the total, [1] the flags.  chunk_g (nullable): the owners of the chunks
+// of the first rec_cap records, for project_emit.
 struct ScanWs {
     uint32_t* partial;  // >= scan_blocks(cap) entries
 };
 int scan_blocks(uint64_t cap);
-void scan_u32(const uint32_t* in, const uint32_t* gather, uint32_t* out, const uint32_t* n_dev,
-              uint32_t cap, uint32_t* total, uint32_t* flags, ScanWs ws, hipStream_t s);
+void scan_u32(const uint32_t* in, uint32_t* out, const uint32_t* n_dev, uint32_t cap, uint32_t* total, uint32_t* flags,
+              ScanWs ws, hipStream_t s, uint32_t* mirror = nullptr, uint32_t* chunk_g = nullptr, uint32_t rec_cap = 0);
 
 // Stable LSD radix sort of (key, value) pairs on bits [0, nbits) of the key; returns 1 if the result is in
 // (k1, v1), 0 if it is in (k0, v0).  With count, the values are the items' positions (v0 need not be filled) and
@@ -185,7 +187,8 @@ void render_backward(int tw, int th, int batch, const ViewDev* views, int n_view
 void project_backward(const GaussDev& g, const ViewDev* views, SetDev st, const uint32_t* rec_off,
                       const uint32_t* cnt, const EmitRec* emit, const double* g2d,
                       float* d_means, float* d_log_scales, float* d_quats, float* d_opacity,
-                      float* d_colors, const uint32_t* flags, hipStream_t s);
+                      float* d_colors, const uint32_t* flags, hipStream_t s,
+                      uint32_t* flag_host = nullptr);
 
 // Scoring: per-(view, tile) partial sums of the composited uncertainty.
 // mode 0 sums u a T per pixel, mode 1 sums u over the contributing splats.
@@ -223,7 +226,8 @@ void region_utility(int64_t n, const float* means, const float* u, const double*
 // scores[v] = sum of view v's tile partials, in a fixed order; NaN when
 // *flags is non-zero.
 void score_reduce(const ViewDev* views, const Header* hdr, int n_views_cap, const double* partial,
-                  double* scores, const uint32_t* flags, hipStream_t s);
+                  double* scores, const uint32_t* flags, hipStream_t s,
+                  uint32_t* flag_host = nullptr);
 
 void export_pairs(const uint32_t* tile_key, const uint32_t* inst_rec, const uint32_t* K_dev,
                   Records rec, uint64_t* keys, uint32_t* vals, uint32_t cap, hipStream_t s);

@@ -507,7 +507,9 @@ constexpr int PC_FEW = 32;
 
 __global__ __launch_bounds__(256) void k_project_count(GaussDev g, const ViewDev* __restrict__ views,
                                                        const Header* __restrict__ hdr, SetDev st,
-                                                       uint32_t* __restrict__ cnt, uint32_t* __restrict__ mask) {
+                                                       uint32_t* __restrict__ cnt, uint32_t* __restrict__ mask,
+                                                       uint32_t* __restrict__ zero, int n_zero) {
+    if (blockIdx.x == 0 && (int)threadIdx.x < n_zero) zero[threadIdx.x] = 0u;
     // the cameras' test values, staged in LDS (every thread reads the same camera at a time)
     __shared__ CullView s_vf[PC_FEW];
     const int nv = min((int)hdr->n_views, PC_FEW);
@@ -550,7 +552,9 @@ __device__ __noinline__ bool pair_visible(const GaussDev& g, int64_t i, const Vi
 template <int VIEWS, int NT>
 __global__ __launch_bounds__(NT, 4) void k_project_count_queued(GaussDev g, const ViewDev* __restrict__ views,
                                                          const Header* __restrict__ hdr, int words, SetDev st,
-                                                         uint32_t* __restrict__ cnt, uint32_t* __restrict__ mask) {
+                                                         uint32_t* __restrict__ cnt, uint32_t* __restrict__ mask,
+                                                         uint32_t* __restrict__ zero, int n_zero) {
+    if (blockIdx.x == 0 && (int)threadIdx.x < n_zero) zero[threadIdx.x] = 0u;
     static_assert(VIEWS <= NT && VIEWS % 32 == 0 && VIEWS <= 256, "a thread stages a camera; a queue entry holds 8 bits of it");
     __shared__ ScreenView s_v[VIEWS];
     __shared__ uint32_t s_vis[VIEWS / 32][NT];
@@ -672,13 +676,8 @@ __device__ __forceinline__ void chunk_of(uint32_t n, int nblocks, uint32_t& begi
     end = (uint32_t)min<uint64_t>(b + per, n);
 }
 
-__device__ __forceinline__ uint32_t scan_in(const uint32_t* in, const uint32_t* gather, uint32_t i) {
-    return gather ? in[gather[i]] : in[i];
-}
-
 // Multi-block exclusive scan of n = min(*n_dev, cap) items (n = cap when n_dev is
-// null), in[gather[i]] when gather is given: per-block totals here, then
-// k_scan_down.  Totals are formed in 64 bits; a block total is stored
+// null): per-block totals here, then k_scan_down.  Totals are formed in 64 bits; a block total is stored
 // saturated at SCAN_LIMIT, so that k_scan_down can tell a sum of 2^31 or more
 // from one that merely wrapped.
 constexpr uint64_t SCAN_LIMIT = 0x80000000ull;
@@ -696,7 +695,6 @@ __device__ __forceinline__ uint64_t block_sum64(uint64_t x, uint64_t* ws) {
 }
 
 __global__ __launch_bounds__(SC_THREADS) void k_scan_reduce(const uint32_t* __restrict__ in,
-                                                            const uint32_t* __restrict__ gather,
                                                             const uint32_t* __restrict__ n_dev,
                                                             uint32_t cap, uint32_t* __restrict__ partial) {
     __shared__ uint64_t ws[SC_THREADS / 64];
@@ -704,46 +702,79 @@ __global__ __launch_bounds__(SC_THREADS) void k_scan_reduce(const uint32_t* __re
     uint32_t begin, end;
     chunk_of(n, gridDim.x, begin, end);
     uint64_t acc = 0;
-    for (uint32_t i = begin + threadIdx.x; i < end; i += SC_THREADS) acc += scan_in(in, gather, i);
+    for (uint32_t i = begin + threadIdx.x; i < end; i += SC_THREADS) acc += in[i];
     const uint64_t total = block_sum64(acc, ws);
     if (threadIdx.x == 0) partial[blockIdx.x] = (uint32_t)min(total, SCAN_LIMIT);
 }
 
 
+// What a scan leaves beside the offsets (all nullable): the total, on the device and in pinned host memory
+// with the flags word (mirror[0], mirror[1]; a copy would be a launch of its own), and for the records of each Gaussian
+// the owners of the chunk ends (chunk_owners).
+struct ScanOut {
+    uint32_t* total;
+    uint32_t* flags;
+    uint32_t* mirror;
+    uint32_t* chunk_g;
+    uint32_t rec_cap;
+};
+
+// The Gaussians that own the first and the last record of every chunk of
+// PE_CHUNK records (chunk_g[2c], chunk_g[2c + 1]): each Gaussian i, of c records from a, writes the
+// chunk ends that fall among its records, so every entry has one writer.
+// Record p is owned by the Gaussian i with rec_off[i] <= p < rec_off[i] +
+// cnt[i], which is the last Gaussian whose first record is at or before p.
+__device__ __forceinline__ void chunk_owners(uint32_t i, uint32_t a, uint32_t c, uint32_t R, uint32_t* chunk_g) {
+    if (c == 0 || a >= R) return;
+    const uint32_t b = (uint32_t)min<uint64_t>((uint64_t)a + c, R);  // records [a, b)
+    for (uint32_t k = a / PE_CHUNK; k <= (b - 1) / PE_CHUNK; k++) {
+        const uint32_t first = k * PE_CHUNK;
+        const uint32_t last = (uint32_t)min<uint64_t>((uint64_t)first + PE_CHUNK - 1, R - 1);
+        if (first >= a) chunk_g[2 * k] = i;
+        if (last < b) chunk_g[2 * k + 1] = i;
+    }
+}
+
 // partial[b] holds block b's total (k_scan_reduce); each block adds up the
-// totals before it, and block 0 writes the grand total to *total (nullable).
+// totals before it, and block 0 writes the grand total.  Without partial a single block adds up its
+// items itself.
 // A grand total of 2^31 or more is not representable by the 32-bit offsets:
-// then *total is 0, flags (nullable) gets FLAG_COUNT_OVERFLOW and nothing is
+// then the total is 0, flags gets FLAG_COUNT_OVERFLOW and nothing is
 // written to out, so every consumer of the total sees an empty list.
 // in and out may be the same array (each item is read and written by one thread).
-__global__ __launch_bounds__(SC_THREADS) void k_scan_down(const uint32_t* in,
-                                                          const uint32_t* __restrict__ gather,
-                                                          uint32_t* out,
+__global__ __launch_bounds__(SC_THREADS) void k_scan_down(const uint32_t* in, uint32_t* out,
                                                           const uint32_t* __restrict__ n_dev, uint32_t cap,
-                                                          const uint32_t* __restrict__ partial,
-                                                          uint32_t* __restrict__ total_out,
-                                                          uint32_t* __restrict__ flags) {
+                                                          const uint32_t* __restrict__ partial, ScanOut o) {
     __shared__ uint32_t ws[SC_THREADS / 64];
     __shared__ uint64_t ws64[SC_THREADS / 64];
     const uint32_t n = n_dev ? min(*n_dev, cap) : cap;
     uint32_t begin, end;
     chunk_of(n, gridDim.x, begin, end);
     uint64_t before = 0, all = 0;
-    for (uint32_t t = threadIdx.x; t < gridDim.x; t += SC_THREADS) {
-        const uint64_t p = partial[t];
-        all += p;
-        before += t < blockIdx.x ? p : 0u;
+    if (partial) {
+        for (uint32_t t = threadIdx.x; t < gridDim.x; t += SC_THREADS) {
+            const uint64_t p = partial[t];
+            all += p;
+            before += t < blockIdx.x ? p : 0u;
+        }
+    } else {
+        for (uint32_t i = begin + threadIdx.x; i < end; i += SC_THREADS) all += in[i];
     }
     uint32_t run = (uint32_t)block_sum64(before, ws64);
     all = block_sum64(all, ws64);
-    if (all >= SCAN_LIMIT) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            if (total_out) *total_out = 0u;
-            if (flags) atomicOr(flags, FLAG_COUNT_OVERFLOW);
+    const bool over = all >= SCAN_LIMIT;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const uint32_t total = over ? 0u : (uint32_t)all;
+        if (o.total) *o.total = total;
+        if (o.flags && over) atomicOr(o.flags, FLAG_COUNT_OVERFLOW);
+        if (o.mirror) {
+            __hip_atomic_store(o.mirror, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(o.mirror + 1, (over ? FLAG_COUNT_OVERFLOW : 0u) | (o.flags ? *o.flags : 0u), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
         }
-        return;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && total_out) *total_out = (uint32_t)all;
+    if (over) return;
+    const uint32_t R = (uint32_t)min<uint64_t>(all, o.rec_cap);
     for (uint32_t t0 = begin; t0 < end; t0 += SC_TILE) {
         // thread owns SC_IPT consecutive items
         uint32_t v[SC_IPT];
@@ -752,7 +783,7 @@ __global__ __launch_bounds__(SC_THREADS) void k_scan_down(const uint32_t* in,
 #pragma unroll
         for (int j = 0; j < SC_IPT; j++) {
             uint32_t idx = first + j;
-            v[j] = idx < end ? scan_in(in, gather, idx) : 0;
+            v[j] = idx < end ? in[idx] : 0;
             sum += v[j];
         }
         uint32_t total;
@@ -760,7 +791,10 @@ __global__ __launch_bounds__(SC_THREADS) void k_scan_down(const uint32_t* in,
 #pragma unroll
         for (int j = 0; j < SC_IPT; j++) {
             uint32_t idx = first + j;
-            if (idx < end) out[idx] = ex;
+            if (idx < end) {
+                out[idx] = ex;
+                if (o.chunk_g) chunk_owners(idx, ex, v[j], R, o.chunk_g);
+            }
             ex += v[j];
         }
         run += total;
@@ -1035,6 +1069,82 @@ __global__ __launch_bounds__(NT, 4) void k_rs_scatter(const uint32_t* __restrict
     }
 }
 
+// The whole sort of up to RS_ONE items in one block: every pass ranks as above and moves the items through LDS.
+constexpr int RS_ONE_THREADS = 1024, RS_ONE_IPT = 4;
+constexpr uint32_t RS_ONE = RS_ONE_THREADS * RS_ONE_IPT;
+
+__global__ __launch_bounds__(RS_ONE_THREADS) void k_rs_one(const uint32_t* __restrict__ kin,
+                                                           const uint32_t* __restrict__ vin,
+                                                           uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
+                                                           const uint32_t* __restrict__ n_dev, uint32_t cap, int nbits,
+                                                           const uint32_t* __restrict__ count,
+                                                           uint32_t* __restrict__ gout) {
+    constexpr int NB = 1 << RS_DB, WAVES = RS_ONE_THREADS / 64, IPT = RS_ONE_IPT;
+    __shared__ uint32_t wh[WAVES][NB];
+    __shared__ uint32_t ws[WAVES];
+    __shared__ uint32_t s_k[RS_ONE], s_v[RS_ONE];
+    const int tid = threadIdx.x, wv = tid >> 6;
+    const uint32_t lane = lane_id(), n = min(min(*n_dev, cap), RS_ONE), seg = wv * (64 * IPT);
+    uint32_t k[IPT], v[IPT], pos[IPT];
+#pragma unroll
+    for (int j = 0; j < IPT; j++) {
+        const uint32_t idx = seg + j * 64 + lane;
+        k[j] = idx < n ? kin[idx] : 0u;
+        v[j] = count ? idx : idx < n ? vin[idx] : 0u;
+    }
+    for (int shift = 0; shift < nbits; shift += RS_DB) {
+        const uint32_t mask = (1u << min(RS_DB, nbits - shift)) - 1u;
+        for (int i = tid; i < WAVES * NB; i += RS_ONE_THREADS) (&wh[0][0])[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPT; j++) {
+            const bool valid = seg + j * 64 + lane < n;
+            const uint32_t d = (k[j] >> shift) & mask;
+            const uint64_t m = digit_peers(d, __ballot(valid));
+            const uint32_t before = valid ? wh[wv][d] : 0u;
+            pos[j] = before + (uint32_t)__popcll(m & lanemask_lt());
+            if (valid && lane == (uint32_t)__builtin_ctzll(m)) wh[wv][d] = before + (uint32_t)__popcll(m);
+        }
+        __syncthreads();
+        uint32_t run = 0;
+        if (tid < NB)
+#pragma unroll
+            for (int w = 0; w < WAVES; w++) run += wh[w][tid];
+        uint32_t at = rs_block_excl<RS_ONE_THREADS>(run, ws);
+        if (tid < NB)
+#pragma unroll
+            for (int w = 0; w < WAVES; w++) {
+                const uint32_t c = wh[w][tid];
+                wh[w][tid] = at;
+                at += c;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPT; j++)
+            if (seg + j * 64 + lane < n) {
+                const uint32_t lp = wh[wv][(k[j] >> shift) & mask] + pos[j];
+                s_k[lp] = k[j];
+                s_v[lp] = v[j];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPT; j++) {
+            const uint32_t idx = seg + j * 64 + lane;
+            k[j] = idx < n ? s_k[idx] : 0u;
+            v[j] = idx < n ? s_v[idx] : 0u;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < IPT; j++) {
+        const uint32_t idx = seg + j * 64 + lane;
+        if (idx < n) {
+            kout[idx] = k[j];
+            vout[idx] = v[j];
+            if (gout) gout[idx] = count[v[j]];
+        }
+    }
+}
+
 // ---------------------------------------------------------------- binning
 
 __device__ __forceinline__ uint32_t last_le(const uint32_t* a, uint32_t n, uint32_t x) {
@@ -1135,28 +1245,14 @@ __device__ __forceinline__ int nth_set_bit(uint32_t x, uint32_t k) {
 
 static_assert(PE_THREADS == PE_CHUNK, "a block step of the record emission is one chunk");
 
-// The Gaussians that own the first and the last record of every chunk of
-// PE_CHUNK records (chunk_g[2c], chunk_g[2c + 1]): each Gaussian writes the
-// chunk ends that fall among its records, so every entry has one writer.
-// Record p is owned by the Gaussian i with rec_off[i] <= p < rec_off[i] +
-// cnt[i], which is the last Gaussian whose first record is at or before p.
+// The chunk ends' owners where the record buffers are sized only after the scan.
 __global__ __launch_bounds__(256) void k_chunk_owners(const uint32_t* __restrict__ cnt,
                                                       const uint32_t* __restrict__ rec_off, int64_t n,
                                                       const uint32_t* __restrict__ R_dev, uint32_t rec_cap,
                                                       uint32_t* __restrict__ chunk_g) {
     const uint32_t R = min(*R_dev, rec_cap);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t c = cnt[i];
-        const uint32_t a = rec_off[i];
-        if (c == 0 || a >= R) continue;
-        const uint32_t b = (uint32_t)min<uint64_t>((uint64_t)a + c, R);  // records [a, b)
-        for (uint32_t k = a / PE_CHUNK; k <= (b - 1) / PE_CHUNK; k++) {
-            const uint32_t first = k * PE_CHUNK;
-            const uint32_t last = (uint32_t)min<uint64_t>((uint64_t)first + PE_CHUNK - 1, R - 1);
-            if (first >= a) chunk_g[2 * k] = (uint32_t)i;
-            if (last < b) chunk_g[2 * k + 1] = (uint32_t)i;
-        }
-    }
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        chunk_owners((uint32_t)i, rec_off[i], cnt[i], R, chunk_g);
 }
 
 // Bound by the instructions of the binary64 form (two divisions and two square roots beyond the projection's own) and
@@ -1550,6 +1646,37 @@ __global__ __launch_bounds__(256) void k_tile_order_place(const uint2* __restric
         if (t < n) order[start[b] + base[b] + rank] = t;
         __syncthreads();
     }
+}
+
+// The same in one block, for up to TO_ONE tiles: the sizes of the buckets, then the places.
+constexpr uint32_t TO_ONE = 8192;
+
+__global__ __launch_bounds__(1024) void k_tile_order_one(const uint2* __restrict__ ranges,
+                                                         const Header* __restrict__ hdr, uint32_t tiles_cap,
+                                                         uint32_t* __restrict__ order) {
+    __shared__ uint32_t h[TO_BUCKETS];
+    if (threadIdx.x < TO_BUCKETS) h[threadIdx.x] = 0u;
+    __syncthreads();
+    const uint32_t n = min(hdr->tiles_total, tiles_cap);
+    int b[TO_ONE / 1024];
+#pragma unroll
+    for (uint32_t j = 0; j < TO_ONE / 1024; j++) {
+        const uint32_t t = j * 1024 + threadIdx.x;
+        b[j] = t < n ? tile_bucket(ranges[t]) : -1;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < TO_ONE / 1024; j++)
+        if (b[j] >= 0) atomicAdd(&h[b[j]], 1u);
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const uint32_t c = threadIdx.x < TO_BUCKETS ? h[threadIdx.x] : 0u;
+        const uint32_t start = wave_incl_scan(c) - c;
+        if (threadIdx.x < TO_BUCKETS) h[threadIdx.x] = start;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < TO_ONE / 1024; j++)
+        if (b[j] >= 0) order[atomicAdd(&h[b[j]], 1u)] = j * 1024 + threadIdx.x;
 }
 
 // ------------------------------------------------------------ compositing
@@ -2291,8 +2418,10 @@ __global__ __launch_bounds__(256) void k_project_bwd(GaussDev g, const ViewDev* 
                                                      const double* __restrict__ g2d,
                                                      float* __restrict__ d_means, float* __restrict__ d_ls,
                                                      float* __restrict__ d_quats, float* __restrict__ d_op,
-                                                     float* __restrict__ d_col, const uint32_t* __restrict__ flags) {
+                                                     float* __restrict__ d_col, const uint32_t* __restrict__ flags,
+                                                     uint32_t* __restrict__ flag_host) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (flag_host && i == 0) __hip_atomic_store(flag_host, *flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (i >= g.n) return;
     if (flags && *flags) return;
     uint32_t c = cnt[i];
@@ -2639,9 +2768,12 @@ __global__ __launch_bounds__(256) void k_score_reduce(const ViewDev* __restrict_
                                                       const Header* __restrict__ hdr,
                                                       const double* __restrict__ partial,
                                                       double* __restrict__ scores,
-                                                      const uint32_t* __restrict__ flags) {
+                                                      const uint32_t* __restrict__ flags,
+                                                      uint32_t* __restrict__ flag_host) {
     __shared__ double ws[4];
     const uint32_t v = blockIdx.x;
+    if (flag_host && v == 0 && threadIdx.x == 0)
+        __hip_atomic_store(flag_host, *flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (v >= hdr->n_views) return;
     if (*flags) {  // an overflowed or inconsistent binning: the scores are invalid
         if (threadIdx.x == 0) scores[v] = __builtin_nan("");
@@ -3328,14 +3460,18 @@ void fill_u32(uint32_t* p, uint32_t v, uint64_t n, hipStream_t s) {
 }
 
 void project_count(const GaussDev& g, const ViewDev* views, const Header* hdr, int n_views_cap, SetDev st,
-                   uint32_t* cnt, uint32_t* mask, hipStream_t s) {
-    if (g.n == 0) return;
+                   uint32_t* cnt, uint32_t* mask, uint32_t* zero, int n_zero, hipStream_t s) {
+    if (g.n == 0) {
+        fill_u32(zero, 0u, n_zero, s);
+        return;
+    }
     int words = (n_views_cap + 31) / 32;
     // one thread per Gaussian: the grid covers every n below 2^31
     if (n_views_cap <= PC_FEW)
-        k_project_count<<<grid_for(g.n, 256, 0xffffffffu), 256, 0, s>>>(g, views, hdr, st, cnt, mask);
+        k_project_count<<<grid_for(g.n, 256, 0xffffffffu), 256, 0, s>>>(g, views, hdr, st, cnt, mask, zero, n_zero);
     else
-        k_project_count_queued<PC_VIEWS, 512><<<grid_for(g.n, 512, 0xffffffffu), 512, 0, s>>>(g, views, hdr, words, st, cnt, mask);
+        k_project_count_queued<PC_VIEWS, 512><<<grid_for(g.n, 512, 0xffffffffu), 512, 0, s>>>(g, views, hdr, words, st, cnt, mask, zero,
+                                                                                               n_zero);
 }
 
 // log2 of a power-of-two tile side (8, 16 or 32)
@@ -3348,11 +3484,12 @@ static int ilog2(int x) {
 void project_emit(const GaussDev& g, const ViewDev* views, const Header* hdr, int n_views_cap, SetDev st,
                   int tw, int th, const uint32_t* mask, const uint32_t* cnt, const uint32_t* rec_off,
                   const uint32_t* R_dev, uint32_t rec_cap, Records rec, uint32_t* sortkey,
-                  bool write_attr, uint32_t* chunk_g, uint32_t* flags, hipStream_t s) {
+                  bool write_attr, uint32_t* chunk_g, bool owners, uint32_t* flags, hipStream_t s) {
     (void)hdr;
     if (g.n == 0 || rec_cap == 0) return;
     int words = (n_views_cap + 31) / 32;
-    k_chunk_owners<<<grid_for(g.n, 256, 16384), 256, 0, s>>>(cnt, rec_off, g.n, R_dev, rec_cap, chunk_g);
+    if (!owners)
+        k_chunk_owners<<<grid_for(g.n, 256, 16384), 256, 0, s>>>(cnt, rec_off, g.n, R_dev, rec_cap, chunk_g);
     k_project_emit<<<grid_for(rec_cap, PE_THREADS, 32768), PE_THREADS, 0, s>>>(
         g, views, words, st, ilog2(tw), ilog2(th), mask, rec_off, R_dev, rec_cap, rec, sortkey,
         write_attr ? 1 : 0, chunk_g, flags);
@@ -3365,11 +3502,19 @@ int scan_blocks(uint64_t cap) {
     return (int)b;
 }
 
-void scan_u32(const uint32_t* in, const uint32_t* gather, uint32_t* out, const uint32_t* n_dev, uint32_t cap,
-              uint32_t* total, uint32_t* flags, ScanWs ws, hipStream_t s) {
+// One launch up to SCAN_ONE items (a block reads 16 k of them twice in 9 us; the two launches take 10).
+constexpr uint32_t SCAN_ONE = 8 * SC_TILE;
+
+void scan_u32(const uint32_t* in, uint32_t* out, const uint32_t* n_dev, uint32_t cap, uint32_t* total, uint32_t* flags,
+              ScanWs ws, hipStream_t s, uint32_t* mirror, uint32_t* chunk_g, uint32_t rec_cap) {
+    const ScanOut o{total, flags, mirror, chunk_g, rec_cap};
+    if (cap <= SCAN_ONE) {
+        k_scan_down<<<1, SC_THREADS, 0, s>>>(in, out, n_dev, cap, nullptr, o);
+        return;
+    }
     int nb = scan_blocks(cap);
-    k_scan_reduce<<<nb, SC_THREADS, 0, s>>>(in, gather, n_dev, cap, ws.partial);
-    k_scan_down<<<nb, SC_THREADS, 0, s>>>(in, gather, out, n_dev, cap, ws.partial, total, flags);
+    k_scan_reduce<<<nb, SC_THREADS, 0, s>>>(in, n_dev, cap, ws.partial);
+    k_scan_down<<<nb, SC_THREADS, 0, s>>>(in, out, n_dev, cap, ws.partial, o);
 }
 
 // The form of a pass over at most cap items: items per lane, threads and blocks (one per tile, up to RS_MAX_BLOCKS).
@@ -3411,6 +3556,11 @@ static void rs_pass(uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint32_t* vo
 // of three over 192 M pairs took 1,220 us each (the 8-bit ones 700 to 930): twice the buckets, half the runs.
 int radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uint32_t* n_dev, uint32_t cap,
                int nbits, SortWs ws, hipStream_t s, const uint32_t* count, uint32_t* gout) {
+    if (cap <= RS_ONE) {
+        // the passes of 2 k items in one launch of 16 us; 8 launches took 31 and the gaps between them
+        k_rs_one<<<1, RS_ONE_THREADS, 0, s>>>(k0, v0, k1, v1, n_dev, cap, nbits, count, gout);
+        return 1;
+    }
     const RsForm f = sort_form(cap);
     const int passes = std::max(1, (nbits + RS_DB - 1) / RS_DB);
     RsCounts rc{count, 32};
@@ -3462,6 +3612,11 @@ void tile_ranges(const uint32_t* tile_key, const uint32_t* K_dev, uint32_t inst_
 void tile_order(const uint2* ranges, const Header* hdr, uint32_t tiles_cap, uint32_t* ws, uint32_t* order,
                 hipStream_t s) {
     if (tiles_cap == 0) return;
+    if (tiles_cap <= TO_ONE) {
+        // one launch of 5 us instead of three
+        k_tile_order_one<<<1, 1024, 0, s>>>(ranges, hdr, tiles_cap, order);
+        return;
+    }
     fill_u32(ws, 0u, 2 * TO_BUCKETS, s);
     const unsigned grid = grid_for(tiles_cap, 256, 1024);
     k_tile_order_count<<<grid, 256, 0, s>>>(ranges, hdr, tiles_cap, ws);
@@ -3552,10 +3707,10 @@ void render_backward(int tw, int th, int batch, const ViewDev* views, int n_view
 void project_backward(const GaussDev& g, const ViewDev* views, SetDev st, const uint32_t* rec_off,
                       const uint32_t* cnt, const EmitRec* emit, const double* g2d, float* d_means,
                       float* d_log_scales, float* d_quats, float* d_opacity, float* d_colors, const uint32_t* flags,
-                      hipStream_t s) {
+                      hipStream_t s, uint32_t* flag_host) {
     if (g.n == 0) return;
     k_project_bwd<<<grid_for(g.n, 256, 0xffffffffu), 256, 0, s>>>(g, views, st, rec_off, cnt, emit, g2d, d_means,
-                                                     d_log_scales, d_quats, d_opacity, d_colors, flags);
+                                                     d_log_scales, d_quats, d_opacity, d_colors, flags, flag_host);
 }
 
 void score_tiles(int tw, int th, int batch, int mode, bool persistent, int grid_persistent, const ViewDev* views,
@@ -3580,8 +3735,8 @@ void score_tiles(int tw, int th, int batch, int mode, bool persistent, int grid_
 }
 
 void score_reduce(const ViewDev* views, const Header* hdr, int n_views_cap, const double* partial,
-                  double* scores, const uint32_t* flags, hipStream_t s) {
-    k_score_reduce<<<n_views_cap, 256, 0, s>>>(views, hdr, partial, scores, flags);
+                  double* scores, const uint32_t* flags, hipStream_t s, uint32_t* flag_host) {
+    k_score_reduce<<<n_views_cap, 256, 0, s>>>(views, hdr, partial, scores, flags, flag_host);
 }
 
 void sum_u32_pair(const uint32_t* a, const uint32_t* b, uint64_t n, unsigned long long* out, hipStream_t s) {

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 # about one record per Gaussian, and one pair per record but for the big ones
-@pytest.mark.parametrize("n", [1, 255, 1023, 1025, 32_700, 32_900, 262_100, 262_300, 1_048_500, 1_048_700, 2_097_300])
+@pytest.mark.parametrize("n", [1, 255, 1023, 1025, 4096, 4097, 16_384, 16_385, 32_700, 32_900, 262_100, 262_300, 1_048_500, 1_048_700, 2_097_300])
 def test_sorted_pairs(n):
     from paper_2409_18122_amd import raster
     print(f"sort n={n}", flush=True)
