@@ -1576,8 +1576,7 @@ rtg_status rtg_region_utility(rtg_ctx* ctx, int64_t n, const float* means, const
     RTG_TRY(acc.ensure(ctx, (2 * sizeof(unsigned long long) + sizeof(unsigned int)) * (size_t)nr));
     unsigned long long* cnt = acc.as<unsigned long long>();
     int dm[3] = {dims[0], dims[1], dims[2]};
-    region_utility(n, means, u, box, size, dm, cnt, cnt + nr, reinterpret_cast<unsigned int*>(cnt + 2 * nr), count,
-                   sum, mean, s);
+    region_utility(n, means, u, box, size, dm, cnt, count, sum, mean, s);
     return check_launch("region utility");
 }
 

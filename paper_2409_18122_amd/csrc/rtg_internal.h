@@ -219,10 +219,9 @@ void collision_check(const GaussDev& g, const float* pts, int64_t np, float r_ro
 void uncertainty_update(int64_t n, const float* prev, const float* cur, const float* u_prev, int squared,
                         float* u_out, hipStream_t s);
 // Region utility over dims[0] x dims[1] x dims[2] cuboids from lo (host
-// values) with edge size; cnt/fix (u64) and bad (u32) are nr-entry scratch.
+// values) with edge size; cnt: scratch of 20 bytes per region (counts and sums of 8, marks of 4).
 void region_utility(int64_t n, const float* means, const float* u, const double* lo, double size, const int* dims,
-                    unsigned long long* cnt, unsigned long long* fix, unsigned int* bad, int64_t* count, double* sum,
-                    double* mean, hipStream_t s);
+                    unsigned long long* cnt, int64_t* count, double* sum, double* mean, hipStream_t s);
 // scores[v] = sum of view v's tile partials, in a fixed order; NaN when
 // *flags is non-zero.
 void score_reduce(const ViewDev* views, const Header* hdr, int n_views_cap, const double* partial,

@@ -3305,16 +3305,24 @@ __global__ __launch_bounds__(256) void k_uncertainty_update(int64_t n, const flo
 constexpr double RG_FIX = 4294967296.0;  // 2^32
 constexpr int RG_LDS = 2048;             // regions privatised in LDS per block
 
-__device__ __forceinline__ int64_t region_of(const float* __restrict__ means, int64_t n, int64_t i, double lx,
-                                             double ly, double lz, double size, int nx, int ny, int nz) {
-    const double fx = floor(((double)means[i] - lx) / size);
-    const double fy = floor(((double)means[n + i] - ly) / size);
-    const double fz = floor(((double)means[2 * n + i] - lz) / size);
+__device__ __forceinline__ int64_t region_of(float mx, float my, float mz, double lx, double ly, double lz, double size,
+                                             int nx, int ny, int nz) {
+    const double fx = floor(((double)mx - lx) / size);
+    const double fy = floor(((double)my - ly) / size);
+    const double fz = floor(((double)mz - lz) / size);
     if (!(fx >= 0.0 && fx < (double)nx && fy >= 0.0 && fy < (double)ny && fz >= 0.0 && fz < (double)nz)) return -1;
     return (int64_t)fx + (int64_t)nx * ((int64_t)fy + (int64_t)ny * (int64_t)fz);
 }
 
-__global__ __launch_bounds__(256) void k_region_utility(int64_t n, const float* __restrict__ means,
+// Bound by the latency of a thread's turns (few blocks, so that few add their tables up at the end): RG_BATCH
+// Gaussians a turn, all their loads in flight, and by the blocks that add their tables up at the end: 2 M Gaussians, 128
+// regions: 256 blocks of 1,024 threads 16.4 us, 128 20.7, 512 18.1; blocks of 256 threads that took one Gaussian a turn:
+// 34 us with 488 of them, 47 with 1,953.
+constexpr int RG_BATCH = 4;
+constexpr int RG_THREADS = 1024;
+constexpr unsigned RG_BLOCKS = 256;
+
+__global__ __launch_bounds__(RG_THREADS) void k_region_utility(int64_t n, const float* __restrict__ means,
                                                         const float* __restrict__ u, double lx, double ly,
                                                         double lz, double size, int nx, int ny, int nz,
                                                         unsigned long long* __restrict__ cnt,
@@ -3327,19 +3335,33 @@ __global__ __launch_bounds__(256) void k_region_utility(int64_t n, const float* 
         for (int r = threadIdx.x; r < nr; r += blockDim.x) s_cnt[r] = s_fix[r] = 0ull;
         __syncthreads();
     }
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = region_of(means, n, i, lx, ly, lz, size, nx, ny, nz);
-        if (r < 0) continue;
-        const float v = u[i];
-        const bool ok = isfinite(v) && fabsf(v) < 1048576.0f;
-        const long long f = ok ? __double2ll_rn((double)v * RG_FIX) : 0ll;
-        if (!ok) atomicOr(&bad[r], 1u);
-        if (lds) {
-            atomicAdd(&s_cnt[r], 1ull);
-            atomicAdd(&s_fix[r], (unsigned long long)f);  // two's complement: signed sums wrap correctly
-        } else {
-            atomicAdd(&cnt[r], 1ull);
-            atomicAdd(&fix[r], (unsigned long long)f);
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < n; i0 += RG_BATCH * stride) {
+        float m[RG_BATCH][4];
+#pragma unroll
+        for (int k = 0; k < RG_BATCH; k++) {
+            const int64_t i = i0 + k * stride;
+            const bool in = i < n;
+            m[k][0] = in ? means[i] : 0.0f;
+            m[k][1] = in ? means[n + i] : 0.0f;
+            m[k][2] = in ? means[2 * n + i] : 0.0f;
+            m[k][3] = in ? u[i] : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < RG_BATCH; k++) {
+            const int64_t r = region_of(m[k][0], m[k][1], m[k][2], lx, ly, lz, size, nx, ny, nz);
+            if (r < 0 || i0 + k * stride >= n) continue;
+            const float v = m[k][3];
+            const bool ok = isfinite(v) && fabsf(v) < 1048576.0f;
+            const long long f = ok ? __double2ll_rn((double)v * RG_FIX) : 0ll;
+            if (!ok) atomicOr(&bad[r], 1u);
+            if (lds) {
+                atomicAdd(&s_cnt[r], 1ull);
+                atomicAdd(&s_fix[r], (unsigned long long)f);  // two's complement: signed sums wrap correctly
+            } else {
+                atomicAdd(&cnt[r], 1ull);
+                atomicAdd(&fix[r], (unsigned long long)f);
+            }
         }
     }
     if (lds) {
@@ -3751,16 +3773,15 @@ void uncertainty_update(int64_t n, const float* prev, const float* cur, const fl
 }
 
 void region_utility(int64_t n, const float* means, const float* u, const double* lo, double size, const int* dims,
-                    unsigned long long* cnt, unsigned long long* fix, unsigned int* bad, int64_t* count, double* sum,
-                    double* mean, hipStream_t s) {
+                    unsigned long long* cnt, int64_t* count, double* sum, double* mean, hipStream_t s) {
     const int64_t nr = (int64_t)dims[0] * dims[1] * dims[2];
-    fill_u32(reinterpret_cast<uint32_t*>(cnt), 0u, 2 * (uint64_t)nr, s);
-    fill_u32(reinterpret_cast<uint32_t*>(fix), 0u, 2 * (uint64_t)nr, s);
-    fill_u32(bad, 0u, (uint64_t)nr, s);
+    unsigned long long* fix = cnt + nr;
+    unsigned int* bad = reinterpret_cast<unsigned int*>(fix + nr);
+    fill_u32(reinterpret_cast<uint32_t*>(cnt), 0u, 5 * (uint64_t)nr, s);
     if (n > 0) {
-        const unsigned grid = grid_for((uint64_t)n, 256 * 16, 2048);  // blocks walk 16 x 256 Gaussians
-        k_region_utility<<<grid, 256, 0, s>>>(n, means, u, lo[0], lo[1], lo[2], size, dims[0], dims[1], dims[2], cnt,
-                                              fix, bad);
+        const unsigned grid = grid_for((uint64_t)n, RG_THREADS * RG_BATCH, RG_BLOCKS);
+        k_region_utility<<<grid, RG_THREADS, 0, s>>>(n, means, u, lo[0], lo[1], lo[2], size, dims[0], dims[1], dims[2], cnt,
+                                                     fix, bad);
     }
     k_region_finish<<<grid_for((uint64_t)nr, 256, 4096), 256, 0, s>>>(nr, cnt, fix, bad, count, sum, mean);
 }
