@@ -39,3 +39,23 @@ def test_sorted_pairs(n):
     keep = np.isin(ids(k_box, v_box), ids(keys, vals))
     assert keep.sum() == len(keys) >= len(np.unique(v_box))
     assert np.array_equal(keys, k_box[keep]) and np.array_equal(vals, v_box[keep])
+
+
+@pytest.mark.parametrize("n", [3, 2047, 2049, 16_386, 70_001])
+def test_scanned_offsets(n):
+    """Records of sparse visibility: the scan's ragged ends and long runs of zero counts."""
+    from paper_2409_18122_amd import raster
+    print(f"scan n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    g = {k: v.copy() for k, v in scenes.config1(n=n, seed=2)[0].items()}
+    cams = scenes.config1(n=2)[1] * 3
+    g["means"][2, rng.random(n) < 0.7] *= -1.0
+    f = raster.Frame(raster.Context(0), raster.to_device(g), cams, dict(scenes.DEFAULT_SETTINGS))
+    f.bin_sort()
+    keys, vals, _ = f.export()
+    keys, vals = keys.cpu().numpy().view(np.uint64), vals.cpu().numpy().view(np.uint32)
+    k_box, v_box = oracle.keys(g, cams, dict(scenes.DEFAULT_SETTINGS), (16, 16))
+    ids = lambda k, v: (k >> np.uint64(32)) << np.uint64(32) | v.astype(np.uint64)
+    keep = np.isin(ids(k_box, v_box), ids(keys, vals))
+    assert keep.sum() == len(keys)
+    assert np.array_equal(keys, k_box[keep]) and np.array_equal(vals, v_box[keep])
