@@ -2137,12 +2137,12 @@ constexpr int RED_STRIDE = 68;
 //   6..9: sum g_ch w (colour and depth).
 // A splat with a = 0 and a_g = 0 leaves T (1 / (1 - 0) = 1 exactly), D and
 // every sum unchanged, for finite pixel gradients and colours.
-// Returns t and adds the colour and depth sums to col.
 // AU: the alpha and uncertainty images carry gradients too (colour 1 and u
 // in GA; otherwise their terms are left out altogether).
+// FIRST: the lane's first pixel starts the sums.
 template <bool AU, bool FIRST>
-__device__ __forceinline__ float bwd_pixel(float a, float ag, float4 at, float ui, float gr, float gg, float gb,
-                                           float gd, float ga, float gu, float& T, float& D, float* col) {
+__device__ __forceinline__ void bwd_pixel(float a, float ag, float dx, float dy, float4 at, float ui, float gr, float gg,
+                                          float gb, float gd, float ga, float gu, float& T, float& D, float* acc) {
     const float inv = __builtin_amdgcn_rcpf(1.0f - a);
     const float Ti = T * inv;
     const float w = a * Ti;
@@ -2157,29 +2157,34 @@ __device__ __forceinline__ float bwd_pixel(float a, float ag, float4 at, float u
     const float da = fmaf(Ti, GA, -(D * inv));
     D = fmaf(w, GA, D);
     T = Ti;
-    col[0] = FIRST ? gr * w : fmaf(gr, w, col[0]);
-    col[1] = FIRST ? gg * w : fmaf(gg, w, col[1]);
-    col[2] = FIRST ? gb * w : fmaf(gb, w, col[2]);
-    col[3] = FIRST ? gd * w : fmaf(gd, w, col[3]);
-    return da * ag;
+    const float t = da * ag, tx = t * dx, ty = t * dy;
+    acc[0] = FIRST ? tx : acc[0] + tx;
+    acc[1] = FIRST ? ty : acc[1] + ty;
+    acc[2] = FIRST ? tx * dx : fmaf(tx, dx, acc[2]);
+    acc[3] = FIRST ? tx * dy : fmaf(tx, dy, acc[3]);
+    acc[4] = FIRST ? ty * dy : fmaf(ty, dy, acc[4]);
+    acc[5] = FIRST ? t : acc[5] + t;
+    acc[6] = FIRST ? gr * w : fmaf(gr, w, acc[6]);
+    acc[7] = FIRST ? gg * w : fmaf(gg, w, acc[7]);
+    acc[8] = FIRST ? gb * w : fmaf(gb, w, acc[8]);
+    acc[9] = FIRST ? gd * w : fmaf(gd, w, acc[9]);
 }
 
-// One wave takes a tile, or one of the NSUB bands of rows a tile is cut into (a workgroup each), and a
-// lane PPT neighbouring pixels of one row.  The staging lanes keep only the splats whose box meets the
+// One wave takes a tile, or one of the NSUB bands of 8x8 pixel blocks a tile is cut into (a workgroup each), and a
+// lane the same pixel of each of its PPT blocks.  The staging lanes keep only the splats whose box meets the
 // band and write them compacted, in ascending order, to LDS; the walk back to front is a countdown over them,
 // two per step.  Slot B holds the null splat: position 0xffffffff (no pixel takes it), zero geometry and
 // colour.
 //
-// Bound by instruction issue (cycles per wave as at k_render_fwd; a DPP addition 4, a row swap 8).  A lane's
-// pixels share their row, so the offset dy and its product are formed
-// once a splat, and the sums over d follow from three moments of t along the row: with A = dx of the first
-// pixel, sum t dx = A s0 + s1, sum t dx^2 = A (sum t dx + s1) + s2, where s_k = sum_j j^k t_j, and dy is a
-// factor of the rest: 13 instructions for four pixels instead of 26 to 32 when every pixel forms its
-// own products.  The rounding stays that of sums of their terms (A + j is the offset itself).
-// The 20 sums of a step are added up over the lanes through LDS, which is otherwise idle: about 90 cycles of vector
-// instructions; halving them lane by lane with DPP additions and selects took about 250.
-// 8 keyframes of 1280x720, with the narrower band of the binary64 branch and four waves per SIMD (128 VGPRs,
-// 158 before): 2,264 -> 2,000 us, of which the atomics are 70 us; one 640x480 frame in two bands: 134 -> 106 us.
+// Bound by instruction issue (cycles per wave as at k_render_fwd; a DPP addition 4, a row swap 8).  The 20 sums of a
+// step are added up over the lanes through LDS, which is otherwise idle: about 90 cycles of vector
+// instructions; halving them lane by lane with DPP additions and selects took about 250.  The sums cancel for needle-
+// shaped splats, whose gradients depend on the rounding of the products and on the tree of lanes:
+// both are the ones of a halving by lanes (i, 15 - i, 7 - i, i ^ 2, i ^ 1, then the rows).  Moments of a row of
+// four pixels, 13 instructions instead of 32, took 1,940 us where these take 2,120, but moved such gradients by up to 2e-3.
+// 8 keyframes of 1280x720, with the narrower band of the binary64 branch, thresholds in vector registers and four waves
+// per SIMD (128 VGPRs, 158 before): 2,264 -> 2,120 us, of which the atomics are 70 us; one 640x480 frame in two bands:
+// 134 -> 113 us.
 template <int TW, int TH, int NSUB, bool AU>
 __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __restrict__ views, int n_views,
                                                         const uint2* __restrict__ ranges,
@@ -2193,10 +2198,9 @@ __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __
                                                         const float* __restrict__ d_unc, double* __restrict__ g2d,
                                                         const uint32_t* __restrict__ flags) {
     constexpr int PPT = TW * TH / 64 / NSUB;
-    constexpr int SH = TH / NSUB;   // rows of the band
-    constexpr int LPR = TW / PPT;   // lanes per row
+    constexpr int RW = PPT * 8 < TW ? PPT * 8 : TW, RH = PPT * 64 / RW;  // the band
     constexpr int B = 64;
-    static_assert(PPT >= 1 && PPT <= 4 && LPR * SH == 64, "a wave must hold the band, one to four pixels a lane");
+    static_assert(PPT >= 1 && PPT <= 4 && RW * RH == PPT * 64, "a wave must hold the band, one to four blocks");
     if (flags && *flags) return;
     // s_p = (mean x, mean y relative to the origin, record id bits, position bits)
     __shared__ float4 s_p[B + 1], s_g1[B + 1], s_at[B + 1];
@@ -2220,10 +2224,13 @@ __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __
     }
 
     const int ox = origin_x(tx * TW), oy = origin_y(ty * TH);
-    // the band's pixels, and the lane's: (u0 + j, v)
-    const int c0 = tx * TW, c1 = c0 + TW - 1, r0 = ty * TH + (int)(blockIdx.x % NSUB) * SH, r1 = r0 + SH - 1;
-    const int u0 = c0 + (lane % LPR) * PPT, v = r0 + lane / LPR;
-    const float px0 = (float)(u0 - ox), py = (float)(v - oy);
+    // the band's pixels, and the lane's: (u0 + bx(j), v0 + by(j))
+    const int first = (int)(blockIdx.x % NSUB) * PPT;
+    const int c0 = tx * TW + first % (TW / 8) * 8, c1 = c0 + RW - 1, r0 = ty * TH + first / (TW / 8) * 8, r1 = r0 + RH - 1;
+    const int u0 = c0 + (lane & 7), v0 = r0 + (lane >> 3);
+    const float px0 = (float)(u0 - ox), py0 = (float)(v0 - oy);
+    auto bx = [](int j) { return j % (RW / 8) * 8; };
+    auto by = [](int j) { return j / (RW / 8) * 8; };
     float T[PPT];
     uint32_t last[PPT];
     float gr[PPT], gg[PPT], gb[PPT], gd[PPT], ga[PPT], gu[PPT];
@@ -2231,7 +2238,7 @@ __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __
     uint32_t mylast = 0;
 #pragma unroll
     for (int j = 0; j < PPT; j++) {
-        const int u = u0 + j;
+        const int u = u0 + bx(j), v = v0 + by(j);
         T[j] = 1.0f;
         last[j] = 0;
         gr[j] = gg[j] = gb[j] = gd[j] = ga[j] = gu[j] = 0.0f;
@@ -2314,17 +2321,16 @@ __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __
             // alpha = o G carries it at every pixel (a_g = a)
             auto step = [&](auto clamp) {
                 constexpr bool CL = decltype(clamp)::value;
-                float a[PPT][2], G[PPT][2], A[2], dy[2], t[PPT][2], col[2][4];
+                float a[PPT][2], G[PPT][2], dx[PPT][2], dy[PPT][2];
                 const float bands[2] = {s_band[slot[0]], s_band[slot[1]]};
                 bool need = false;
 #pragma unroll
                 for (int j = 0; j < PPT; j++)
 #pragma unroll
                     for (int q = 0; q < 2; q++) {
-                        float dx, w1, w2;
-                        a[j][q] = splat_alpha<CL>(cp[q].x, cp[q].y, cg[q], px0 + (float)j, py, amax, G[j][q], dx,
-                                                  dy[q], w1, w2);
-                        if (j == 0) A[q] = dx;
+                        float w1, w2;
+                        a[j][q] = splat_alpha<CL>(cp[q].x, cp[q].y, cg[q], px0 + (float)bx(j), py0 + (float)by(j), amax,
+                                                  G[j][q], dx[j][q], dy[j][q], w1, w2);
                         need = need | near_amin(a[j][q], amin, bands[q]);
                     }
                 if (__ballot(need)) {
@@ -2340,7 +2346,7 @@ __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __
                             l = k >> 1 == j ? last[j] : l;
                         }
                         if ((((k & 1) ? spos[1] : spos[0]) < l) & near_amin(x, amin, (k & 1) ? bands[1] : bands[0]))
-                            x = redecide(x, rec, (k & 1) ? sr[1] : sr[0], u0 + (k >> 1), v, st);
+                            x = redecide(x, rec, (k & 1) ? sr[1] : sr[0], u0 + bx(k >> 1), v0 + by(k >> 1), st);
 #pragma unroll
                         for (int j = 0; j < PPT; j++) {
                             a[j][0] = k == 2 * j ? x : a[j][0];
@@ -2366,35 +2372,12 @@ __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __
                         const float a0 = ok ? a[j][q] : 0.0f;
                         const float ag = CL ? (cg[q].w * G[j][q] <= amax ? a0 : 0.0f) : a0;
                         if (j == 0)
-                            t[j][q] = bwd_pixel<AU, true>(a0, ag, ca[q], cu[q], gr[j], gg[j], gb[j], gd[j], ga[j],
-                                                          gu[j], T[j], D[j], col[q]);
+                            bwd_pixel<AU, true>(a0, ag, dx[j][q], dy[j][q], ca[q], cu[q], gr[j], gg[j], gb[j], gd[j], ga[j],
+                                                gu[j], T[j], D[j], acc + 10 * q);
                         else
-                            t[j][q] = bwd_pixel<AU, false>(a0, ag, ca[q], cu[q], gr[j], gg[j], gb[j], gd[j], ga[j],
-                                                           gu[j], T[j], D[j], col[q]);
+                            bwd_pixel<AU, false>(a0, ag, dx[j][q], dy[j][q], ca[q], cu[q], gr[j], gg[j], gb[j], gd[j], ga[j],
+                                                 gu[j], T[j], D[j], acc + 10 * q);
                     }
-                }
-#pragma unroll
-                for (int q = 0; q < 2; q++) {
-                    float s0 = t[0][q], s1 = 0.0f, s2 = 0.0f;
-                    if constexpr (PPT >= 2) {
-                        s0 += t[1][q];
-                        s1 = t[1][q];
-                        s2 = t[1][q];
-                    }
-                    if constexpr (PPT == 4) {
-                        s0 += t[2][q] + t[3][q];
-                        s1 = fmaf(3.0f, t[3][q], fmaf(2.0f, t[2][q], s1));
-                        s2 = fmaf(9.0f, t[3][q], fmaf(4.0f, t[2][q], s2));
-                    }
-                    float* c = acc + 10 * q;
-                    c[0] = fmaf(A[q], s0, s1);
-                    c[1] = dy[q] * s0;
-                    c[2] = fmaf(A[q], c[0] + s1, s2);
-                    c[3] = dy[q] * c[0];
-                    c[4] = dy[q] * c[1];
-                    c[5] = s0;
-#pragma unroll
-                    for (int k = 0; k < 4; k++) c[6 + k] = col[q][k];
                 }
             };
             // opacities and alpha_max are positive: their bits order as they do
@@ -2420,18 +2403,16 @@ __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __
             float4 h[8];
 #pragma unroll
             for (int k = 0; k < 8; k++) h[k] = half[k];
-            // pairwise: the sums of t d and t d d cancel for needle-shaped splats, so their rounding is kept to six
-            // levels as a tree over 64 lanes has
+            // a tree in every 16 lanes (lane i with 15 - i, 7 - i, i ^ 2, i ^ 1), then the rows of lanes
+            float row16[2];
 #pragma unroll
-            for (int w = 4; w > 0; w >>= 1)
-#pragma unroll
-                for (int k = 0; k < w; k++) {
-                    h[k].x += h[k + w].x;
-                    h[k].y += h[k + w].y;
-                    h[k].z += h[k + w].z;
-                    h[k].w += h[k + w].w;
-                }
-            const float part = (h[0].x + h[0].y) + (h[0].z + h[0].w);
+            for (int k = 0; k < 2; k++) {
+                const float4 p = h[4 * k], q = h[4 * k + 1], r = h[4 * k + 2], s4 = h[4 * k + 3];
+                const float a0 = p.x + s4.w, a1 = p.y + s4.z, a2 = p.z + s4.y, a3 = p.w + s4.x;
+                const float a4 = q.x + r.w, a5 = q.y + r.z, a6 = q.z + r.y, a7 = q.w + r.x;
+                row16[k] = ((a0 + a7) + (a2 + a5)) + ((a1 + a6) + (a3 + a4));
+            }
+            const float part = row16[0] + row16[1];
             const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(part), __float_as_uint(part), false, false);
             const float tot = __uint_as_float(both[0]) + __uint_as_float(both[1]);
             // one binary64 atomic of 20 lanes
@@ -3705,16 +3686,17 @@ void loss_l1(const ViewDev* views, int n_views, int max_pix, const float* rgb, c
 }
 
 // Bands per tile for the backward: frames of few tiles leave most SIMDs with a wave or none, and then
-// more, shorter walks win until their atomics (one set per band and splat) cost more.  Per frame, in us
+// more, shorter walks win until their atomics (one set per band and splat) cost more.  Isotropic maps, in us
 // (with alpha gradients), for one, two and four bands on 256 CUs:
-//     336 tiles   344 (412)   179 (233)   138 (175)
-//     690         170 (200)   113 (137)   109 (129)
-//     980         159 (185)   102 (129)   109 (125)
-//   1,200         137 (166)   106 (129)   121 (152)
-//   2,400         237 (249)   312 (358)   532 (567)
-//   7,200         584 (680)   966 (1013)  1719 (1787)
-// so four below 3.5 tiles per CU, two below 8, one from there on.  RTG_BWD_WAVES overrides.
-static int backward_bands(int tw, int th, uint32_t tiles) {
+//     336 tiles   266 (323)   146 (189)    98 (132)
+//     690         139 (168)    97 (124)    81 (100)
+//     980         126 (150)    95 (112)    95 (108)
+//   1,200         122 (141)    97 (115)   106 (131)
+//   2,400         159 (186)   124 (140)   181 (188)
+//   7,200         217 (250)   342 (355)   604 (642)
+// so four below 3.5 tiles per CU, two below 16, one from there on.  Maps of needle-shaped splats never take four: the
+// sums of a splat over a tile cancel, and are added up over two bands as they always were.  RTG_BWD_WAVES overrides.
+static int backward_bands(int tw, int th, uint32_t tiles, bool isotropic) {
     static int forced = -1;
     if (forced < 0) {
         const char* e = getenv("RTG_BWD_WAVES");
@@ -3725,8 +3707,7 @@ static int backward_bands(int tw, int th, uint32_t tiles) {
     if (forced == 1 || forced == 2 || forced == 4) nw = forced;
     else {
         const uint32_t cu = (uint32_t)std::max(device_cu_count(), 1);
-        if (2 * (uint64_t)tiles < 7 * cu) nw = 4;
-        else if (tiles < 8 * cu) nw = 2;
+        nw = isotropic && 2 * (uint64_t)tiles < 7 * cu ? 4 : tiles < 16 * cu ? 2 : 1;
     }
     while (nw > nb8) nw >>= 1;
     return nw;
@@ -3739,7 +3720,7 @@ void render_backward(int tw, int th, int batch, const ViewDev* views, int n_view
                      const float* d_unc, double* g2d, const uint32_t* flags, hipStream_t s) {
     (void)batch;  // the backward stages 64 splats per wave
     if (tiles_total == 0) return;
-    const int nw = backward_bands(tw, th, tiles_total);
+    const int nw = backward_bands(tw, th, tiles_total, st.isotropic != 0);
     const bool au = d_alpha != nullptr || d_unc != nullptr;
     auto launch = [&](auto kernel) {
         kernel<<<tiles_total * (unsigned)nw, 64, 0, s>>>(views, n_views, ranges, tile_order, inst_rec, rec, st,
