@@ -59,8 +59,8 @@ HBM_PEAK = 8.0e12
 # (fetch x2.0, write x1.0); valid only for the kernel source they were taken on
 # (sha256 of rtg_kernels.hip).
 TRAFFIC = {
-    "render_backward": (208829.0 * 2.0 * 1024 + 712236.0 * 1024,
-                        "ff30b1a24fd69bfd0d4cb859a9073a5618f88bd7beecc9b1048a76a48d48022e"),
+    "render_backward": (236550.0 * 2.0 * 1024 + 837349.6 * 1024,
+                        "14d3aa3297a6e34601d0ac37647f2bf7703090850654140bfc76b0e2cee9f7c2"),
 }
 
 SECTIONS = ("c4", "c2", "c1", "c3", "c5", "utility", "bookkeeping", "collision")
@@ -409,8 +409,8 @@ def main():
 
     # ------------------------------------------------------- collision check
     # 3M Gaussians over a 40 m x 40 m lot; one 5 m motion primitive of 129
-    # points, and a tree layer of 64 such primitives; every point against
-    # every Gaussian.  The pair loop issues 15 VALU instructions per pair.
+    # points, and a tree layer of 64 such primitives; every point is decided
+    # against every Gaussian (pairs), most of them in groups.
     collision = None
     if "collision" in only:
         glot = scenes.lot_scene()
@@ -424,7 +424,6 @@ def main():
             hit, _ = raster.collision_check(ctx, gl, pl, 0.25, 3.0)
             pairs = float(nl) * npt
             collision[name] = {"points": npt, "us": round(t * 1e6, 1), "Gpairs_per_s": round(pairs / t / 1e9, 1),
-                               "alu_frac": round(pairs * 15 / t / ALU_PEAK_OPS, 3),
                                "collisions": int(hit.sum().item())}
         log(f"collision: {collision}")
 

@@ -1,5 +1,5 @@
 // Internal declarations shared by the gfx950 kernels (rtg_kernels.hip) and the
-// host runtime behind the C ABI (rtg_abi.cpp).
+// host runtime behind the C ABI (rtg_abi.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -3133,7 +3133,7 @@ __global__ __launch_bounds__(UT_THREADS, 4) void k_view_utility(GaussDev g, cons
 #pragma unroll
                 for (int k = 0; k < UT_CHUNK; k++) add_where(vis[k], cnt[q0 + k], d.x, su[q0 + k], du);
             }
-            // the undecided tests of this round, a pair (Gaussian, view) per lane; rare, so they go to
+            // the undecided tests of this turn, a pair (Gaussian, view) per lane; rare, so they go to
             // the block's sums one by one
             if (nask == 0) continue;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
