@@ -30,24 +30,28 @@ def _scene(n, seed, w, h):
     return g, cams
 
 
-# 16x16 tiles on 256 CUs: 4 bands below 896 tiles, 2 below 2,048, then 1; 8x8 tiles have one band
+# on 256 CUs: 2 bands below 4,096 tiles (isotropic maps: 4 below 896), then 1; 8x8 tiles have one band
 @pytest.mark.parametrize("au", [False, True])
-@pytest.mark.parametrize("tile,w,h,views,n,amin", [((16, 16), 33, 17, 1, 60, 1 / 255), ((16, 16), 567, 441, 1, 400, 0.02),
-                                                   ((32, 8), 289, 130, 2, 300, 1 / 255), ((32, 8), 573, 433, 1, 400, 1e-4),
-                                                   ((16, 16), 477, 381, 3, 400, 1 / 255), ((32, 8), 477, 381, 3, 400, 0.02),
-                                                   ((8, 8), 61, 47, 2, 200, 0.1)])
-def test_backward_bands(au, tile, w, h, views, n, amin):
+@pytest.mark.parametrize("iso,tile,w,h,views,n,amin", [(0, (16, 16), 33, 17, 1, 60, 1 / 255), (0, (16, 16), 567, 441, 1, 400, 0.02),
+                                                       (0, (32, 8), 289, 130, 2, 300, 1 / 255), (0, (32, 8), 573, 433, 1, 400, 1e-4),
+                                                       (0, (16, 16), 477, 381, 6, 400, 1 / 255), (0, (32, 8), 477, 381, 6, 400, 0.02),
+                                                       (0, (8, 8), 61, 47, 2, 200, 0.1), (1, (16, 16), 33, 17, 1, 60, 1 / 255),
+                                                       (1, (32, 8), 289, 130, 2, 300, 0.02), (1, (16, 16), 567, 441, 1, 400, 1 / 255)])
+def test_backward_bands(au, iso, tile, w, h, views, n, amin):
     from paper_2409_18122_amd import raster
-    print(f"bands au={au} tile={tile} {w}x{h} views={views} n={n} alpha_min={amin:.4g}", flush=True)
+    print(f"bands au={au} iso={iso} tile={tile} {w}x{h} views={views} n={n} alpha_min={amin:.4g}", flush=True)
     g, cams = _scene(n, n + w, w, h)
+    if iso:
+        g = scenes.isotropic_scene(g)
     cams = [scenes.make_camera(w, h, cams[0]["fx"], cams[0]["fy"], cams[0]["cx"] + 3.0 * v, cams[0]["cy"] - 2.0 * v)
             for v in range(views)]
-    s = _settings(tile, amin)
+    s = dict(_settings(tile, amin), isotropic=iso)
     f = raster.Frame(raster.Context(0), raster.to_device(g), cams, s)
     f.bin_sort()
     imgs = raster.unpack_images(f.render(), cams)
     rng = np.random.default_rng(3)
-    ref = {k: np.zeros_like(np.asarray(g[k], np.float64)) for k in ("means", "log_scales", "quats", "opacity", "colors")}
+    ref = {k: np.zeros((rows, n)) for k, rows in (("means", 3), ("log_scales", 3), ("quats", 4), ("colors", 3))}
+    ref["opacity"] = np.zeros(n)
     touched = np.zeros(n, bool)
     planes = [[], [], [], []]
     pairs = slack = 0
@@ -67,6 +71,10 @@ def test_backward_bands(au, tile, w, h, views, n, amin):
     assert abs(f.stats()["contrib_pairs"] - pairs) <= slack
     p = [torch.as_tensor(np.concatenate(x)).cuda() for x in planes]
     got = grads_to_numpy(f.backward(p[0], p[1], p[2] if au else None, p[3] if au else None))
+    if iso:  # one log-radius (the oracle leaves its gradient in the first row), no quaternion
+        assert "quats" not in got
+        ref["log_scales"], ref["quats"], got["quats"] = ref["log_scales"][:1], np.zeros((4, n)), np.zeros((4, n))
+        got["log_scales"] = got["log_scales"].reshape(1, n)
     ok = {k: np.where(touched, 0.0, x) for k, x in got.items()}
     rel = grad_rel_errors(ok, {k: np.where(touched, 0.0, x) for k, x in ref.items()})
     assert all(e <= GRAD_REL_TOL for e in rel.values()), rel
