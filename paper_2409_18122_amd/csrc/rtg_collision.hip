@@ -359,6 +359,8 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
             float b = r_robot;
             if (CLR) b = x == x ? clearance[P.index[at]] : -CC_INF;
             s_pt[gr * 64 + lane] = make_float4(x, y, z, b);
+            // -inf where lambda_g r overflows: finite, so that the reach is no NaN and such a Gaussian still passes
+            b = fmaxf(b, -3e38f);
             float4 sub = P.sub[at / 8];
             ball = P.ball[at / 64];
             for (int o = 1; CLR && o < 8; o <<= 1) b = fmaxf(b, __shfl_xor(b, o, 64));
