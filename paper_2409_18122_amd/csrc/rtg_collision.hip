@@ -22,14 +22,16 @@ namespace {
 // Gaussian can matter to a point only if it lies within the point's clearance.  So:
 //   k_cc_points puts the points of a batch in spatial order and covers every 64 of them (one per
 //     lane) with a ball (c, R);
-//   k_cc_bound gives every point an upper bound of its clearance from a strided sample of the map;
+//   k_cc_bound gives every point an upper bound of its clearance from a strided sample of the map, above the
+//     exact clearance of the pair that sets it by more than every rounding;
 //   k_cc_check streams the map once per slab of points: a lane takes a Gaussian and tests it against the
 //     balls; one that is nearer to c than R + w + the largest bound of the group's points is tested
 //     against the group's 64 points, a point per lane.
-// What is left out is further from all 64 points than a clearance that some pair reaches, so it
-// neither sets a minimum nor (where the clearance is below r_robot, that pair collides itself) a
-// flag: the results do not depend on the grouping.  Points far apart or in no order cost
-// more tests, at worst all pairs.
+// What is left out is further from all 64 points than the bounds, so it sets no minimum; and no flag that the
+// pair of the bound does not set too, since that pair's exact clearance is the smaller one and it is always
+// tested itself.  So the results do not depend on the grouping.  (A binary32 clearance would not do as
+// the bound: that of an axis of 100 m is off by 1e-5 m, and its pair may miss a point that it seems to hold.)
+// Points far apart or in no order cost more tests, at worst all pairs.
 // Flags are decided in binary32 outside a relative CC_BAND of the bound, inside it in
 // binary64 (from the original parameters, in the oracle's order).  A clearance is a minimum of
 // binary32 values (the hardware square root, within an ulp), the same in every order.
@@ -57,6 +59,7 @@ constexpr int CK_UNROLL = 4;  // balls tested per branch
 // batch's finite points hold NaN coordinates, which no comparison passes.
 struct CcPoints {
     float *x, *y, *z;
+    float* ub;  // bound of the clearance (k_cc_bound)
     uint32_t* index;
     float4 *ball, *sub;  // per 64 and per 8 points: centre, radius (NaN centre: no finite point)
 };
@@ -219,6 +222,8 @@ __global__ __launch_bounds__(CP_THREADS) void k_cc_points(const float* __restric
         P.index[at] = (uint32_t)(begin + tid + k * CP_THREADS);
     }
     const float nan = __builtin_nanf("");
+    if (clearance)
+        for (int i = tid; i < per; i += CP_THREADS) P.ub[begin + i] = CC_INF;
     for (uint32_t i = total + tid; i < (uint32_t)per; i += CP_THREADS) {
         P.x[begin + i] = nan;
         P.y[begin + i] = nan;
@@ -257,9 +262,10 @@ __global__ __launch_bounds__(CP_THREADS) void k_cc_points(const float* __restric
 // sample (sample s is Gaussian s n / m), staged 256 at a time.  Each LDS read of a Gaussian serves PPL
 // tests; below 16,384 points one test each, which gives four times as many waves (8,256 points and
 // 4,096 Gaussians: 18 us, against 22 us with PPL = 4).
+// The bound is d (1 + 1e-6) - w (1 - 1e-6): d is off by a relative 3.6e-7 at most (its differences, sum and root), w and the
+// result by 6e-8.  An axis beyond binary32 counts as 3e38, so the bound is finite wherever d is.
 template <int PPL>
-__global__ __launch_bounds__(256) void k_cc_bound(GaussDev g, int m, int per, float lambda_g, CcPoints P, int npad,
-                                                  float* __restrict__ clearance) {
+__global__ __launch_bounds__(256) void k_cc_bound(GaussDev g, int m, int per, float lambda_g, CcPoints P, int npad) {
     __shared__ float4 s_c[256];
     const float nan = __builtin_nanf("");
     float px[PPL], py[PPL], pz[PPL], best[PPL];
@@ -280,6 +286,8 @@ __global__ __launch_bounds__(256) void k_cc_bound(GaussDev g, int m, int per, fl
             const float v[6] = {g.means[i],      g.means[g.n + i],      g.means[2 * g.n + i],
                                 g.log_scales[i], g.log_scales[g.n + i], g.log_scales[2 * g.n + i]};
             c = cc_gauss(v, lambda_g);
+            if (c.w == CC_INF) c.w = 3e38f;
+            c.w *= 0.999999f;
         }
         s_c[threadIdx.x] = c;
         __syncthreads();
@@ -290,14 +298,14 @@ __global__ __launch_bounds__(256) void k_cc_bound(GaussDev g, int m, int per, fl
             for (int k = 0; k < PPL; k++) {
                 const float dx = px[k] - q.x, dy = py[k] - q.y, dz = pz[k] - q.z;
                 const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                best[k] = fminf(best[k], __builtin_amdgcn_sqrtf(d2) - q.w);
+                best[k] = fminf(best[k], fmaf(__builtin_amdgcn_sqrtf(d2), 1.000001f, -q.w));
             }
         }
     }
 #pragma unroll
     for (int k = 0; k < PPL; k++) {  // a place past the points has found nothing
         const int j = (blockIdx.x * PPL + k) * 256 + threadIdx.x;
-        if (best[k] < CC_INF) atomic_min_float(&clearance[P.index[j]], best[k]);
+        if (best[k] < CC_INF) atomic_min_float(&P.ub[j], best[k]);
     }
 }
 
@@ -341,7 +349,7 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
                                                          float* clearance) {
     extern __shared__ float4 s_all[];
     const int ngp = (gps + CK_UNROLL - 1) / CK_UNROLL * CK_UNROLL;  // ck_lds_bytes
-    float4* s_pt = s_all;             // x, y, z and the least clearance so far
+    float4* s_pt = s_all;             // x, y, z and the least clearance so far, at first its bound
     float4* s_sub = s_pt + ngp * 64;  // balls of 8 points: centre and reach (radius + bound)
     float4* s_ball = s_sub + ngp * 8;  // of 64
     unsigned long long* s_hit = reinterpret_cast<unsigned long long*>(s_ball + ngp);
@@ -349,7 +357,7 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g0 = blockIdx.y * gps, ng = min(gps, ngroups - g0);
     const float nan = __builtin_nanf("");
-    // a reach, widened by far more than the rounding of a distance
+    // a reach, widened by more than the rounding of the test (passes adds that of the Gaussian's own axis)
     auto reach_of = [](float r, float ub) { return (r + ub) + 1e-5f * (r + fabsf(ub)); };
     for (int gr = wv; gr < ngp; gr += CK_THREADS / 64) {
         float4 ball = make_float4(nan, nan, nan, 0.0f);
@@ -357,10 +365,8 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
             const int at = (g0 + gr) * 64 + lane;
             const float x = P.x[at], y = P.y[at], z = P.z[at];
             float b = r_robot;
-            if (CLR) b = x == x ? clearance[P.index[at]] : -CC_INF;
+            if (CLR) b = x == x ? P.ub[at] : -CC_INF;
             s_pt[gr * 64 + lane] = make_float4(x, y, z, b);
-            // -inf where lambda_g r overflows: finite, so that the reach is no NaN and such a Gaussian still passes
-            b = fmaxf(b, -3e38f);
             float4 sub = P.sub[at / 8];
             ball = P.ball[at / 64];
             for (int o = 1; CLR && o < 8; o <<= 1) b = fmaxf(b, __shfl_xor(b, o, 64));
@@ -524,7 +530,7 @@ size_t collision_ws_bytes(int64_t np) {
     if (np <= 0) return 256;
     // the largest set of launches; a smaller last one needs no more
     const CcBatches b(std::min(np, CC_MAX_POINTS));
-    return (size_t)b.groups * (64 * 16 + 9 * 16);
+    return (size_t)b.groups * (64 * 20 + 9 * 16);
 }
 
 void collision_check(const GaussDev& g, const float* pts, int64_t np_all, float r_robot, float lambda_g, void* ws,
@@ -539,7 +545,8 @@ void collision_check(const GaussDev& g, const float* pts, int64_t np_all, float 
         P.x = reinterpret_cast<float*>(P.sub + 8 * b.groups);
         P.y = P.x + npad;
         P.z = P.y + npad;
-        P.index = reinterpret_cast<uint32_t*>(P.z + npad);
+        P.ub = P.z + npad;
+        P.index = reinterpret_cast<uint32_t*>(P.ub + npad);
         int32_t* hit = collide + p0;
         float* clr = clearance ? clearance + p0 : nullptr;
         k_cc_points<<<b.blocks, CP_THREADS, 0, s>>>(pts + p0, np_all, np, b.per, P, hit, clr);
@@ -553,8 +560,8 @@ void collision_check(const GaussDev& g, const float* pts, int64_t np_all, float 
             const int gy = std::max(1, std::min(rounds, 1024 / gx));
             const int per = (rounds + gy - 1) / gy * 256;
             const dim3 grid((unsigned)gx, (unsigned)((m + per - 1) / per));
-            if (wide) k_cc_bound<4><<<grid, 256, 0, s>>>(g, m, per, lambda_g, P, npad, clr);
-            else k_cc_bound<1><<<grid, 256, 0, s>>>(g, m, per, lambda_g, P, npad, clr);
+            if (wide) k_cc_bound<4><<<grid, 256, 0, s>>>(g, m, per, lambda_g, P, npad);
+            else k_cc_bound<1><<<grid, 256, 0, s>>>(g, m, per, lambda_g, P, npad);
         }
         // slabs of equal numbers of groups, and blocks for about two rounds of the chip
         const int ny = (b.groups + CK_GROUPS - 1) / CK_GROUPS, gps = (b.groups + ny - 1) / ny;

@@ -210,7 +210,7 @@ void loss_ssim(const ViewDev* views, int n_views, int blocks_per_view, uint64_t 
                const float* depth, const float* trgb, const float* tdepth, float w_depth, float l1, float l2,
                float* maps, double* partial, float* d_rgb, float* d_depth, double* loss, hipStream_t s);
 // Collision check of np points (planar 3 x np) against the map; ws: scratch of
-// collision_ws_bytes(np) (about 16 bytes per point, at most 17 MiB), collide:
+// collision_ws_bytes(np) (about 22 bytes per point, at most 23 MiB), collide:
 // np int32 (required), clearance: np floats or NULL.
 size_t collision_ws_bytes(int64_t np);
 void collision_check(const GaussDev& g, const float* pts, int64_t np, float r_robot, float lambda_g, void* ws,
