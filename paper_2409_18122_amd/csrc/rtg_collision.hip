@@ -386,8 +386,9 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
     auto passes = [&](float4 b, float4 q) {
         const float dx = q.x - b.x, dy = q.y - b.y, dz = q.z - b.z;
         const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+        // below 0 where a bound lies deeper inside another Gaussian than this one is wide: nothing passes
         const float reach = fmaf(q.w, 1.00001f, b.w);
-        return d2 <= reach * reach;
+        return d2 <= reach * fabsf(reach);
     };
     // appends the entries of the lanes in m
     auto push = [&](uint16_t* queue, int& n, bool pass, uint64_t m, uint32_t entry) {
