@@ -278,6 +278,27 @@ struct ScreenView {
     float4 kx, ky;    // (cx, fx^2, (W - 1) / 2, slack in pixels), (cy, fy^2, (H - 1) / 2, min(fx, fy))
 };
 
+// Bounds hi and lo of the singular values of a camera's matrix, which may be any finite one, from the row sums
+// of R^T R; both 1 for a rotation (within 1e-3, which the screens' constants cover).
+__device__ __forceinline__ float2 camera_norms(const ViewDev& V) {
+    float hi = 0.0f, lo = INFINITY, off = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        float diag = 0.0f, rest = 0.0f;
+#pragma unroll
+        for (int b = 0; b < 3; b++) {
+            const float dot = V.Rf[a] * V.Rf[b] + V.Rf[3 + a] * V.Rf[3 + b] + V.Rf[6 + a] * V.Rf[6 + b];
+            if (a == b) diag = dot;
+            else rest += fabsf(dot);
+        }
+        off = fmaxf(off, fmaxf(fabsf(diag - 1.0f), rest));
+        hi = fmaxf(hi, diag + rest);
+        lo = fminf(lo, diag - rest);
+    }
+    if (off <= 1e-3f) return make_float2(1.0f, 1.0f);
+    return make_float2(sqrtf(hi) * 1.00001f, sqrtf(fmaxf(lo - 1e-5f * hi, 0.0f)) * 0.99999f);
+}
+
 __device__ __forceinline__ ScreenView screen_view(const ViewDev& V, const float* T0) {
     ScreenView f;
     double w[3];
@@ -297,17 +318,10 @@ __device__ __forceinline__ ScreenView screen_view(const ViewDev& V, const float*
     f.v = make_float4((float)Y[0], (float)Y[1], (float)Y[2], (float)Y[3]);
     f.z = make_float4((float)Z[0], (float)Z[1], (float)Z[2], (float)Z[3]);
     const float fx = fabsf(V.fxf), fy = fabsf(V.fyf), wx = (float)(V.W - 1), wy = (float)(V.H - 1);
-    // an R that is not a rotation, a field of view beyond 71 degrees to a side or far from square pixels would
-    // spoil the bounds: all pairs to binary64 then
-    bool plain = fx <= 2.0f * fy && fy <= 2.0f * fx && fmaxf(fabsf(V.cxf), fabsf(wx - V.cxf)) <= 3.0f * fx &&
-                 fmaxf(fabsf(V.cyf), fabsf(wy - V.cyf)) <= 3.0f * fy;
-#pragma unroll
-    for (int a = 0; a < 3; a++)
-#pragma unroll
-        for (int b = a; b < 3; b++) {
-            const float dot = V.Rf[a] * V.Rf[b] + V.Rf[3 + a] * V.Rf[3 + b] + V.Rf[6 + a] * V.Rf[6 + b];
-            plain = plain && fabsf(dot - (a == b ? 1.0f : 0.0f)) <= 1e-3f;
-        }
+    // a field of view beyond 71 degrees to a side or pixels far from square would spoil the bounds in the image: such
+    // a view's pairs are settled by the near plane alone
+    const bool plain = fx <= 2.0f * fy && fy <= 2.0f * fx && fmaxf(fabsf(V.cxf), fabsf(wx - V.cxf)) <= 3.0f * fx &&
+                       fmaxf(fabsf(V.cyf), fabsf(wy - V.cyf)) <= 3.0f * fy;
     const float slack = plain ? 0.05f + 4e-4f * fmaxf(fx + 2.0f * fabsf(V.cxf), fy + 2.0f * fabsf(V.cyf)) : INFINITY;
     f.kx = make_float4(V.cxf, fx * fx, 0.5f * wx, slack);
     f.ky = make_float4(V.cyf, fy * fy, 0.5f * wy, fminf(fx, fy));
@@ -317,7 +331,8 @@ __device__ __forceinline__ ScreenView screen_view(const ViewDev& V, const float*
 // What the screen knows of a Gaussian.  z is off by less than 3.5e-7 m, m = |offset|_1 + the largest |camera
 // offset|_1, and U, V by that times (f + |c|); err is 2e-6 m.  For z >= 1e3 err the pixel offset a - c is
 // then off by less than 2e-4 (f + 2 |c| + |a - c|) and the extent by less than a relative 1e-3: the
-// slack, 4e-4 |a - c| and 0.003 of the extent cover both.
+// slack, 4e-4 |a - c| and 0.003 of the extent cover both.  That holds for rotations; where a camera of
+// the batch has another matrix, err and hi are taken times the largest singular value and lo times the smallest.
 struct ScreenGauss {
     float dx, dy, dz;  // offset from the first camera's centre
     float hi, lo;      // bounds of rho s_max and rho s_min, rho^2 = 2 ln(o / alpha_min)
@@ -559,7 +574,8 @@ __global__ __launch_bounds__(NT, 4) void k_project_count_queued(GaussDev g, cons
     __shared__ ScreenView s_v[VIEWS];
     __shared__ uint32_t s_vis[VIEWS / 32][NT];
     __shared__ uint16_t s_q[NT / 64][64 * (PC_STEP + 1)];  // lane | view << 6
-    __shared__ uint32_t s_spread;           // bits of the largest |camera offset|_1
+    // bits of the largest |camera offset|_1 and of the cameras' largest and smallest singular value
+    __shared__ uint32_t s_spread, s_hi, s_lo;
     const int nv = (int)hdr->n_views;
     const int tid = threadIdx.x, wv = tid >> 6, lane = (int)lane_id();
     const int64_t i0 = (int64_t)blockIdx.x * NT + 64 * wv, i = i0 + lane;
@@ -569,18 +585,30 @@ __global__ __launch_bounds__(NT, 4) void k_project_count_queued(GaussDev g, cons
         for (int k = 0; k < 3; k++) T0[k] = views[0].Tf[k];
     ScreenGauss G{};
     const bool ok = i < g.n && screen_gauss(g, i, st, T0, G);
+    const float hi1 = G.hi, lo1 = G.lo;
     uint32_t c = 0;
     for (int base = 0; base < 32 * words; base += VIEWS) {
         const int lim = max(0, min(VIEWS, nv - base));
-        if (tid == 0) s_spread = 0u;
+        if (tid == 0) {
+            s_spread = s_hi = 0u;
+            s_lo = 0x7f800000u;
+        }
         __syncthreads();
         if (tid < lim) {
             const ViewDev& V = views[base + tid];
             s_v[tid] = screen_view(V, T0);
             atomicMax(&s_spread, __float_as_uint(fabsf(V.Tf[0] - T0[0]) + fabsf(V.Tf[1] - T0[1]) + fabsf(V.Tf[2] - T0[2])));
+            const float2 norms = camera_norms(V);
+            atomicMax(&s_hi, __float_as_uint(norms.x));
+            atomicMin(&s_lo, __float_as_uint(norms.y));
         }
         __syncthreads();
-        const float err = 2e-6f * (fabsf(G.dx) + fabsf(G.dy) + fabsf(G.dz) + __uint_as_float(s_spread));
+        const float norm = __uint_as_float(s_hi);
+        const float err = 2e-6f * norm * (fabsf(G.dx) + fabsf(G.dy) + fabsf(G.dz) + __uint_as_float(s_spread));
+        if (!st.isotropic) {  // the isotropic extent does not see the matrix
+            G.hi = hi1 * norm;
+            G.lo = lo1 * __uint_as_float(s_lo);
+        }
         G.zlo = st.z_near - err;
         G.zhi = fmaxf(st.z_near + err, 1e3f * err);
         uint32_t nq = 0;  // queued pairs of the wave
