@@ -123,23 +123,47 @@ __device__ inline bool pre_gauss(const GaussDev& g, int64_t i, const SetDev& st,
     return true;
 }
 
+// Bounds hi and lo of the singular values of a camera's matrix, which may be any finite one, from the row sums
+// of R^T R; both 1 for a rotation (within 1e-3, which the screens' constants cover).
+__device__ __forceinline__ float2 camera_norms(const ViewDev& V) {
+    float hi = 0.0f, lo = INFINITY, off = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        float diag = 0.0f, rest = 0.0f;
+#pragma unroll
+        for (int b = 0; b < 3; b++) {
+            const float dot = V.Rf[a] * V.Rf[b] + V.Rf[3 + a] * V.Rf[3 + b] + V.Rf[6 + a] * V.Rf[6 + b];
+            if (a == b) diag = dot;
+            else rest += fabsf(dot);
+        }
+        off = fmaxf(off, fmaxf(fabsf(diag - 1.0f), rest));
+        hi = fmaxf(hi, diag + rest);
+        lo = fminf(lo, diag - rest);
+    }
+    if (off <= 1e-3f) return make_float2(1.0f, 1.0f);
+    return make_float2(sqrtf(hi) * 1.00001f, sqrtf(fmaxf(lo - 1e-5f * hi, 0.0f)) * 0.99999f);
+}
+
 // Conservative binary32 test: false only if the exact binary64 projection is
 // certain to be culled (behind the near plane, or its support box cannot meet
 // the image).  The half extent of the support box is bounded through
-// Sigma_xx <= s_max^2 |J_row0|^2 = s_max^2 fx^2 / t_z^2 (1 + t_x^2 / t_z^2).
+// Sigma_xx <= s_max^2 |J_row0|^2 = s_max^2 fx^2 / t_z^2 (1 + t_x^2 / t_z^2), times the square of the largest
+// singular value of R where that is no rotation (the isotropic extent does not see R).
 // The binary32 camera values the test reads, packed in five 16-byte words:
-// the columns of R with the camera centre, (fx, fy, cx, cy), (W - 1, H - 1).
+// the columns of R with the camera centre, (fx, fy, cx, cy), (W - 1, H - 1,
+// the factors of the depth's error and of the extent).
 struct CullView {
     float4 c0, c1, c2, k, wh;
 };
 
-__device__ __forceinline__ CullView cull_view(const ViewDev& V) {
+__device__ __forceinline__ CullView cull_view(const ViewDev& V, const SetDev& st) {
     CullView f;
     f.c0 = make_float4(V.Rf[0], V.Rf[3], V.Rf[6], V.Tf[0]);
     f.c1 = make_float4(V.Rf[1], V.Rf[4], V.Rf[7], V.Tf[1]);
     f.c2 = make_float4(V.Rf[2], V.Rf[5], V.Rf[8], V.Tf[2]);
     f.k = make_float4(V.fxf, V.fyf, V.cxf, V.cyf);
-    f.wh = make_float4((float)(V.W - 1), (float)(V.H - 1), 0.0f, 0.0f);
+    const float norm = camera_norms(V).x;
+    f.wh = make_float4((float)(V.W - 1), (float)(V.H - 1), norm, st.isotropic ? 1.0f : norm);
     return f;
 }
 
@@ -149,7 +173,7 @@ __device__ inline bool may_be_visible(const GPre& P, const CullView& V, const Se
     float dz = P.mu_f[2] - V.c2.w;
     float mag = fabsf(dx) + fabsf(dy) + fabsf(dz) + 1.0f;
     float tz = dx * V.c2.x + dy * V.c2.y + dz * V.c2.z;
-    float err = 1e-5f * mag;
+    float err = 1e-5f * mag * V.wh.z;
     if (tz + err <= st.z_near) return false;
     if (tz <= 0.5f * st.z_near) return true;  // let the exact test decide
     float tx = dx * V.c0.x + dy * V.c0.y + dz * V.c0.z;
@@ -161,7 +185,8 @@ __device__ inline bool may_be_visible(const GPre& P, const CullView& V, const Se
     float fx = V.k.x, fy = V.k.y;
     float ax = fx * ux + V.k.z;
     float ay = fy * uy + V.k.w;
-    float rx = P.reach * fx * iz, ry = P.reach * fy * iz;
+    const float reach = P.reach * V.wh.w;
+    float rx = reach * fx * iz, ry = reach * fy * iz;
     const float ep = 2.0f * P.rho_f * st.eps2d + st.eps2d * P.rho2_f;
     float hx = __builtin_amdgcn_sqrtf(rx * rx * (1.0f + ux * ux) + ep);
     float hy = __builtin_amdgcn_sqrtf(ry * ry * (1.0f + uy * uy) + ep);
@@ -277,27 +302,6 @@ struct ScreenView {
     float4 u, v, z;   // coefficients of the offset from the first camera's centre, and the constant
     float4 kx, ky;    // (cx, fx^2, (W - 1) / 2, slack in pixels), (cy, fy^2, (H - 1) / 2, min(fx, fy))
 };
-
-// Bounds hi and lo of the singular values of a camera's matrix, which may be any finite one, from the row sums
-// of R^T R; both 1 for a rotation (within 1e-3, which the screens' constants cover).
-__device__ __forceinline__ float2 camera_norms(const ViewDev& V) {
-    float hi = 0.0f, lo = INFINITY, off = 0.0f;
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        float diag = 0.0f, rest = 0.0f;
-#pragma unroll
-        for (int b = 0; b < 3; b++) {
-            const float dot = V.Rf[a] * V.Rf[b] + V.Rf[3 + a] * V.Rf[3 + b] + V.Rf[6 + a] * V.Rf[6 + b];
-            if (a == b) diag = dot;
-            else rest += fabsf(dot);
-        }
-        off = fmaxf(off, fmaxf(fabsf(diag - 1.0f), rest));
-        hi = fmaxf(hi, diag + rest);
-        lo = fminf(lo, diag - rest);
-    }
-    if (off <= 1e-3f) return make_float2(1.0f, 1.0f);
-    return make_float2(sqrtf(hi) * 1.00001f, sqrtf(fmaxf(lo - 1e-5f * hi, 0.0f)) * 0.99999f);
-}
 
 __device__ __forceinline__ ScreenView screen_view(const ViewDev& V, const float* T0) {
     ScreenView f;
@@ -528,7 +532,7 @@ __global__ __launch_bounds__(256) void k_project_count(GaussDev g, const ViewDev
     // the cameras' test values, staged in LDS (every thread reads the same camera at a time)
     __shared__ CullView s_vf[PC_FEW];
     const int nv = min((int)hdr->n_views, PC_FEW);
-    if ((int)threadIdx.x < nv) s_vf[threadIdx.x] = cull_view(views[threadIdx.x]);
+    if ((int)threadIdx.x < nv) s_vf[threadIdx.x] = cull_view(views[threadIdx.x], st);
     __syncthreads();
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.n) return;

@@ -44,13 +44,13 @@ def check_records(g, cams, iso):
 
 
 @pytest.mark.parametrize("scale", [0.02, 1.0, 10.0, 100.0, 1000.0])
-@pytest.mark.parametrize("views,iso", [(40, False), (40, True)])
+@pytest.mark.parametrize("views,iso", [(40, False), (40, True), (20, False), (20, True)])
 def test_scaled_cameras_at_the_near_plane(views, iso, scale):
     print(f"scaled cameras views={views} scale={scale} iso={iso}", flush=True)
     check_records(*scaled_scene(scale, views), iso)
 
 
-@pytest.mark.parametrize("views,iso", [(40, False), (40, True)])
+@pytest.mark.parametrize("views,iso", [(40, False), (40, True), (20, False), (20, True)])
 def test_sheared_cameras(views, iso):
     print(f"sheared cameras views={views} iso={iso}", flush=True)
     rng = np.random.default_rng(views)
