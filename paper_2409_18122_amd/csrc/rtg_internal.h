@@ -132,8 +132,8 @@ void scan_u32(const uint32_t* in, uint32_t* out, const uint32_t* n_dev, uint32_t
               ScanWs ws, hipStream_t s, uint32_t* mirror = nullptr, uint32_t* chunk_g = nullptr, uint32_t rec_cap = 0);
 
 // Stable LSD radix sort of (key, value) pairs on bits [0, nbits) of the key; returns 1 if the result is in
-// (k1, v1), 0 if it is in (k0, v0).  With count, the values are the items' positions (v0 need not be filled) and
-// gout[i] = count[value at sorted position i].
+// (k1, v1), 0 if it is in (k0, v0).  With count, the values are the items' positions (v0 need not be filled),
+// gout[i] = count[value at sorted position i], k0 keeps its keys and the sorted ones are not written.
 struct SortWs {
     uint32_t* hist;     // sort_hist_words(cap) entries
 };

@@ -1118,7 +1118,7 @@ __global__ __launch_bounds__(NT, 4) void k_rs_scatter(const uint32_t* __restrict
             const uint32_t d = (kk >> shift) & mask;
             const uint32_t dst = bbase[d] + (i - lst[d]);
             uint32_t vv = s_v[i];
-            kout[dst] = kk;
+            if (kout) kout[dst] = kk;
             if (gout) {
                 uint32_t c = sat;
                 if (rc.pb < 32) {
@@ -3640,6 +3640,9 @@ int radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uin
     uint32_t *ki = k0, *vi = v0, *ko = k1, *vo = v1;
     int shift = 0;
     for (int p = 0; p < passes; p++) {
+        // with count k0 stays as it is (the same frame may be sorted again): the keys go by k1 and, until the last
+        // pass fills it, gout, and the last pass reads them from k1 and leaves them out
+        if (count) ko = p + 1 == passes ? nullptr : (passes - p) % 2 == 0 ? k1 : gout;
         const int bits = std::max(nbits / passes + (p < nbits % passes ? 1 : 0), 1);
         const uint32_t* vin = count && p == 0 ? nullptr : vi;
         uint32_t* go = p + 1 == passes ? gout : nullptr;
