@@ -32,11 +32,11 @@ namespace {
 // tested itself.  So the results do not depend on the grouping.  (A binary32 clearance would not do as
 // the bound: that of an axis of 100 m is off by 1e-5 m, and its pair may miss a point that it seems to hold.)
 // Points far apart or in no order cost more tests, at worst all pairs.
-// Flags are decided in binary32 outside a relative CC_BAND of the bound, inside it in
-// binary64 (from the original parameters, in the oracle's order).  A clearance is a minimum of
+// Flags are decided in binary32 outside a relative CC_BAND of the bound (r_robot + w)^2, which is formed in binary64
+// and rounded once, and inside it in binary64 (from the original parameters, in the oracle's order).  A clearance is a minimum of
 // binary32 values (the hardware square root, within an ulp), the same in every order.
 
-constexpr float CC_BAND = 5e-6f;  // relative band re-taken in binary64 (errors of d^2 and of the bound below 8e-7)
+constexpr double CC_BAND = 4e-6;  // relative band re-taken in binary64 (d^2 error < 4e-7)
 constexpr float CC_INF = __builtin_inff();
 
 // Points of a batch (one block of k_cc_points) and their spatial order: 2^CP_BITS bins, the box
@@ -82,14 +82,24 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
-// One Gaussian's mean and w = lambda_g r, formed in binary64 and rounded once; an ignored one (a
-// non-finite mean or log-scale) gets a NaN mean, which no comparison passes.
-__device__ __forceinline__ float4 cc_gauss(const float (&v)[6], float lambda_g) {
+// w = lambda_g r of one Gaussian, from its mean and log-scales.
+__device__ __forceinline__ double cc_axis(const float (&v)[6], float lambda_g) {
+    return (double)lambda_g * exp((double)fmaxf(fmaxf(v[3], v[4]), v[5]));
+}
+
+// Its mean and w, rounded once; an ignored one (a non-finite mean or log-scale) gets a NaN mean, which no
+// comparison passes.
+__device__ __forceinline__ float4 cc_gauss(const float (&v)[6], double w) {
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < 6; k++) ok = ok && isfinite(v[k]);
-    const double w = (double)lambda_g * exp((double)fmaxf(fmaxf(v[3], v[4]), v[5]));
     return make_float4(ok ? v[0] : __builtin_nanf(""), v[1], v[2], (float)w);
+}
+
+// The squared bound of its collisions, a band below and above.
+__device__ __forceinline__ float2 cc_band(double w, float r_robot) {
+    const double gm = (double)r_robot + w, g2 = gm * gm;
+    return make_float2((float)(g2 * (1.0 - CC_BAND)), (float)(g2 * (1.0 + CC_BAND)));
 }
 
 // Block b orders the points [b per, (b + 1) per) of the caller's planar arrays (stride np_all) and
@@ -285,7 +295,7 @@ __global__ __launch_bounds__(256) void k_cc_bound(GaussDev g, int m, int per, fl
             const int64_t i = (int64_t)(s + threadIdx.x) * g.n / m;
             const float v[6] = {g.means[i],      g.means[g.n + i],      g.means[2 * g.n + i],
                                 g.log_scales[i], g.log_scales[g.n + i], g.log_scales[2 * g.n + i]};
-            c = cc_gauss(v, lambda_g);
+            c = cc_gauss(v, cc_axis(v, lambda_g));
             if (c.w == CC_INF) c.w = 3e38f;
             c.w *= 0.999999f;
         }
@@ -409,7 +419,9 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
     int64_t base = (int64_t)blockIdx.x * CK_THREADS + wv * 64;
     if (base < g.n) fetch(base);
     for (; base < g.n; base += stride) {
-        float4 q = cc_gauss(raw, lambda_g);
+        const double w = cc_axis(raw, lambda_g);
+        float4 q = cc_gauss(raw, w);
+        const float2 band = cc_band(w, r_robot);
         if (base + lane >= g.n) q.x = nan;
         if (base + stride < g.n) fetch(base + stride);  // in flight during this step
         for (int gr0 = 0; gr0 < ng; gr0 += CK_UNROLL) {
@@ -455,10 +467,9 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
                         c.x = __shfl(q.x, src, 64);
                         c.y = __shfl(q.y, src, 64);
                         c.z = __shfl(q.z, src, 64);
-                        c.w = __shfl(q.w, src, 64);
+                        c.w = CLR ? __shfl(q.w, src, 64) : 0.0f;
+                        const float lo = __shfl(band.x, src, 64), hi = __shfl(band.y, src, 64);
                         wave_lds_fence();
-                        const float gm = r_robot + c.w, g2 = gm * gm;
-                        const float lo = g2 * (1.0f - CC_BAND), hi = g2 * (1.0f + CC_BAND);
                         uint32_t amb = 0;  // points in the band
                         if (lane < t2) {
 #pragma unroll
