@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rtg {
 
@@ -334,6 +335,114 @@ __device__ __forceinline__ bool collide64(const GaussDev& g, int64_t i, float px
     return d2 < gm * gm;
 }
 
+// Every point against every Gaussian, for maps too small for the grouping to pay (pairs_pay).  A block of 16 waves takes
+// 64 PPL points for every SPLIT waves, PPL per lane, and shares out the Gaussians between these waves, 1,024 at a time in
+// LDS; the shares' minima meet at the end, so one launch does it all.  Few points need the waves (SPLIT 16: a chain
+// a sixteenth as long); for many, two per lane halve the reads of LDS.  Bound by issue, with no branch but the one for
+// the rare step of CC_STEP Gaussians that holds a hit or a binary64 decision: a clearance costs 15 cycles (root,
+// difference, minimum), a test whether it is lower 11 and a branch that is taken often (2,000 Gaussians, 2^20 points:
+// 780 us with that branch, 634 without).  Two blocks a CU at 64 VGPRs (the binary64 decision spills five of them;
+// one block: 719 us).  100 Gaussians and 100,000 points 23 us, where the groups took 118 to 450 and a loop over all
+// pairs in four launches 31.
+constexpr int CC_STEP = 4;
+
+template <bool CLR, int SPLIT, int PPL>
+__global__ __launch_bounds__(CP_THREADS, 8) void k_cc_pairs(GaussDev g, float r_robot, float lambda_g,
+                                                         const float* __restrict__ pts, int64_t np,
+                                                         int32_t* __restrict__ collide, float* __restrict__ clearance) {
+    constexpr int WAVES = CP_THREADS / 64;
+    __shared__ float4 s_c[CP_THREADS];
+    __shared__ float s_hi[CP_THREADS], s_lo[CP_THREADS];
+    __shared__ float s_best[WAVES][PPL][64];
+    __shared__ uint32_t s_hit[WAVES][64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t j0 = ((int64_t)blockIdx.x * (WAVES / SPLIT) + wv / SPLIT) * (64 * PPL) + lane;
+    const float nan = __builtin_nanf("");
+    float px[PPL], py[PPL], pz[PPL], best[PPL];
+    bool hit[PPL];
+#pragma unroll
+    for (int p = 0; p < PPL; p++) {
+        const int64_t j = j0 + 64 * p;
+        px[p] = j < np ? pts[j] : nan;
+        py[p] = j < np ? pts[np + j] : nan;
+        pz[p] = j < np ? pts[2 * np + j] : nan;
+        best[p] = CC_INF;
+        hit[p] = false;
+    }
+    for (int64_t t0 = 0; t0 < g.n; t0 += CP_THREADS) {
+        __syncthreads();
+        float4 c = make_float4(nan, nan, nan, 0.0f);
+        float2 b = make_float2(0.0f, 0.0f);
+        if (t0 + tid < g.n) {
+            const int64_t i = t0 + tid;
+            const float v[6] = {g.means[i],      g.means[g.n + i],      g.means[2 * g.n + i],
+                                g.log_scales[i], g.log_scales[g.n + i], g.log_scales[2 * g.n + i]};
+            const double w = cc_axis(v, lambda_g);
+            c = cc_gauss(v, w);
+            b = cc_band(w, r_robot);
+        }
+        s_c[tid] = c;
+        s_lo[tid] = b.x;
+        s_hi[tid] = b.y;
+        __syncthreads();
+        // the wave's share, in whole steps (a step may reach into the next share or past the last Gaussian: no harm)
+        const int cnt = (int)min<int64_t>(CP_THREADS, g.n - t0);
+        const int per = (cnt + SPLIT * CC_STEP - 1) / (SPLIT * CC_STEP) * CC_STEP;
+        const int u0 = wv % SPLIT * per, u1 = min(u0 + per, cnt);
+        for (int u = u0; u < u1; u += CC_STEP) {
+            float d2[PPL][CC_STEP];
+            bool near = false;
+#pragma unroll
+            for (int k = 0; k < CC_STEP; k++) {
+                const float4 q = s_c[u + k];
+                const float hi = s_hi[u + k];
+#pragma unroll
+                for (int p = 0; p < PPL; p++) {
+                    const float dx = px[p] - q.x, dy = py[p] - q.y, dz = pz[p] - q.z;
+                    d2[p][k] = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                    near |= (d2[p][k] <= hi) & !hit[p];
+                    if (CLR) best[p] = fminf(best[p], __builtin_amdgcn_sqrtf(d2[p][k]) - q.w);
+                }
+            }
+            if (__ballot(near)) {
+#pragma unroll
+                for (int p = 0; p < PPL; p++)
+#pragma unroll
+                    for (int k = 0; k < CC_STEP; k++)
+                        if (!hit[p] && d2[p][k] <= s_hi[u + k])
+                            hit[p] = d2[p][k] < s_lo[u + k] ||
+                                     collide64(g, t0 + u + k, px[p], py[p], pz[p], r_robot, lambda_g);
+            }
+        }
+    }
+    if constexpr (SPLIT > 1) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int p = 0; p < PPL; p++) {
+            bits |= (uint32_t)hit[p] << p;
+            s_best[wv][p][lane] = best[p];
+        }
+        s_hit[wv][lane] = bits;
+        __syncthreads();
+        if (wv % SPLIT) return;
+#pragma unroll
+        for (int w = 1; w < SPLIT; w++) {
+            bits |= s_hit[wv + w][lane];
+#pragma unroll
+            for (int p = 0; p < PPL; p++) best[p] = fminf(best[p], s_best[wv + w][p][lane]);
+        }
+#pragma unroll
+        for (int p = 0; p < PPL; p++) hit[p] = bits >> p & 1u;
+    }
+#pragma unroll
+    for (int p = 0; p < PPL; p++) {
+        const int64_t j = j0 + 64 * p;
+        if (j >= np) continue;
+        collide[j] = hit[p];
+        if (CLR) clearance[j] = best[p];
+    }
+}
+
 // Orders a wave's LDS stores before its later LDS loads (its own lanes' queues below).
 __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -520,6 +629,14 @@ constexpr int64_t CC_MAX_POINTS = (int64_t)1 << 20;
 // average; four times as many cost 30 us more for 8,256 points and leave a tenth fewer pairs.
 constexpr int64_t CC_SAMPLE = 4096;
 
+// Whether all pairs in one launch beat the grouping, whose launches take 35 (129 points) to 100 us (8,256 and more) however
+// few the Gaussians: up to 8,192 of them while the pairs take no longer (2^28: 85 us; without clearances the groups
+// need less, 2^27).  More points than that keep the groups, which are faster by 2 where points lie close, from 2,048 Gaussians
+// on (2,000 and 2^20 points: 634 us here; scattered points take the groups 1,770).
+bool pairs_pay(int64_t n, int64_t np, bool clearance) {
+    return (n <= 8192 && n * np <= (clearance ? (int64_t)1 << 28 : (int64_t)1 << 27)) || (clearance && n <= 2048);
+}
+
 // LDS of k_cc_check for slabs of gps groups.
 size_t ck_lds_bytes(int gps) {
     const int ngp = (gps + CK_UNROLL - 1) / CK_UNROLL * CK_UNROLL;
@@ -547,6 +664,22 @@ size_t collision_ws_bytes(int64_t np) {
 
 void collision_check(const GaussDev& g, const float* pts, int64_t np_all, float r_robot, float lambda_g, void* ws,
                      int32_t* collide, float* clearance, hipStream_t s) {
+    if (pairs_pay(g.n, np_all, clearance != nullptr)) {
+        auto launch = [&](auto kernel, int64_t points) {
+            kernel<<<(unsigned)((np_all + points - 1) / points), CP_THREADS, 0, s>>>(g, r_robot, lambda_g, pts, np_all,
+                                                                                     collide, clearance);
+        };
+        // 64 points per block until that is two blocks a CU, then 256, then 1,024
+        auto split = [&](auto clr) {
+            constexpr bool CLR = decltype(clr)::value;
+            if (np_all < 32768) launch(k_cc_pairs<CLR, 16, 1>, 64);
+            else if (np_all < 262144) launch(k_cc_pairs<CLR, 8, 2>, 256);
+            else launch(k_cc_pairs<CLR, 2, 2>, 1024);
+        };
+        if (clearance) split(std::true_type{});
+        else split(std::false_type{});
+        return;
+    }
     for (int64_t p0 = 0; p0 < np_all; p0 += CC_MAX_POINTS) {
         const int np = (int)std::min(np_all - p0, CC_MAX_POINTS);
         const CcBatches b(np);
@@ -562,7 +695,6 @@ void collision_check(const GaussDev& g, const float* pts, int64_t np_all, float 
         int32_t* hit = collide + p0;
         float* clr = clearance ? clearance + p0 : nullptr;
         k_cc_points<<<b.blocks, CP_THREADS, 0, s>>>(pts + p0, np_all, np, b.per, P, hit, clr);
-        if (g.n <= 0) continue;
         if (clr) {
             const int m = (int)std::min<int64_t>(g.n, std::max<int64_t>(1024, std::min<int64_t>(CC_SAMPLE, g.n / 128)));
             const bool wide = npad >= 16384;  // enough points for 256 blocks with four per lane
