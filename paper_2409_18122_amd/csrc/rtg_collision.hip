@@ -32,7 +32,7 @@ namespace {
 // pair of the bound does not set too, since that pair's exact clearance is the smaller one and it is always
 // tested itself.  So the results do not depend on the grouping.  (A binary32 clearance would not do as
 // the bound: that of an axis of 100 m is off by 1e-5 m, and its pair may miss a point that it seems to hold.)
-// Points far apart or in no order cost more tests, at worst all pairs.
+// Points far apart or in no order cost more tests, at worst all pairs (check_dense).
 // Flags are decided in binary32 outside a relative CC_BAND of the bound (r_robot + w)^2, which is formed in binary64
 // and rounded once, and inside it in binary64 (from the original parameters, in the oracle's order).  A clearance is a minimum of
 // binary32 values (the hardware square root, within an ulp), the same in every order.
@@ -70,6 +70,12 @@ struct CcPoints {
 __device__ __forceinline__ void atomic_min_float(float* p, float v) {
     if (v >= 0.0f) atomicMin(reinterpret_cast<int*>(p), __float_as_int(v));
     else atomicMax(reinterpret_cast<unsigned*>(p), __float_as_uint(v));
+}
+
+// The next number above x (x never -0; infinity stays).
+__device__ __forceinline__ float next_up(float x) {
+    const int b = __float_as_int(x);
+    return x < CC_INF ? __int_as_float(b < 0 ? b - 1 : b + 1) : x;
 }
 
 __device__ __forceinline__ float wave_min(float v) {
@@ -271,7 +277,7 @@ __global__ __launch_bounds__(CP_THREADS) void k_cc_points(const float* __restric
 
 // Upper bounds of the clearances: 256 PPL ordered points of a block against `per` Gaussians of the
 // sample (sample s is Gaussian s n / m), staged 256 at a time.  Each LDS read of a Gaussian serves PPL
-// tests; below 16,384 points one test each, which gives four times as many waves (8,256 points and
+// tests; below 65,536 points one test each, which gives four times as many waves (8,256 points and
 // 4,096 Gaussians: 18 us, against 22 us with PPL = 4).
 // The bound is d (1 + 1e-6) - w (1 - 1e-6): d is off by a relative 3.6e-7 at most (its differences, sum and root), w and the
 // result by 6e-8.  An axis beyond binary32 counts as 3e38, so the bound is finite wherever d is.
@@ -335,17 +341,77 @@ __device__ __forceinline__ bool collide64(const GaussDev& g, int64_t i, float px
     return d2 < gm * gm;
 }
 
+// A tile of Gaussians in LDS: mean and w, and the band of the squared bound.
+struct CcTile {
+    float4* c;
+    float *lo, *hi;
+};
+
+// Gaussian i (past the last one: an ignored one) as the tile's entry at.
+__device__ __forceinline__ void stage_gauss(const GaussDev& g, int64_t i, float r_robot, float lambda_g, const CcTile& s,
+                                            int at) {
+    float4 c = make_float4(__builtin_nanf(""), 0.0f, 0.0f, 0.0f);
+    float2 b = make_float2(0.0f, 0.0f);
+    if (i < g.n) {
+        const float v[6] = {g.means[i],      g.means[g.n + i],      g.means[2 * g.n + i],
+                            g.log_scales[i], g.log_scales[g.n + i], g.log_scales[2 * g.n + i]};
+        const double w = cc_axis(v, lambda_g);
+        c = cc_gauss(v, w);
+        b = cc_band(w, r_robot);
+    }
+    s.c[at] = c;
+    s.lo[at] = b.x;
+    s.hi[at] = b.y;
+}
+
+// PPL points per lane against the tile's entries [u0, u1) in whole steps of CC_STEP (entry 0 is Gaussian `first`); hit: a
+// lane mask per point.  No branch but the one for the rare step that holds a hit or a binary64 decision: a clearance
+// costs 13 cycles (root, difference, half a minimum of three), a test whether it is lower 11 and a branch that is
+// taken often.  31 cycles a pair of 64 points.
+constexpr int CC_STEP = 4;
+
+template <bool CLR, int PPL>
+__device__ __forceinline__ void walk_pairs(const GaussDev& g, int64_t first, float r_robot, float lambda_g, const CcTile& s,
+                                           int u0, int u1, const float (&px)[PPL], const float (&py)[PPL],
+                                           const float (&pz)[PPL], float (&best)[PPL], uint64_t (&hit)[PPL]) {
+    for (int u = u0; u < u1; u += CC_STEP) {
+        float d2[PPL][CC_STEP];
+        uint64_t near[PPL] = {}, rare = 0;
+#pragma unroll
+        for (int k = 0; k < CC_STEP; k++) {
+            const float4 q = s.c[u + k];
+            const float hi = s.hi[u + k];
+#pragma unroll
+            for (int p = 0; p < PPL; p++) {
+                const float dx = px[p] - q.x, dy = py[p] - q.y, dz = pz[p] - q.z;
+                d2[p][k] = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                near[p] |= __ballot(d2[p][k] <= hi);
+                if (CLR) best[p] = fminf(best[p], __builtin_amdgcn_sqrtf(d2[p][k]) - q.w);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < PPL; p++) rare |= near[p] & ~hit[p];
+        if (rare) {
+#pragma unroll
+            for (int p = 0; p < PPL; p++) {
+                bool h = hit[p] >> (threadIdx.x & 63) & 1u;
+#pragma unroll
+                for (int k = 0; k < CC_STEP; k++)
+                    if (!h && d2[p][k] <= s.hi[u + k])
+                        h = d2[p][k] < s.lo[u + k] ||
+                            collide64(g, first + u + k, px[p], py[p], pz[p], r_robot, lambda_g);
+                hit[p] = __ballot(h);
+            }
+        }
+    }
+}
+
 // Every point against every Gaussian, for maps too small for the grouping to pay (pairs_pay).  A block of 16 waves takes
 // 64 PPL points for every SPLIT waves, PPL per lane, and shares out the Gaussians between these waves, 1,024 at a time in
 // LDS; the shares' minima meet at the end, so one launch does it all.  Few points need the waves (SPLIT 16: a chain
-// a sixteenth as long); for many, two per lane halve the reads of LDS.  Bound by issue, with no branch but the one for
-// the rare step of CC_STEP Gaussians that holds a hit or a binary64 decision: a clearance costs 15 cycles (root,
-// difference, minimum), a test whether it is lower 11 and a branch that is taken often (2,000 Gaussians, 2^20 points:
-// 780 us with that branch, 634 without).  Two blocks a CU at 64 VGPRs (the binary64 decision spills five of them;
-// one block: 719 us).  100 Gaussians and 100,000 points 23 us, where the groups took 118 to 450 and a loop over all
-// pairs in four launches 31.
-constexpr int CC_STEP = 4;
-
+// a sixteenth as long); for many, two per lane halve the reads of LDS.  Bound by issue.  Two blocks a CU at 64 VGPRs (the
+// binary64 decision spills five of them; one block: 719 us for 2,000 Gaussians and 2^20 points instead of 634).
+// 100 Gaussians and 100,000 points 23 us, where the groups took 118 to 450 and a loop over all pairs in four launches 31.
 template <bool CLR, int SPLIT, int PPL>
 __global__ __launch_bounds__(CP_THREADS, 8) void k_cc_pairs(GaussDev g, float r_robot, float lambda_g,
                                                          const float* __restrict__ pts, int64_t np,
@@ -353,13 +419,14 @@ __global__ __launch_bounds__(CP_THREADS, 8) void k_cc_pairs(GaussDev g, float r_
     constexpr int WAVES = CP_THREADS / 64;
     __shared__ float4 s_c[CP_THREADS];
     __shared__ float s_hi[CP_THREADS], s_lo[CP_THREADS];
+    const CcTile s{s_c, s_lo, s_hi};
     __shared__ float s_best[WAVES][PPL][64];
-    __shared__ uint32_t s_hit[WAVES][64];
+    __shared__ uint64_t s_hit[WAVES][PPL];
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t j0 = ((int64_t)blockIdx.x * (WAVES / SPLIT) + wv / SPLIT) * (64 * PPL) + lane;
     const float nan = __builtin_nanf("");
     float px[PPL], py[PPL], pz[PPL], best[PPL];
-    bool hit[PPL];
+    uint64_t hit[PPL];
 #pragma unroll
     for (int p = 0; p < PPL; p++) {
         const int64_t j = j0 + 64 * p;
@@ -367,78 +434,39 @@ __global__ __launch_bounds__(CP_THREADS, 8) void k_cc_pairs(GaussDev g, float r_
         py[p] = j < np ? pts[np + j] : nan;
         pz[p] = j < np ? pts[2 * np + j] : nan;
         best[p] = CC_INF;
-        hit[p] = false;
+        hit[p] = 0;
     }
     for (int64_t t0 = 0; t0 < g.n; t0 += CP_THREADS) {
         __syncthreads();
-        float4 c = make_float4(nan, nan, nan, 0.0f);
-        float2 b = make_float2(0.0f, 0.0f);
-        if (t0 + tid < g.n) {
-            const int64_t i = t0 + tid;
-            const float v[6] = {g.means[i],      g.means[g.n + i],      g.means[2 * g.n + i],
-                                g.log_scales[i], g.log_scales[g.n + i], g.log_scales[2 * g.n + i]};
-            const double w = cc_axis(v, lambda_g);
-            c = cc_gauss(v, w);
-            b = cc_band(w, r_robot);
-        }
-        s_c[tid] = c;
-        s_lo[tid] = b.x;
-        s_hi[tid] = b.y;
+        stage_gauss(g, t0 + tid, r_robot, lambda_g, s, tid);
         __syncthreads();
         // the wave's share, in whole steps (a step may reach into the next share or past the last Gaussian: no harm)
         const int cnt = (int)min<int64_t>(CP_THREADS, g.n - t0);
         const int per = (cnt + SPLIT * CC_STEP - 1) / (SPLIT * CC_STEP) * CC_STEP;
-        const int u0 = wv % SPLIT * per, u1 = min(u0 + per, cnt);
-        for (int u = u0; u < u1; u += CC_STEP) {
-            float d2[PPL][CC_STEP];
-            bool near = false;
-#pragma unroll
-            for (int k = 0; k < CC_STEP; k++) {
-                const float4 q = s_c[u + k];
-                const float hi = s_hi[u + k];
-#pragma unroll
-                for (int p = 0; p < PPL; p++) {
-                    const float dx = px[p] - q.x, dy = py[p] - q.y, dz = pz[p] - q.z;
-                    d2[p][k] = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                    near |= (d2[p][k] <= hi) & !hit[p];
-                    if (CLR) best[p] = fminf(best[p], __builtin_amdgcn_sqrtf(d2[p][k]) - q.w);
-                }
-            }
-            if (__ballot(near)) {
-#pragma unroll
-                for (int p = 0; p < PPL; p++)
-#pragma unroll
-                    for (int k = 0; k < CC_STEP; k++)
-                        if (!hit[p] && d2[p][k] <= s_hi[u + k])
-                            hit[p] = d2[p][k] < s_lo[u + k] ||
-                                     collide64(g, t0 + u + k, px[p], py[p], pz[p], r_robot, lambda_g);
-            }
-        }
+        const int u0 = wv % SPLIT * per;
+        walk_pairs<CLR, PPL>(g, t0, r_robot, lambda_g, s, u0, min(u0 + per, cnt), px, py, pz, best, hit);
     }
     if constexpr (SPLIT > 1) {
-        uint32_t bits = 0;
 #pragma unroll
         for (int p = 0; p < PPL; p++) {
-            bits |= (uint32_t)hit[p] << p;
+            if (lane == 0) s_hit[wv][p] = hit[p];
             s_best[wv][p][lane] = best[p];
         }
-        s_hit[wv][lane] = bits;
         __syncthreads();
         if (wv % SPLIT) return;
 #pragma unroll
-        for (int w = 1; w < SPLIT; w++) {
-            bits |= s_hit[wv + w][lane];
+        for (int w = 1; w < SPLIT; w++)
 #pragma unroll
-            for (int p = 0; p < PPL; p++) best[p] = fminf(best[p], s_best[wv + w][p][lane]);
-        }
-#pragma unroll
-        for (int p = 0; p < PPL; p++) hit[p] = bits >> p & 1u;
+            for (int p = 0; p < PPL; p++) {
+                hit[p] |= s_hit[wv + w][p];
+                best[p] = fminf(best[p], s_best[wv + w][p][lane]);
+            }
     }
 #pragma unroll
     for (int p = 0; p < PPL; p++) {
         const int64_t j = j0 + 64 * p;
         if (j >= np) continue;
-        collide[j] = hit[p];
+        collide[j] = (int32_t)(hit[p] >> lane & 1u);
         if (CLR) clearance[j] = best[p];
     }
 }
@@ -449,7 +477,52 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// grid: x over the Gaussians (a block takes every gridDim.x-th step), y over slabs of `gps` groups.
+// Whether a block's minimum for place `at` is worth an atomic: no Gaussian above the point's bound is its nearest, the one
+// that set the bound is in some block, and most blocks hold none below it.
+__device__ __forceinline__ bool lower(float v, const CcPoints& P, int at, float found) {
+    return v < next_up(P.ub[at]) && v < found;
+}
+
+// All pairs of a block's Gaussians (every gridDim.x-th step) and its slab of ng groups from g0: a wave takes four
+// groups, a point of each per lane, and where that leaves waves over they share the Gaussians.
+template <bool CLR>
+__device__ __forceinline__ void check_dense(const GaussDev& g, float r_robot, float lambda_g, const CcPoints& P, int g0,
+                                            int ng, float4* lds, int32_t* collide, float* clearance) {
+    constexpr int PPL = 4;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const CcTile s{lds, reinterpret_cast<float*>(lds + CK_THREADS), reinterpret_cast<float*>(lds + CK_THREADS) + CK_THREADS};
+    const int units = (ng + PPL - 1) / PPL, split = CK_THREADS / 64 / units, share = wv / units;
+    const float nan = __builtin_nanf("");
+    float px[PPL], py[PPL], pz[PPL], best[PPL];
+    uint64_t hit[PPL];
+#pragma unroll
+    for (int p = 0; p < PPL; p++) {
+        const int gr = wv % units * PPL + p, at = (g0 + gr) * 64 + lane;
+        px[p] = gr < ng ? P.x[at] : nan;
+        py[p] = gr < ng ? P.y[at] : nan;
+        pz[p] = gr < ng ? P.z[at] : nan;
+        best[p] = CC_INF;
+        hit[p] = 0;
+    }
+    for (int64_t t0 = (int64_t)blockIdx.x * CK_THREADS; t0 < g.n; t0 += (int64_t)gridDim.x * CK_THREADS) {
+        __syncthreads();
+        stage_gauss(g, t0 + tid, r_robot, lambda_g, s, tid);
+        __syncthreads();
+        const int cnt = (int)min<int64_t>(CK_THREADS, g.n - t0);
+        const int per = (cnt + split * CC_STEP - 1) / (split * CC_STEP) * CC_STEP;
+        const int u0 = share * per;  // none for the waves past the shares
+        if (share < split) walk_pairs<CLR, PPL>(g, t0, r_robot, lambda_g, s, u0, min(u0 + per, cnt), px, py, pz, best, hit);
+    }
+#pragma unroll
+    for (int p = 0; p < PPL; p++) {
+        if (!(px[p] == px[p])) continue;
+        const uint32_t i = P.index[(g0 + wv % units * PPL + p) * 64 + lane];
+        if (hit[p] >> lane & 1u) collide[i] = 1;  // every writer writes 1
+        if (CLR && lower(best[p], P, (g0 + wv % units * PPL + p) * 64 + lane, clearance[i])) atomic_min_float(&clearance[i], best[p]);
+    }
+}
+
+// grid: x over the Gaussians (a block takes every gridDim.x-th step), y over slabs of `gps` groups (CkGrid).
 // CLR: the clearance is wanted; otherwise a group's reach is r_robot alone.
 //
 // A wave takes 64 Gaussians, one per lane, and tests them against the slab's balls of 64 points; a
@@ -460,6 +533,10 @@ __device__ __forceinline__ void wave_lds_fence() {
 // per lane) for each passing Gaussian took 931 us for 8,256 points and 3M Gaussians, with the queues 440 us.
 // Bound by instruction issue there (about 1.8e8 vector and 1.4e8 scalar wave instructions); for few points
 // by the one pass over the map (129 points, 3M Gaussians: 37 us, 1.9 TB/s).
+// Where points lie far from the map or from each other most pairs pass the balls, and 8 points of a queue's entry, read
+// from as many places of LDS, cost 65 cycles a pair of 64 lanes, where a plain walk costs 31: a block whose first Gaussians pass
+// more than half of the balls of 8 takes check_dense instead (8,256 points in a cube of 400 m: 12,400 -> 5,900 us, the
+// former loop over all pairs 7,600).
 // Slabs of 44 groups: 63 KB of LDS, two blocks of twelve waves a CU at 80 VGPRs (512 threads and 24
 // groups, which read the map twice as often: 533 us).
 template <bool CLR>
@@ -468,12 +545,14 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
                                                          float* clearance) {
     extern __shared__ float4 s_all[];
     const int ngp = (gps + CK_UNROLL - 1) / CK_UNROLL * CK_UNROLL;  // ck_lds_bytes
-    float4* s_pt = s_all;             // x, y, z and the least clearance so far, at first its bound
+    float4* s_pt = s_all;             // x, y, z and the least clearance so far, at first above its bound
     float4* s_sub = s_pt + ngp * 64;  // balls of 8 points: centre and reach (radius + bound)
     float4* s_ball = s_sub + ngp * 8;  // of 64
     unsigned long long* s_hit = reinterpret_cast<unsigned long long*>(s_ball + ngp);
     __shared__ uint16_t s_q1[CK_THREADS / 64][64 * (CK_UNROLL + 1)], s_q2[CK_THREADS / 64][128];
+    __shared__ uint32_t s_near;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (tid == 0) s_near = 0u;
     const int g0 = blockIdx.y * gps, ng = min(gps, ngroups - g0);
     const float nan = __builtin_nanf("");
     // a reach, widened by more than the rounding of the test (passes adds that of the Gaussian's own axis)
@@ -485,7 +564,7 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
             const float x = P.x[at], y = P.y[at], z = P.z[at];
             float b = r_robot;
             if (CLR) b = x == x ? P.ub[at] : -CC_INF;
-            s_pt[gr * 64 + lane] = make_float4(x, y, z, b);
+            s_pt[gr * 64 + lane] = make_float4(x, y, z, CLR ? next_up(b) : b);
             float4 sub = P.sub[at / 8];
             ball = P.ball[at / 64];
             for (int o = 1; CLR && o < 8; o <<= 1) b = fmaxf(b, __shfl_xor(b, o, 64));
@@ -516,7 +595,7 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
         n += (int)__popcll(m);
     };
     const int64_t stride = (int64_t)gridDim.x * CK_THREADS;
-    float raw[6];
+    float raw[6] = {nan, nan, nan, 0.0f, 0.0f, 0.0f};
     auto fetch = [&](int64_t i0) {
         const int64_t i = min(i0 + lane, g.n - 1);
 #pragma unroll
@@ -527,6 +606,21 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
     };
     int64_t base = (int64_t)blockIdx.x * CK_THREADS + wv * 64;
     if (base < g.n) fetch(base);
+    // two pairs of a Gaussian of the first step and a ball of 8 points per lane tell whether the balls sort anything out
+    // (1.5 us; up to 256 points the queues cost no more than the walk)
+    if (ngroups > 4) {
+        float4 q = cc_gauss(raw, cc_axis(raw, lambda_g));
+        if (base + lane >= g.n) q.x = nan;
+        uint32_t near = 0;
+        for (int t = 0; t < 2; t++) near += (uint32_t)__popcll(__ballot(passes(s_sub[(lane + 64 * t) * ng / 16], q)));
+        if (lane == 0) atomicAdd(&s_near, near);
+        __syncthreads();
+        const int64_t first = (int64_t)blockIdx.x * CK_THREADS;
+        if (s_near > (uint32_t)min<int64_t>(CK_THREADS, g.n - first)) {
+            check_dense<CLR>(g, r_robot, lambda_g, P, g0, ng, s_all, collide, clearance);
+            return;
+        }
+    }
     for (; base < g.n; base += stride) {
         const double w = cc_axis(raw, lambda_g);
         float4 q = cc_gauss(raw, w);
@@ -619,7 +713,7 @@ __global__ __launch_bounds__(CK_THREADS, 6) void k_cc_check(GaussDev g, float r_
         if (!(p.x == p.x)) continue;
         const uint32_t i = P.index[(g0 + gr) * 64 + lane];
         if ((s_hit[gr] >> lane) & 1ull) collide[i] = 1;  // every writer writes 1
-        if (CLR && p.w < clearance[i]) atomic_min_float(&clearance[i], p.w);
+        if (CLR && lower(p.w, P, (g0 + gr) * 64 + lane, clearance[i])) atomic_min_float(&clearance[i], p.w);
     }
 }
 
@@ -629,18 +723,21 @@ constexpr int64_t CC_MAX_POINTS = (int64_t)1 << 20;
 // average; four times as many cost 30 us more for 8,256 points and leave a tenth fewer pairs.
 constexpr int64_t CC_SAMPLE = 4096;
 
-// Whether all pairs in one launch beat the grouping, whose launches take 35 (129 points) to 100 us (8,256 and more) however
-// few the Gaussians: up to 8,192 of them while the pairs take no longer (2^28: 85 us; without clearances the groups
-// need less, 2^27).  More points than that keep the groups, which are faster by 2 where points lie close, from 2,048 Gaussians
-// on (2,000 and 2^20 points: 634 us here; scattered points take the groups 1,770).
+// Whether all pairs in one launch beat the grouping, whose launches take 35 (129 points) to 100 us (8,256) however few the
+// Gaussians, 170 (100,000 close by) to 350 (scattered): while the pairs take no longer (8.7e8: 240 us; without
+// clearances the groups need less, 2^27), and neither does a wave's chain (a sixteenth of the Gaussians; 8,192: 27 us).  More
+// points than that keep the groups, which are faster by 2 where points lie close, from 2,048 Gaussians on.
 bool pairs_pay(int64_t n, int64_t np, bool clearance) {
-    return (n <= 8192 && n * np <= (clearance ? (int64_t)1 << 28 : (int64_t)1 << 27)) || (clearance && n <= 2048);
+    if (!clearance) return n <= 8192 && n * np <= (int64_t)1 << 27;
+    if (n <= 8192) return n <= 2048 || n * np <= (int64_t)13 << 26;
+    return n <= 12288 && np >= 8192 && n * np <= (int64_t)1 << 29;
 }
 
 // LDS of k_cc_check for slabs of gps groups.
 size_t ck_lds_bytes(int gps) {
     const int ngp = (gps + CK_UNROLL - 1) / CK_UNROLL * CK_UNROLL;
-    return (size_t)ngp * ((64 + 8 + 1) * sizeof(float4) + sizeof(unsigned long long));
+    const size_t groups = (size_t)ngp * ((64 + 8 + 1) * sizeof(float4) + sizeof(unsigned long long));
+    return std::max(groups, CK_THREADS * (sizeof(float4) + 2 * sizeof(float)));  // check_dense's tile
 }
 
 // Batches of k_cc_points for np points: their number and (equal) size, whole groups.
@@ -650,6 +747,31 @@ struct CcBatches {
         blocks = (int)((np + CP_BATCH - 1) / CP_BATCH);
         per = (int)(((np + blocks - 1) / blocks + 63) / 64 * 64);
         groups = blocks * per / 64;
+    }
+};
+
+// Grid of k_cc_check: ny slabs of gps groups (numbers that check_dense deals out to twelve waves) and nx blocks over the
+// Gaussians.  512 blocks run at a time; the least of their rounds and turns is taken, in units of a group's tests
+// of a step: a step costs about two more, setting up and ending a block sixteen (their atomics too, so that more,
+// shorter blocks lose: 30,000 Gaussians and 100,000 points 250 us as 504 blocks, 374 as 1,440).
+struct CkGrid {
+    int gps = 0, ny = 0, nx = 0;
+    CkGrid(int groups, int64_t n) {
+        const int64_t steps = (n + CK_THREADS - 1) / CK_THREADS;
+        int64_t least = INT64_MAX;
+        for (int s : {CK_GROUPS, 24, 16, 12, 8, 4}) {
+            const int64_t slabs = (groups + s - 1) / s;
+            for (int r = 1; r <= 4; r++) {
+                const int64_t blocks = std::min<int64_t>(steps, std::max<int64_t>(1, 512 * r / slabs));
+                const int64_t rounds = (blocks * slabs + 511) / 512, turns = (steps + blocks - 1) / blocks;
+                const int64_t cost = rounds * (turns * (s + 2) + 16);
+                if (cost >= least) continue;
+                least = cost;
+                gps = s;
+                ny = (int)slabs;
+                nx = (int)blocks;
+            }
+        }
     }
 };
 
@@ -697,7 +819,7 @@ void collision_check(const GaussDev& g, const float* pts, int64_t np_all, float 
         k_cc_points<<<b.blocks, CP_THREADS, 0, s>>>(pts + p0, np_all, np, b.per, P, hit, clr);
         if (clr) {
             const int m = (int)std::min<int64_t>(g.n, std::max<int64_t>(1024, std::min<int64_t>(CC_SAMPLE, g.n / 128)));
-            const bool wide = npad >= 16384;  // enough points for 256 blocks with four per lane
+            const bool wide = npad >= 65536;  // enough points for 256 blocks with four per lane
             const int gx = (npad + (wide ? 1023 : 255)) / (wide ? 1024 : 256);
             // about 1,024 blocks, each with whole rounds of 256 Gaussians
             const int rounds = (m + 255) / 256;
@@ -707,14 +829,11 @@ void collision_check(const GaussDev& g, const float* pts, int64_t np_all, float 
             if (wide) k_cc_bound<4><<<grid, 256, 0, s>>>(g, m, per, lambda_g, P, npad);
             else k_cc_bound<1><<<grid, 256, 0, s>>>(g, m, per, lambda_g, P, npad);
         }
-        // slabs of equal numbers of groups, and blocks for about two rounds of the chip
-        const int ny = (b.groups + CK_GROUPS - 1) / CK_GROUPS, gps = (b.groups + ny - 1) / ny;
-        const int64_t steps = (g.n + CK_THREADS - 1) / CK_THREADS;
-        const int nx = (int)std::min<int64_t>(steps, std::max(1, 512 / ny));
-        const dim3 grid((unsigned)nx, (unsigned)ny);
-        const size_t lds = ck_lds_bytes(gps);
-        if (clr) k_cc_check<true><<<grid, CK_THREADS, lds, s>>>(g, r_robot, lambda_g, P, b.groups, gps, hit, clr);
-        else k_cc_check<false><<<grid, CK_THREADS, lds, s>>>(g, r_robot, lambda_g, P, b.groups, gps, hit, clr);
+        const CkGrid k(b.groups, g.n);
+        const dim3 grid((unsigned)k.nx, (unsigned)k.ny);
+        const size_t lds = ck_lds_bytes(k.gps);
+        if (clr) k_cc_check<true><<<grid, CK_THREADS, lds, s>>>(g, r_robot, lambda_g, P, b.groups, k.gps, hit, clr);
+        else k_cc_check<false><<<grid, CK_THREADS, lds, s>>>(g, r_robot, lambda_g, P, b.groups, k.gps, hit, clr);
     }
 }
 

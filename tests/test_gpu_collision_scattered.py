@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,p", [(0, 65), (1, 1), (3, 64), (5, 65), (4, 32_767), (7, 32_768), (9, 262_143), (2, 262_145),
                                  (63, 1025), (1023, 1000), (1024, 4097), (1025, 300), (2048, 131), (2049, 8000),
-                                 (8192, 500), (8193, 500), (8192, 16_383), (8192, 16_385), (2047, 66_000), (2049, 133_000)])
+                                 (8192, 500), (8193, 500), (8192, 16_383), (8192, 16_385), (2047, 66_000), (2049, 133_000),
+                                 (12_288, 8192), (12_289, 8192), (40_000, 6000)])
 def test_all_pairs(n, p):
     print(f"collision all pairs n={n} p={p}", flush=True)
     rng = np.random.default_rng(n + p)
@@ -45,7 +46,8 @@ def test_all_pairs(n, p):
     check(hit[some], clr[some], ref_hit, ref_clr, sure, maybe, w_max(ls, 3.0))
 
 
-@pytest.mark.parametrize("n,p", [(1, 1 << 20), (100, 1000), (100, 100_000), (2000, 30_000), (8000, 8192)])
+@pytest.mark.parametrize("n,p", [(1, 1 << 20), (100, 1000), (100, 100_000), (2000, 30_000), (8000, 8192), (30_000, 4096),
+                                 (100_000, 8256), (3_000_000, 8256)])
 def test_scattered_points_cost_no_more_than_all_pairs(n, p):
     from paper_2409_18122_amd import raster
     rng = np.random.default_rng(n)
@@ -57,3 +59,24 @@ def test_scattered_points_cost_no_more_than_all_pairs(n, p):
     print(f"collision scattered n={n} p={p}: {us:.0f} us", flush=True)
     assert us < 100.0 + n * p / 2.5e6
     ctx.close()
+
+
+@pytest.mark.parametrize("n,p,spread", [(9000, 3000, 300.0), (20_000, 2817, 300.0), (100_000, 500, 1000.0), (70_000, 700, 60.0)])
+def test_scattered_points(n, p, spread):
+    """Blocks whose balls sort nothing out, and such ones beside others."""
+    print(f"collision scattered parity n={n} p={p}", flush=True)
+    rng = np.random.default_rng(n + p)
+    means = rng.uniform(-20, 20, (3, n)).astype(np.float32)
+    ls = rng.normal(-2.5, 0.6, (3, n)).astype(np.float32)
+    means[0, 5], ls[1, 6], ls[2, 7] = np.nan, np.inf, -np.inf
+    pts = rng.uniform(-spread, spread, (3, p)).astype(np.float32)
+    pts[:, :p // 3] = means[:, 10:10 + p // 3] + rng.uniform(-0.6, 0.6, (3, p // 3)).astype(np.float32)
+    pts[0, 7], pts[1, 70], pts[2, 130] = np.nan, np.inf, -np.inf
+    fin = np.isfinite(pts).all(0)
+    hit, clr = run(means, ls, pts)
+    hit2, _ = run(means, ls, pts, clearance=False, no_alloc=True)
+    assert np.array_equal(hit, hit2) and not hit[~fin].any() and np.all(np.isinf(clr[~fin]))
+    sub = np.ascontiguousarray(pts[:, fin])
+    ref_hit, ref_clr = oracle.collision(means, ls, sub, 0.25, 3.0)
+    sure, maybe = tie_bands(means, ls, sub, 0.25, 3.0)
+    check(hit[fin], clr[fin], ref_hit, ref_clr, sure, maybe, w_max(ls, 3.0))
