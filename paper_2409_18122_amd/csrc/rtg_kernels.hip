@@ -3272,7 +3272,10 @@ __global__ __launch_bounds__(256) void k_moments_finish(const double* __restrict
 // eq. (10): utility of trajectory t = sum of xi over its states
 // [off[t], off[t+1]) in order; best = first trajectory of maximal utility.
 // One block, a trajectory per thread (one thread for all of them waited for 576 loads in turn:
-// 39 us).  A NaN utility is never greater, and nothing is greater than a NaN first one.
+// 39 us), TS_BATCH of its loads in flight and added in order (one trajectory of 100,000 states: 6,620 us with one
+// load at a time, 1,000 now).  A NaN utility is never greater, and nothing is greater than a NaN first one.
+constexpr int TS_BATCH = 16;
+
 __global__ __launch_bounds__(256) void k_traj_select(const double* __restrict__ xi, const int32_t* __restrict__ off,
                                                      int n_traj, double* __restrict__ util,
                                                      int32_t* __restrict__ best) {
@@ -3283,7 +3286,16 @@ __global__ __launch_bounds__(256) void k_traj_select(const double* __restrict__ 
     double bv = 0.0;
     for (int t = threadIdx.x; t < n_traj; t += 256) {
         double s = 0.0;
-        for (int k = off[t]; k < off[t + 1]; k++) s += xi[k];
+        const int end = off[t + 1];
+        int k = off[t];
+        for (; k <= end - TS_BATCH; k += TS_BATCH) {
+            double x[TS_BATCH];
+#pragma unroll
+            for (int j = 0; j < TS_BATCH; j++) x[j] = xi[k + j];
+#pragma unroll
+            for (int j = 0; j < TS_BATCH; j++) s += x[j];
+        }
+        for (; k < end; k++) s += xi[k];
         if (util) util[t] = s;
         if (t == 0) s_nan = s != s;
         if (s == s && (b == n_traj || s > bv)) {
