@@ -380,7 +380,7 @@ struct rtg_frame {
     uint32_t* sorted_tkey() const { return inst_in_alt ? tkey2.as<uint32_t>() : tkey.as<uint32_t>(); }
     uint32_t* sorted_irec() const { return inst_in_alt ? irec2.as<uint32_t>() : irec.as<uint32_t>(); }
     uint32_t* ctr(int k) const { return counters.as<uint32_t>() + k; }
-    Buf n_contrib, stats, d_img;
+    Buf contrib, stats, d_img;
 };
 
 namespace {
@@ -731,7 +731,9 @@ rtg_status rtg_render(rtg_ctx* ctx, rtg_frame* f, float* rgb, float* depth, floa
         return set_err(RTG_ERR_INVALID, "unc requested but the map has no uncertainty");
     hipStream_t s = (hipStream_t)stream;
     RTG_TRY(ensure_pixel_state(f));
-    RenderOut o{rgb, depth, alpha, unc, f->T_final.as<float>(), f->n_last.as<uint32_t>(), nullptr};
+    const size_t words = contrib_words(f->st.tile_w, f->st.tile_h, f->L.hdr.tiles_total);
+    RTG_TRY(f->contrib.ensure(ctx, sizeof(uint64_t) * std::max<size_t>(words, 1)));
+    RenderOut o{rgb, depth, alpha, unc, f->T_final.as<float>(), f->n_last.as<uint32_t>(), f->contrib.as<uint64_t>()};
     Timer tm(ctx, 3, s);
     render_forward(f->st.tile_w, f->st.tile_h, f->st.batch, f->views.as<ViewDev>(), f->n_views,
                    f->L.hdr.tiles_total, f->ranges.as<uint2>(), f->tile_ord.as<uint32_t>(), f->sorted_irec(), f->records(), to_dev(f->st), o,
@@ -841,15 +843,8 @@ rtg_status rtg_frame_stats(rtg_ctx* ctx, rtg_frame* f, int64_t out[4], void* str
     hipStream_t s = (hipStream_t)stream;
     RTG_TRY(f->stats.ensure(ctx, 2 * sizeof(unsigned long long)));
     fill_u32(f->stats.as<uint32_t>(), 0u, 4, s);
-    // the contributors are counted here, by the forward's walk without its sums
-    RTG_TRY(f->n_contrib.ensure(ctx, 4 * (size_t)std::max<uint64_t>(f->L.hdr.pix_total, 1)));
-    RenderOut o{};
-    o.n_contrib = f->n_contrib.as<uint32_t>();
-    render_forward(f->st.tile_w, f->st.tile_h, f->st.batch, f->views.as<ViewDev>(), f->n_views, f->L.hdr.tiles_total,
-                   f->ranges.as<uint2>(), f->tile_ord.as<uint32_t>(), f->sorted_irec(), f->records(), to_dev(f->st), o,
-                   f->ctr(C_FLAGS), s);
-    sum_u32_pair(f->n_contrib.as<uint32_t>(), f->n_last.as<uint32_t>(), f->L.hdr.pix_total,
-                 f->stats.as<unsigned long long>(), s);
+    sum_counts(f->contrib.as<uint64_t>(), contrib_words(f->st.tile_w, f->st.tile_h, f->L.hdr.tiles_total),
+               f->n_last.as<uint32_t>(), f->L.hdr.pix_total, f->stats.as<unsigned long long>(), s);
     RTG_TRY(check_launch("frame stats"));
     unsigned long long h[2] = {0, 0};
     HIP_TRY(hipMemcpyAsync(ctx->pinned, f->stats.p, sizeof(h), hipMemcpyDeviceToHost, s));

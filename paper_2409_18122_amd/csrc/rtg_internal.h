@@ -164,11 +164,13 @@ struct RenderOut {
     float *rgb, *depth, *alpha, *unc;
     float* T_final;      // per pixel
     uint32_t* n_last;    // per pixel: list position after the last contributor
-    uint32_t* n_contrib; // per pixel: number of contributing splats (then nothing else is written)
+    uint64_t* contrib;   // per tile and wave of it (contrib_words): contributing splats of its pixels; null only without unc
 };
 
-// out[0] += sum a[i], out[1] += sum b[i] over i < n (64-bit).
-void sum_u32_pair(const uint32_t* a, const uint32_t* b, uint64_t n, unsigned long long* out, hipStream_t s);
+inline size_t contrib_words(int tw, int th, uint32_t tiles_total) { return (size_t)tiles_total * (size_t)(tw * th / 64); }
+
+// out[0] += sum a[i] over i < na, out[1] += sum b[i] over i < nb (64-bit).
+void sum_counts(const uint64_t* a, uint64_t na, const uint32_t* b, uint64_t nb, unsigned long long* out, hipStream_t s);
 void render_forward(int tw, int th, int batch, const ViewDev* views, int n_views,
                     uint32_t tiles_total, const uint2* ranges, const uint32_t* tile_order,
                     const uint32_t* inst_rec, Records rec, SetDev st, RenderOut out, const uint32_t* flags,

@@ -1913,7 +1913,8 @@ __device__ __forceinline__ float redecide(float a, const Records& rec, uint32_t 
 
 // B splats are staged per batch (B <= TW * TH; threads below B load them).
 // UNC: the uncertainty image is requested (otherwise it is not composited).
-// COUNT: only the number of contributing splats per pixel is wanted.
+// COUNT: the contributing splats are counted (out.contrib), per wave and by the scalar unit, whose two instructions
+// a splat cost 1 to 2 %; captured iterations, whose counts nobody can read, leave them out.
 //
 // Front to back over the wave's list, FWD_STEP splats per step: their alphas
 // are independent of the pixel state, the updates follow in order.  A pixel
@@ -1925,10 +1926,9 @@ __device__ __forceinline__ float redecide(float a, const Records& rec, uint32_t 
 //
 // Bound by instruction issue (cycles per wave: additions, products and their fusions 2; comparisons, selects,
 // minima and maxima, and anything with a scalar register 4; exp2 8).  So the thresholds sit in vector
-// registers, a batch whose splats are all at most alpha_max opaque leaves the clamp out, and the
-// contributors are counted only for the work counters.  8 keyframes of 1280x720, with the narrower band
-// of the binary64 branch and 64 instead of 80 VGPRs (eight waves per SIMD): 1,172 -> 1,027 us.
-template <int TW, int TH, int B, bool UNC, bool COUNT = false>
+// registers, and a batch whose splats are all at most alpha_max opaque leaves the clamp out.
+// 8 keyframes of 1280x720, with the narrower band of the binary64 branch and 64 instead of 80 VGPRs (eight waves per SIMD): 1,172 -> 1,027 us.
+template <int TW, int TH, int B, bool UNC, bool COUNT>
 __global__ __launch_bounds__(TW * TH, 8) void k_render_fwd(const ViewDev* __restrict__ views, int n_views,
                                                         const uint2* __restrict__ ranges,
                                                         const uint32_t* __restrict__ tile_order,
@@ -1940,12 +1940,12 @@ __global__ __launch_bounds__(TW * TH, 8) void k_render_fwd(const ViewDev* __rest
     static_assert(32 % TW == 0 && 16 % TH == 0, "tiles must divide the 32 x 16 origin block");
     static_assert(FWD_STEP == 2, "the list is padded for steps of two");
     if (flags && *flags) return;
-    __shared__ float4 s_p[B + 1], s_q[B + 1], s_at[COUNT ? 1 : B + 1];
+    __shared__ float4 s_p[B + 1], s_q[B + 1], s_at[B + 1];
     __shared__ uint32_t s_r[B + 1];
     __shared__ uint2 s_pb[B];
     __shared__ __align__(8) uint32_t s_list[NT / 64 * (B + 2)];
     stage_null_splat<B, false>(s_p, s_q);
-    if (!COUNT && threadIdx.x == 0) s_at[B] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (threadIdx.x == 0) s_at[B] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const uint32_t tile = tile_order[blockIdx.x];
     const uint32_t vi = view_of_tile(views, n_views, tile);
     const ViewDev& V = views[vi];
@@ -1966,9 +1966,10 @@ __global__ __launch_bounds__(TW * TH, 8) void k_render_fwd(const ViewDev* __rest
     const char* sa = reinterpret_cast<const char*>(s_at);
     const uint2 rg = ranges[tile];
     float T = inside ? 1.0f : -1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, dd = 0.0f, uu = 0.0f;
-    uint32_t last = 0, ncontrib = 0;
+    uint32_t last = 0;
+    uint64_t contrib = 0;  // of the wave's pixels
     for (uint32_t b = rg.x; b < rg.y; b += B) {
-        if (__syncthreads_count(T > 0.0f) == 0) break;
+        if (__builtin_amdgcn_readfirstlane(__syncthreads_count(T > 0.0f)) == 0) break;
         uint32_t idx = b + threadIdx.x;
         bool opaque = false;
         if (threadIdx.x < (uint32_t)B && idx < rg.y) {
@@ -1978,7 +1979,7 @@ __global__ __launch_bounds__(TW * TH, 8) void k_render_fwd(const ViewDev* __rest
             s_pb[threadIdx.x] = e.pbox;
             opaque = e.g1.w > amax;
             stage_splat<false>(e, ox, oy, st, s_p[threadIdx.x], s_q[threadIdx.x]);
-            if (!COUNT) s_at[threadIdx.x] = rec.attr[r];
+            s_at[threadIdx.x] = rec.attr[r];
         }
         const bool clamped = __builtin_amdgcn_readfirstlane(__syncthreads_or(opaque));
         const int cnt = (int)min<uint32_t>(B, rg.y - b);
@@ -1990,6 +1991,7 @@ __global__ __launch_bounds__(TW * TH, 8) void k_render_fwd(const ViewDev* __rest
         __syncthreads();  // the wave's list is in LDS
         // LDS offset of the last splat this lane took in this batch
         uint32_t lastoff = 0xffffffffu;
+        uint32_t taken = 0;  // contributors among the wave's pixels and this batch's splats, in a scalar register
         auto walk = [&](auto clamp) {
             for (int i = 0; i < nl && alive; i += FWD_STEP) {
                 uint32_t ko[FWD_STEP];
@@ -2019,24 +2021,21 @@ __global__ __launch_bounds__(TW * TH, 8) void k_render_fwd(const ViewDev* __rest
                     const float Tn = fmaf(-a0, T, T);
                     const bool live = Tn >= tmin;
                     const bool use = ok & live;
-                    if constexpr (COUNT) {
-                        ncontrib += use ? 1u : 0u;
-                    } else {
-                        // weight 0 where the splat is skipped (a0 = 0) or the pixel
-                        // stops: fmaf(x, 0, c) = c for the finite staged attributes,
-                        // so the sums need no per-channel select
-                        const float w = live ? a0 * T : 0.0f;
-                        const float4 at = *reinterpret_cast<const float4*>(sa + ko[q]);
-                        c0 = fmaf(at.x, w, c0);
-                        c1 = fmaf(at.y, w, c1);
-                        c2 = fmaf(at.z, w, c2);
-                        dd = fmaf(at.w, w, dd);
-                        if (UNC) {
-                            const float uk = *reinterpret_cast<const float*>(sq + ko[q] + 8);
-                            uu = fmaf(uk, w, uu);
-                        }
-                        lastoff = use ? ko[q] : lastoff;
+                    if (COUNT) taken += (uint32_t)__popcll(__ballot(ok) & __ballot(live));
+                    // weight 0 where the splat is skipped (a0 = 0) or the pixel
+                    // stops: fmaf(x, 0, c) = c for the finite staged attributes,
+                    // so the sums need no per-channel select
+                    const float w = live ? a0 * T : 0.0f;
+                    const float4 at = *reinterpret_cast<const float4*>(sa + ko[q]);
+                    c0 = fmaf(at.x, w, c0);
+                    c1 = fmaf(at.y, w, c1);
+                    c2 = fmaf(at.z, w, c2);
+                    dd = fmaf(at.w, w, dd);
+                    if (UNC) {
+                        const float uk = *reinterpret_cast<const float*>(sq + ko[q] + 8);
+                        uu = fmaf(uk, w, uu);
                     }
+                    lastoff = use ? ko[q] : lastoff;
                     T = live ? Tn : -fabsf(T);
                     if (q + 1 == FWD_STEP) alive = __ballot(live);
                 }
@@ -2044,16 +2043,14 @@ __global__ __launch_bounds__(TW * TH, 8) void k_render_fwd(const ViewDev* __rest
         };
         if (clamped) walk(BoolC<true>{});
         else walk(BoolC<false>{});
-        if (!COUNT && lastoff != 0xffffffffu) last = b - rg.x + 1 + lastoff / (uint32_t)sizeof(float4);
+        if (COUNT) contrib += (uint32_t)__builtin_amdgcn_readfirstlane((int)taken);
+        if (lastoff != 0xffffffffu) last = b - rg.x + 1 + lastoff / (uint32_t)sizeof(float4);
     }
+    if (COUNT && lane_id() == 0) out.contrib[(uint64_t)tile * (NT / 64) + (threadIdx.x >> 6)] = contrib;
     if (!inside) return;
     T = fabsf(T);
     const uint64_t P = (uint64_t)W * H;
     const uint64_t pix = V.pix_off + (uint64_t)v * W + u;
-    if constexpr (COUNT) {
-        out.n_contrib[pix] = ncontrib;
-        return;
-    }
     if (out.rgb) {
         float* base = out.rgb + 3 * V.pix_off + (uint64_t)v * W + u;
         base[0] = c0;
@@ -2879,15 +2876,14 @@ __global__ __launch_bounds__(256) void k_export_records(const uint32_t* __restri
     }
 }
 
-__global__ __launch_bounds__(256) void k_sum_u32_pair(const uint32_t* __restrict__ a,
-                                                      const uint32_t* __restrict__ b, uint64_t n,
-                                                      unsigned long long* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_sum_counts(const uint64_t* __restrict__ a, uint64_t na,
+                                                    const uint32_t* __restrict__ b, uint64_t nb,
+                                                    unsigned long long* __restrict__ out) {
     __shared__ unsigned long long ws[2][4];
     unsigned long long sa = 0, sb = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-        sa += a[i];
-        sb += b[i];
-    }
+    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = i0; i < na; i += stride) sa += a[i];
+    for (uint64_t i = i0; i < nb; i += stride) sb += b[i];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         sa += __shfl_xor(sa, o, 64);
@@ -3710,15 +3706,15 @@ void render_forward(int tw, int th, int batch, const ViewDev* views, int n_views
                     uint32_t tiles_total, const uint2* ranges, const uint32_t* tile_order, const uint32_t* inst_rec,
                     Records rec, SetDev st, RenderOut out, const uint32_t* flags, hipStream_t s) {
     if (tiles_total == 0) return;
-    if (out.n_contrib) {
-        RTG_TILE_DISPATCH(TW, TH, (k_render_fwd<TW, TH, TW * TH, false, true><<<tiles_total, TW * TH, 0, s>>>(
-                                      views, n_views, ranges, tile_order, inst_rec, rec, st, out, flags)));
+    auto launch = [&](auto kernel) {
+        kernel<<<tiles_total, tw * th, 0, s>>>(views, n_views, ranges, tile_order, inst_rec, rec, st, out, flags);
+    };
+    if (!out.contrib) {  // captured iterations, which composite no uncertainty
+        RTG_BATCH_DISPATCH(TW, TH, B, (launch(k_render_fwd<TW, TH, B, false, false>)));
     } else if (out.unc) {
-        RTG_BATCH_DISPATCH(TW, TH, B, (k_render_fwd<TW, TH, B, true><<<tiles_total, TW * TH, 0, s>>>(
-                                          views, n_views, ranges, tile_order, inst_rec, rec, st, out, flags)));
+        RTG_BATCH_DISPATCH(TW, TH, B, (launch(k_render_fwd<TW, TH, B, true, true>)));
     } else {
-        RTG_BATCH_DISPATCH(TW, TH, B, (k_render_fwd<TW, TH, B, false><<<tiles_total, TW * TH, 0, s>>>(
-                                          views, n_views, ranges, tile_order, inst_rec, rec, st, out, flags)));
+        RTG_BATCH_DISPATCH(TW, TH, B, (launch(k_render_fwd<TW, TH, B, false, true>)));
     }
 }
 
@@ -3822,9 +3818,10 @@ void score_reduce(const ViewDev* views, const Header* hdr, int n_views_cap, cons
     k_score_reduce<<<n_views_cap, 256, 0, s>>>(views, hdr, partial, scores, flags, flag_host);
 }
 
-void sum_u32_pair(const uint32_t* a, const uint32_t* b, uint64_t n, unsigned long long* out, hipStream_t s) {
+void sum_counts(const uint64_t* a, uint64_t na, const uint32_t* b, uint64_t nb, unsigned long long* out, hipStream_t s) {
+    const uint64_t n = std::max(na, nb);
     if (n == 0) return;
-    k_sum_u32_pair<<<grid_for(n, 256, 2048), 256, 0, s>>>(a, b, n, out);
+    k_sum_counts<<<grid_for(n, 256, 2048), 256, 0, s>>>(a, na, b, nb, out);
 }
 
 void uncertainty_update(int64_t n, const float* prev, const float* cur, const float* u_prev, int squared,
