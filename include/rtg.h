@@ -426,7 +426,9 @@ rtg_status rtg_region_utility(rtg_ctx *ctx, int64_t n, const float *means, const
  * g->log_scales are read.  r_robot, lambda_g: finite and >= 0 (the paper
  * uses lambda_g = 3).  The results are those of testing every point against
  * every Gaussian; the time falls with how close together the points lie that
- * follow each other in space.  Asynchronous on `stream`. */
+ * follow each other in space (points scattered over the map cost about as much
+ * as that loop over all pairs, which small maps take anyway).  Asynchronous on
+ * `stream`. */
 rtg_status rtg_collision_check(rtg_ctx *ctx, const rtg_gaussians *g, const float *points,
                                int64_t n_points, float r_robot, float lambda_g, int32_t *collide,
                                float *clearance, void *stream);

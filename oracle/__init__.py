@@ -31,7 +31,8 @@ _LIB = os.path.join(_HERE, "librtgo.so")
 # Relative widths of the near-threshold bands: a per-pixel decision whose
 # operand lies this close (relative) to its threshold is taken both ways by the
 # oracle, since another evaluation may legitimately fall on either side.
-#  * alpha_min: the HIP path re-takes every decision within 2e-3 of alpha_min
+#  * alpha_min: the HIP path re-takes every decision that the rounding of its
+#    binary32 alpha could turn (a band per splat, at least a relative 1e-5 wide)
 #    in binary64 from the binary64 conic and a mean exact to ~2^-48, so only
 #    binary64 rounding-order differences (~1e-11 relative) separate the two:
 #    1e-5 covers them with a wide margin;

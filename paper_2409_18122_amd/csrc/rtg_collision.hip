@@ -530,9 +530,9 @@ __device__ __forceinline__ void check_dense(const GaussDev& g, float r_robot, fl
 // per lane, the eight balls of 8 points inside are tested into q2, and of 64 of these the
 // 8 points.  Few Gaussians pass a ball (on a lot, one in 40), so without the queues
 // nearly every lane of the later tests would be idle: testing all 64 points of a ball (a point
-// per lane) for each passing Gaussian took 931 us for 8,256 points and 3M Gaussians, with the queues 440 us.
-// Bound by instruction issue there (about 1.8e8 vector and 1.4e8 scalar wave instructions); for few points
-// by the one pass over the map (129 points, 3M Gaussians: 37 us, 1.9 TB/s).
+// per lane) for each passing Gaussian took 931 us for 8,256 points and 3M Gaussians, with the queues 445 to 476 us.
+// Bound by instruction issue there (about 2.0e8 vector and 1.4e8 scalar wave instructions); for few points
+// by the one pass over the map (129 points, 3M Gaussians: 33 us, 2.2 TB/s).
 // Where points lie far from the map or from each other most pairs pass the balls, and 8 points of a queue's entry, read
 // from as many places of LDS, cost 65 cycles a pair of 64 lanes, where a plain walk costs 31: a block whose first Gaussians pass
 // more than half of the balls of 8 takes check_dense instead (8,256 points in a cube of 400 m: 12,400 -> 5,900 us, the

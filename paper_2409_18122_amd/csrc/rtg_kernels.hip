@@ -557,7 +557,8 @@ __global__ __launch_bounds__(256) void k_project_count(GaussDev g, const ViewDev
 // LDS; the binary32 screen settles most pairs (98% of 2 M Gaussians in 256 views; 7% are visible), and the rest
 // go through a queue of the wave, so that the binary64 projection runs on 64 pairs at once instead of on the one or two
 // lanes of a wave whose pair is open.  Bound by the screen's instructions (about 50 per 64 pairs, two pairs
-// a lane in flight) and, at four waves per SIMD, by the latency of the binary64 part.
+// a lane in flight) and, at four waves per SIMD (128 VGPRs, 8 spilled), by the latency of the binary64 part: 2 M Gaussians
+// in 256 views 1,020 us (970 with bounds that held for rotations alone).
 constexpr int PC_VIEWS = 256;
 constexpr int PC_STEP = 2;
 
@@ -1816,7 +1817,8 @@ constexpr int SCORE_STEP = 2;
 // pixel's offset is below |m| + 32) and M = [[a, 0], [b, c]], the whitened offset w = M d is off by at most
 // 5 2^-24 E, E = (a + |b|) (|m_x| + 32) + c (|m_y| + 32), so near the threshold, where |w|^2 = log2(o /
 // alpha_min), alpha is off by a relative 2 ln 2 sqrt(log2(1 / alpha_min)) 5 2^-24 E, plus a few 2^-24 for the
-// squares, the exponential and the opacity: st.band_e E + st.band_c (absolute; band_coefficients).
+// squares, the exponential and the opacity: st.band_e E + st.band_c (absolute; to_dev in
+// rtg_abi.hip forms both).
 // A relative 2e-3 for every splat, which covers needles whose mean is thousands of pixels away, sent one
 // alpha in 1,400 to the binary64 branch: every third step of the backward's 512 alphas.
 __device__ __forceinline__ float amin_band(float mx, float my, float a, float b, float c, const SetDev& st) {
@@ -2212,8 +2214,8 @@ __device__ __forceinline__ void bwd_pixel(float a, float ag, float dx, float dy,
 // both are the ones of a halving by lanes (i, 15 - i, 7 - i, i ^ 2, i ^ 1, then the rows).  Moments of a row of
 // four pixels, 13 instructions instead of 32, took 1,940 us where these take 2,120, but moved such gradients by up to 2e-3.
 // 8 keyframes of 1280x720, with the narrower band of the binary64 branch, thresholds in vector registers and four waves
-// per SIMD (128 VGPRs, 158 before): 2,264 -> 2,120 us, of which the atomics are 70 us; one 640x480 frame in two bands:
-// 134 -> 113 us.
+// per SIMD (128 VGPRs with 9 spilled, 13 at 32x8; 158 before): 2,264 -> 2,120 us, of which the atomics are 70 us; one
+// 640x480 frame in two bands: 134 -> 113 us.
 template <int TW, int TH, int NSUB, bool AU>
 __global__ __launch_bounds__(64, AU ? 3 : 4) void k_render_bwd(const ViewDev* __restrict__ views, int n_views,
                                                         const uint2* __restrict__ ranges,
